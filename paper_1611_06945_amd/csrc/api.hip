@@ -77,6 +77,8 @@ State& state()
         register_pwin32_f32(s->variants);
         register_pwin_f16(s->variants);
         register_pwin_bf16(s->variants);
+        register_bwin_f16(s->variants);
+        register_bwin_bf16(s->variants);
         for (size_t i = 0; i < s->variants.size(); ++i) s->by_name[s->variants[i].name] = (int)i;
         return s;
     }();
@@ -265,6 +267,22 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double busy = tiles * waves * mfmas * 0.0305 / 1024.0 / 0.5;
         return 5.0 + 0.05 * waves + std::max(rounds * mfmas * 0.030 * std::max(1.0, waves / 4.0), busy);
     }
+    if (v.traits & TRAIT_BIG_WINDOW) {
+        // two workgroups per CU (one where the slab takes more than half of LDS), each 2.5 us + its output tile's share for
+        // start and store and its MFMAs (8 clocks of the CU each) at the rate two co-resident workgroups reach; the last,
+        // incomplete round runs with one workgroup on most CUs.  Measured on 64 images of 56x56x64 -> 192: workgroups of
+        // 64 x 512 live 17.3 us (model 17.5), of 64 x 256 9.5 us (9.7)
+        const double tiles = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn);
+        const double steps = std::ceil(d.C / 16.0) * d.R * d.S;
+        const double t_mfma = (v.tm / 32.0) * (v.tn / 32.0) * steps * 8.0 / 2100.0;
+        const double own = 2.5 + 4.0 * v.tm * v.tn / 32768.0;
+        const double slots = 256.0 * v.per_cu, full = std::floor(tiles / slots), part = tiles / slots - full;
+        const double alone = own + t_mfma / 0.6, round = v.per_cu == 2 ? own + 2.0 * t_mfma / 0.8 : alone;
+        double t = 2.5 + full * round;
+        if (part > 0.0) t += part > 0.5 ? round : alone;
+        if (v.traits & TRAIT_CONVERTS_FIRST) t += 3.0 + 2.0 * ((double)d.N * d.C * d.H * d.W + (double)d.K * Q) * 2.0 / 6.0e6;
+        return t;
+    }
     const bool window = v.family == FAM_WINDOW || (v.traits & TRAIT_WINDOW_TILES);
     double tiles;
     if (window) {  // one workgroup per (image, band of pixels, channel tile): pixels are not packed across images
@@ -382,6 +400,8 @@ void fill_args(ConvArgs& a, const conv_desc& d, int OH, int OW, const void* in, 
     a.POH = a.pool ? (OH - 3) / 2 + 1 : 0;
     a.POW = a.pool ? (OW - 3) / 2 + 1 : 0;
     if (a.pool) a.out_bytes = (uint32_t)((uint64_t)d.N * d.K * a.POH * a.POW * dtype_size(d.dtype));
+    a.order = 0;
+    a.blk_stride = 0;
     a.nsplit = 1;
     a.steps_per_split = 0;
     a.dRS = make_fastdiv((uint32_t)a.RS);

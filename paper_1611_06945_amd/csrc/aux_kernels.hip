@@ -427,6 +427,79 @@ __global__ __launch_bounds__(256) void prep16_kernel(const uint16_t* __restrict_
     pack_block16(filt, filt_out, K, C, RS, b - in_blocks, pack_lds);
 }
 
+// The filters of one (row block, 16-channel group) as pack_block16, for any channel count: rows are fetched element by
+// element (their pieces start at any 2-byte boundary) and channels past C are zero.
+__device__ __forceinline__ void pack_block16_any(const uint16_t* __restrict__ filt, uint4* __restrict__ out, int K, int C, int RS,
+                                                 int blk, uint16_t* lds)
+{
+    const int C16 = (C + 15) >> 4, rb = blk / C16, c16 = blk - rb * C16;
+    const int pitch = 16 * RS + 8, piece = 16 * RS;
+    const int have = (C - c16 * 16 < 16 ? C - c16 * 16 : 16) * RS;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int row = wave; row < 32; row += 4) {
+        const int k = rb * 32 + row;
+        const uint16_t* src = filt + ((size_t)k * C + c16 * 16) * RS;
+        for (int q = lane; q < piece; q += 64) lds[row * pitch + q] = (k < K && q < have) ? src[q] : (uint16_t)0;
+    }
+    __syncthreads();
+    uint4* dst = out + (size_t)blk * RS * 64;
+    for (int v = threadIdx.x; v < 64 * RS; v += 256) {
+        const int m = v & 31, g = (v >> 5) & 1, t = v >> 6;
+        const uint16_t* src = &lds[m * pitch + g * 8 * RS + t];
+        uint32_t w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = (uint32_t)src[2 * j * RS] | ((uint32_t)src[(2 * j + 1) * RS] << 16);
+        dst[v] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
+
+// Conversion launch of the many-pixel window kernel: blocks [0, filt_blocks) write the filters in MFMA operand order (one
+// row block and channel group each), the others write 256 positions of one 16-channel group of the input copy: a thread
+// reads its position's 16 channels (2-byte loads, consecutive lanes on consecutive pixels of a plane, all 16 in flight)
+// and writes them as 32 contiguous bytes.  Memory bound: input read once, copy written once.
+__global__ __launch_bounds__(256) void prep_blk16_kernel(const uint16_t* __restrict__ in, uint4* __restrict__ copy, int N, int C, int H,
+                                                        int W, int pad, uint32_t NP, int pos_blocks, FastDiv dPB, FastDiv dPW, FastDiv dPH,
+                                                        const uint16_t* __restrict__ filt, uint4* __restrict__ filt_out, int K, int RS,
+                                                        int filt_blocks)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t pack_lds[];
+    const int b = blockIdx.x;
+    if (b < filt_blocks) {
+        if ((C & 15) == 0)
+            pack_block16(filt, filt_out, K, C, RS, b, pack_lds);
+        else
+            pack_block16_any(filt, filt_out, K, C, RS, b, pack_lds);
+        return;
+    }
+    uint32_t c16, pb;
+    dPB.divmod((uint32_t)(b - filt_blocks), c16, pb);
+    const uint32_t pos = pb * 256u + threadIdx.x;
+    if (pos >= NP) return;
+    uint32_t Y, X, n, yy;
+    dPW.divmod(pos, Y, X);
+    dPH.divmod(Y, n, yy);
+    const bool inside = (int)X >= pad && (int)X < pad + W && (int)yy >= pad && (int)n < N;
+    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (inside) {
+        const size_t HW = (size_t)H * W;
+        const int c0 = (int)c16 * 16;
+        const uint16_t* src = in + ((size_t)n * C + c0) * HW + (size_t)((int)yy - pad) * W + ((int)X - pad);
+        uint16_t h[16];
+        if (c0 + 16 <= C) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) h[j] = src[j * HW];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) h[j] = c0 + j < C ? src[j * HW] : (uint16_t)0;
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = (uint32_t)h[2 * j] | ((uint32_t)h[2 * j + 1] << 16);
+    }
+    uint4* dst = copy + ((size_t)c16 * NP + pos) * 2;
+    dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+    dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+}
+
 static size_t pack_lds_bytes(int RS) { return sizeof(uint16_t) * 32 * (size_t)(16 * RS + 8); }
 
 hipError_t launch_pack_filters16(const void* filt, void* out, int K, int C, int RS, hipStream_t s)
@@ -456,6 +529,21 @@ hipError_t launch_prep16(const void* in, void* in_out, int N, int C, int HW, con
     const size_t lds = std::max(pack_lds_bytes(RS), sizeof(uint16_t) * 32 * 33);
     hipLaunchKernelGGL(prep16_kernel, dim3((unsigned)blocks), dim3(256), lds, s, (const uint16_t*)in, (uint16_t*)in_out, C, HW,
                        tiles_s, tiles_c, (int)in_blocks, (const uint16_t*)filt, (uint4*)filt_out, K, RS);
+    return hipGetLastError();
+}
+
+hipError_t launch_prep_blk16(const void* in, void* in_out, int N, int C, int H, int W, int pad, const void* filt, void* filt_out,
+                             int K, int RS, hipStream_t s)
+{
+    if (RS > kPackMaxRS) return hipErrorInvalidValue;
+    const int C16 = (C + 15) / 16;
+    const long long np = ((long long)N * (H + pad) + pad) * (W + pad) + pad;
+    const long long pos_blocks = (np + 255) / 256, filt_blocks = (long long)((K + 31) / 32) * C16;
+    const long long blocks = pos_blocks * C16 + filt_blocks;
+    if (np > 0x7fffffffLL || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(prep_blk16_kernel, dim3((unsigned)blocks), dim3(256), pack_lds_bytes(RS), s, (const uint16_t*)in, (uint4*)in_out,
+                       N, C, H, W, pad, (uint32_t)np, (int)pos_blocks, make_fastdiv((uint32_t)pos_blocks), make_fastdiv((uint32_t)(W + pad)),
+                       make_fastdiv((uint32_t)(H + pad)), (const uint16_t*)filt, (uint4*)filt_out, K, RS, (int)filt_blocks);
     return hipGetLastError();
 }
 

@@ -81,6 +81,8 @@ struct ConvArgs {
     int pool;      // 3x3 stride-2 max-pool fused behind the activation: out is [N][K][POH][POW] (or channel-innermost)
     int POH, POW;  // pooled extent (0 without pool)
     uint32_t in_bytes, filt_bytes, out_bytes;  // extents for the hardware bounds check of tile loads
+    int order;            // tile order (set by the launcher): 1 = channel tiles of one pixel tile are consecutive
+    uint64_t blk_stride;  // bytes of one 16-channel group of a blocked input copy (set by the launcher)
     int nsplit;           // number of reduction splits (gridDim.z)
     int steps_per_split;  // reduction steps (of the kernel's own step size) per split
     FastDiv dRS, dS, dOHW, dOW, dHW, dW;
@@ -107,6 +109,7 @@ struct Variant {
     LaunchFn launch;
     WorkspaceFn ws_extra = nullptr;  // workspace the variant needs beyond split partial sums (null: none)
     unsigned traits = 0;             // TRAIT_* bits read by the cost model used when no measurement exists
+    int per_cu = 1;                  // workgroups that share a CU, for the families whose cost model asks
 };
 
 enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no alignment demands, slower steps)
@@ -120,6 +123,7 @@ enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no a
        TRAIT_PACKED_FILTERS = 256u,    // reads filters in MFMA operand order (CONV_FLAG_FILT_PACKED); checks the tensor formats itself
        TRAIT_CONVERTS_FIRST = 512u,    // serves the plain formats by converting input and filters into the workspace first
        TRAIT_WAVE_SPLIT = 1024u,       // the waves of a workgroup split the reduction of one tile (v.threads / 64 ways), operands from global memory
+       TRAIT_BIG_WINDOW = 4096u,       // 16-bit window kernel whose waves own their outputs (many-pixel layers)
        TRAIT_CHANNEL_WAVES = 2048u };  // fp32 window kernel on linear pixel tiles whose waves split the channels of a chunk
 
 enum { FAM_IGEMM = 0, FAM_POINTWISE = 1, FAM_FIRSTLAYER = 2, FAM_WINDOW = 3, FAM_FC = 4, FAM_NHWC = 5, FAM_WINOGRAD = 6 };
@@ -150,6 +154,8 @@ void register_pwk_bf16(std::vector<Variant>& out);
 void register_pwin32_f32(std::vector<Variant>& out);
 void register_pwin_f16(std::vector<Variant>& out);
 void register_pwin_bf16(std::vector<Variant>& out);
+void register_bwin_f16(std::vector<Variant>& out);
+void register_bwin_bf16(std::vector<Variant>& out);
 
 // Raises a kernel's dynamic-LDS limit to `bytes` on the current device when it is not already that high (once per
 // device and kernel; safe to call from several threads).
@@ -168,6 +174,10 @@ size_t wino_transformed_filter_bytes(int K, int C);
 // input [N][C][HW] -> [N][HW][C] and filters -> MFMA operand order in one launch (aux_kernels.hip); C % 16 == 0
 hipError_t launch_prep16(const void* in, void* in_out, int N, int C, int HW, const void* filt, void* filt_out, int K, int RS,
                          hipStream_t s);
+// input [N][C][H][W] -> [C/16][position][16] with zero borders (the position space of bwin_kernel.h) and filters -> MFMA
+// operand order, in one launch; any C (padded to a multiple of 16 with zeros on both sides)
+hipError_t launch_prep_blk16(const void* in, void* in_out, int N, int C, int H, int W, int pad, const void* filt, void* filt_out,
+                             int K, int RS, hipStream_t s);
 hipError_t launch_pack_filters16(const void* filt, void* out, int K, int C, int RS, hipStream_t s);
 
 // max_i |got_i - ref_i| / max(max_j |ref_j|, 1e-30) of two device tensors of `n` elements (infinity when `got` holds a
