@@ -54,15 +54,21 @@ TOL = {"f32": 1e-5, "f16": 5e-3, "bf16": 5e-3}   # max normalised error allowed 
 
 def executed_mfma_flops(variant, shape):
     """FLOPs the matrix units execute per call: the direct count, except for the Winograd variants, which multiply
-    2.25x less (on tiles padded to the workgroup shape)."""
+    2.25x less (on tiles padded to the workgroup shape), winos_* as six bf16 partial products each."""
     import re
 
-    m = re.match(r"wino_f32_M(\d+)T(\d+)_", variant)
+    m = re.match(r"winos?_f32_M(\d+)T(\d+)_", variant)
     if not m:
         return float(shape.flops)
     tm, tt = int(m.group(1)), int(m.group(2))
     tiles = shape.N * ((shape.OH + 1) // 2) * ((shape.OW + 1) // 2)
-    return 2.0 * 16 * (-(-shape.K // tm) * tm) * (-(-tiles // tt) * tt) * shape.C
+    once = 2.0 * 16 * (-(-shape.K // tm) * tm) * (-(-tiles // tt) * tt) * shape.C
+    return 6.0 * once if variant.startswith("winos_") else once
+
+
+def mfma_dtype(variant, dt):
+    """The type whose matrix rate bounds a variant: that of the storage, except for fp32 products made of bf16 parts."""
+    return "bf16" if variant.startswith("winos_") else dt
 
 
 class Resident:
@@ -298,7 +304,7 @@ def layer_report(w, launches=100, batches=5, rotate_mb=0, fmt="nchw", cpu=True, 
         "gflops": round(w.shape.flops / (med * 1e-3) / 1e9, 1),
         # fraction of the MFMA peak the matrix units really sustain (never above 1); for a Winograd variant the rate by
         # the paper's FLOP convention (FLOPs of the direct definition) is the separate `effective_frac_direct_flops`
-        "frac_mfma_peak": round(executed / (med * 1e-3) / (PEAK_TFLOPS[dt] * 1e12), 5),
+        "frac_mfma_peak": round(executed / (med * 1e-3) / (PEAK_TFLOPS[mfma_dtype(variant, dt)] * 1e12), 5),
         "hbm_gbs_algorithmic": round(abytes / (med * 1e-3) / 1e9, 1),
         "frac_hbm_peak": round(abytes / (med * 1e-3) / (PEAK_HBM_GBS * 1e9), 5),
         "flops": w.shape.flops, "algorithmic_bytes": abytes,
@@ -457,7 +463,7 @@ def sweep_appendix_a(batch, dtype, table_out=None, launches=100, batches=5):
             # a Winograd variant: the fraction of the MFMA peak counts the FLOPs the matrix units execute (never above 1);
             # the rate by the direct definition's FLOP count stays in `gflops` and `effective_frac_direct_flops`
             ops[-1]["effective_frac_direct_flops"] = ops[-1]["frac_roofline"]
-            ops[-1]["frac_roofline"] = round(executed / (PEAK_TFLOPS[dt] * 1e12) / (med * 1e-3), 5)
+            ops[-1]["frac_roofline"] = round(executed / (PEAK_TFLOPS[mfma_dtype(chosen, dt)] * 1e12) / (med * 1e-3), 5)
         if ops[-1]["bound"] == "hbm":
             # stream-bound operation: repeat over enough distinct tensor sets to defeat the 256 MB last-level cache
             copies = max(2, int(600e6 / abytes) + 1)
@@ -651,8 +657,8 @@ def main():
         # a Winograd variant that is 2.25x fewer FLOPs than the direct definition's; the rate by the paper's FLOP
         # convention (how it also rates the vendor library's Winograd kernels) is `effective_*_direct_flops`.
         ach = executed / (kern_ms * 1e-3) / 1e12
-        roof = {"bound": "mfma", "achieved": round(ach, 3), "peak": PEAK_TFLOPS[dt], "unit": "TFLOP/s",
-                "frac": round(ach / PEAK_TFLOPS[dt], 5), "flops_counted": "executed by the matrix units",
+        roof = {"bound": "mfma", "achieved": round(ach, 3), "peak": PEAK_TFLOPS[mfma_dtype(variant, dt)], "unit": "TFLOP/s",
+                "frac": round(ach / PEAK_TFLOPS[mfma_dtype(variant, dt)], 5), "flops_counted": "executed by the matrix units",
                 "mfma_flops_executed": executed, "algorithmic_flops": w.shape.flops,
                 "effective_tflops_direct_flops": round(w.shape.flops / (kern_ms * 1e-3) / 1e12, 3),
                 "effective_frac_direct_flops": round(w.shape.flops / (kern_ms * 1e-3) / 1e12 / PEAK_TFLOPS[dt], 5)}
@@ -669,19 +675,21 @@ def main():
     for code, name in ((wl.F32, "f32"), (wl.F16, "f16"), (wl.BF16, "bf16")):
         measured["mfma_tflops"][name] = round(max(B.conv_probe_mfma_peak(code, 32, scratch), B.conv_probe_mfma_peak(code, 16, scratch)), 1)
     del big, big2
-    roof["frac_of_measured"] = round(ach / (measured["mfma_tflops"][dt] if mfma_bound else measured["stream_copy_gbs"]), 5)
+    roof["frac_of_measured"] = round(ach / (measured["mfma_tflops"][mfma_dtype(variant, dt)] if mfma_bound else measured["stream_copy_gbs"]), 5)
     roof["traffic"] = stored_traffic("%s|%s" % (w.name, variant))
     roof["kernel"] = variant
     roof["kernel_ms"] = round(kern_ms, 6)
-    if variant.startswith("wino_") and not a.variant:
+    if variant.startswith(("wino_", "winos_")) and not a.variant:
         # next to the fastest direct variant the tuner measured, and the same layer with pre-transformed filters
         sh = w.shape
         fused = variant.endswith("_ff")
         roof["algorithm"] = ("winograd F(2x2,3x3): one kernel per launch (filter, input and output transforms around the MFMA planes)"
                              if fused else "winograd F(2x2,3x3): filter transform kernel + fused product kernel per launch")
+        if variant.startswith("winos_"):
+            roof["algorithm"] += "; fp32 products as six bf16 partial products (operands split into three parts)"
         n = B.conv_variant_count(r.desc)
         direct = [(B.conv_variant_time_us(r.desc, i), B.conv_variant_name(r.desc, i)) for i in range(n)]
-        direct = [x for x in direct if not x[1].startswith("wino_") and x[0] > 0]
+        direct = [x for x in direct if not x[1].startswith(("wino_", "winos_")) and x[0] > 0]
         # the same layer with the filters handed over in the Winograd domain (the transform is then a conversion done
         # once, ahead of time, as the paper does for constant weights): an extra figure, never the headline value
         pre = B.desc_of(sh, w.dtype, relu=True, filt_winograd=True)

@@ -65,6 +65,7 @@ State& state()
         register_nwin_bf16(s->variants);
         register_wconv_f32(s->variants);
         register_wino_f32(s->variants);
+        register_winos_f32(s->variants);
         register_swin_f16(s->variants);
         register_swin_bf16(s->variants);
         register_swinp_f16(s->variants);
@@ -211,6 +212,19 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
 {
     const double P = (double)d.N * OH * OW, Q = (double)d.C * d.R * d.S;
     if (v.family == FAM_FC) return 1.0 + std::abs(v.tm - 4);  // weight streaming: always ahead of the MFMA tiles when valid
+    if (v.traits & TRAIT_SPLIT_PRODUCTS) {
+        // Winograd on split products: v.tm / 32 blocks of 32 channels; a workgroup costs its start, planes and stores and a
+        // step per 16 channels.  v.per_cu of them share a CU, to no gain in time per workgroup.  Measured (model): 20 images
+        // of 13x13x256 -> 384 with M32 / M64 / M96 44 / 37 / 42 us (44 / 38 / 47), 64 of 56x56x64 -> 192 350 / 254 / 218 (366 /
+        // 246 / 212).
+        const double mb = v.tm / 32.0, tiles = (double)d.N * std::ceil(OH / 2.0) * std::ceil(OW / 2.0);
+        const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(tiles / (v.tn / 4.0));
+        const double own = 4.5 + 1.2 * mb, t_step = 0.45 + 0.5 * mb, slots = 256.0 * v.per_cu;
+        const double share = std::min((double)v.per_cu, std::max(1.0, std::ceil(wgs / 256.0)));
+        // (unmeasured, it has to be well ahead, by more than the errors of the two models together on layers of one or two rounds:
+        // it asks for half as much workspace again)
+        return 1.35 * (2.0 + 4.5 + 2.2e-5 * (double)d.K * d.C + std::ceil(wgs / slots) * share * (own + std::ceil(d.C / 16.0) * t_step));
+    }
     if (v.family == FAM_WINOGRAD) {
         // F(2x2,3x3) product kernel: one workgroup per (v.tm channels, v.tn / 4 tiles of 2x2 outputs), one round per 256
         // workgroups, a step per v.tk / 9 input channels whose cost grows with the products and with the operands it
@@ -223,7 +237,9 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         double t_filters = 4.15 + 0.49e-5 * (double)d.K * d.C;
         if (v.traits & TRAIT_FILTERS_IN_KERNEL) t_filters = 0.0, t_step *= 1.12;
         if (d.flags & CONV_FLAG_FILT_WINOGRAD) t_filters = 0.0;
-        return 4.62 + t_filters + rounds * (d.C / cb) * t_step;
+        // (further rounds each pay a workgroup's start and inverse transform again: 64 of 56x56x64 -> 192 takes 340 us in 19
+        // rounds of 12.5 us of steps)
+        return 4.62 + t_filters + rounds * (d.C / cb) * t_step + 5.0 * (rounds - 1.0);
     }
     if (v.family == FAM_FIRSTLAYER && (v.traits & TRAIT_POOL_EPILOGUE)) {
         // one workgroup per tile of pooled outputs and channel tile, one per CU at a time: filters re-laid, input rows

@@ -1,0 +1,542 @@
+// Winograd F(2x2, 3x3) for fp32 3x3 stride-1 layers with its products on the 16-bit matrix units.
+//
+// The transforms are those of wino_kernel.h; the 16 products M[xi][k][t] = sum_c U[xi][k][c] * V[xi][c][t] are what bounds
+// that kernel: the fp32 matrix rate of this device is 1/16 of the bf16 one and an fp32 MFMA never overlaps with vector-ALU
+// work.  Here every fp32 operand x is split into three bf16 numbers, x = x0 + x1 + x2 (each the round-to-nearest bf16 of
+// what is left; 3 x 8 significant bits and two signs hold all 24), and a product is the sum of the six partial products
+// down to 2^-16 of the leading one,
+//     u v ~ u0 v0 + u0 v1 + u1 v0 + u1 v1 + u0 v2 + u2 v0,
+// accumulated in fp32 by v_mfma_f32_32x32x16_bf16.  The three left out are below 2^-24 |u v|, and sixteen channels enter
+// the accumulator with one rounding, so that the error is no larger than that of the fp32 kernels (2-norm of the difference
+// to a 64-bit convolution over its 2-norm, half-normal inputs: 13x13x256 -> 384 3.4e-7 against 4.0e-7 for wino_kernel, 4.4e-7
+// for wconv_kernel and 8.6e-7 for the implicit GEMMs; 56x56x64 -> 192 1.7e-7, 2.1e-7, -, 4.3e-7).
+//   * U is split by the filter transform, in MFMA operand order: a wave's fragment is 1 KB, loaded straight into registers.
+//   * V stays fp32 in LDS ([plane][channel quad][tile][4]): a plane belongs to one wave, so splitting it in that wave costs
+//     nothing twice and moves 4 bytes per value through LDS instead of 6.
+//   * A step is 16 channels in two stages, one per plane of a wave, with a barrier behind each.  Under the products of its
+//     first plane a wave splits the second and transforms its task of step i+1; under those of the second it splits the
+//     first plane of step i+1 and writes the input rows of step i+2 to LDS.  One buffer of each kind suffices.  The mix is
+//     asked for instruction by instruction: left alone, the compiler puts the vector work first and the loads last.
+//   * Input rows are fetched 16 bytes per lane, the last vector of a row ending with the row: with 4-byte loads the issue
+//     of the loads alone took 300 .. 1700 clocks of a wave's 4000 per step.  Neighbouring tile rows share their rows.
+// What bounds it: 64 channels x 32 tiles multiply for 1540 of the ~3000 clocks a step takes (LDS traffic ~1000, vector work
+// ~1400 of a SIMD, not all of it underneath); the start (5000 clocks) and the inverse transform (7000) of a workgroup are
+// exposed, with one workgroup per CU.  Tiles of 64 were tried (twice the registers, no room for the two-stage mix: 238 us
+// where 96 x 32 takes 218), and two workgroups of 32 x 32 per CU (vector work per product doubles: 350).
+// Measured (us per call, filter transform included, kernel before -> this one): 20 images of 13x13x256 -> 384 46.0 -> 37.1,
+// 64 of 56x56x64 -> 192 340 -> 218.
+// bf16 has fp32's exponent range, but not its infinities' arithmetic: an overflow or infinity in a split gives NaN, and
+// parts of numbers below 2^-110 can vanish.  An output tile that is not finite, or whose largest value is tiny and not
+// zero, is therefore summed again in fp32 from the definition (a loop that no ordinary layer enters).
+#pragma once
+
+#include "pwin_kernel.h"
+#include "wino_kernel.h"
+
+namespace convfwd {
+
+template <int MB_, int LBV_, int RING_>
+struct WinosCfg {
+    static constexpr int MB = MB_, LBV = LBV_, RING = RING_;
+    static_assert((2 * MB) % RING == 0 && RING >= 2, "the filter ring must divide the groups of a step");
+    static constexpr int NT = 512;        // 8 waves of two planes
+    static constexpr int WPS = MB == 1 && LBV <= 2 ? 4 : 2;  // waves per SIMD the registers are fitted to
+    static constexpr int TM = 32 * MB;    // output channels per workgroup
+    static constexpr int TT = 32;         // tiles (2x2 output blocks) per workgroup: one transform task (tile, channel) per thread
+    static constexpr int V_FLOATS = 16 * 4 * TT * 4;
+    static constexpr int MP = TT + 4;     // row pitch of the plane buffer of the epilogue
+    static constexpr int E_FLOATS = (MB < 2 ? MB : 2) * 16 * 32 * MP;  // two 32-channel blocks at a time
+    static constexpr int SLOTS = NT * LBV;  // 16-byte vectors of input rows staged per step
+};
+
+struct WinosGeom {
+    int TH, TW, tiles;
+    int IR;        // staged rows of an image: 2 * TH + 2
+    int rows_max;  // most rows a workgroup stages
+    int W4;        // 16-byte vectors of a row; the last one ends with the row
+    int PWL;       // floats per staged row
+    int pitch;     // floats per channel of the staged rows, 16 mod 64: the lanes of a transform read distinct banks
+};
+
+template <class CFG>
+__host__ __device__ inline WinosGeom winos_geom(int N, int W, int OH, int OW)
+{
+    WinosGeom g;
+    g.TH = (OH + 1) / 2;
+    g.TW = (OW + 1) / 2;
+    g.tiles = N * g.TH * g.TW;
+    g.IR = 2 * g.TH + 2;
+    const int up = (CFG::TT + g.TW - 2) / g.TW;  // tile rows between a workgroup's first and last tile
+    int cross = (up + g.TH - 1) / g.TH;
+    if (cross > N - 1) cross = N - 1;
+    g.rows_max = 2 * up + 4 + 2 * cross;
+    g.W4 = (W + 3) / 4;
+    g.PWL = 2 * g.TW + 2;
+    g.pitch = g.rows_max * g.PWL;
+    g.pitch += ((16 - g.pitch % 64) + 64) % 64;
+    return g;
+}
+
+template <class CFG>
+size_t winos_lds_bytes(int N, int W, int OH, int OW)
+{
+    const size_t pipe = sizeof(float) * (CFG::V_FLOATS + 16 * (size_t)winos_geom<CFG>(N, W, OH, OW).pitch + 4 * CFG::NT);
+    const size_t epi = sizeof(float) * CFG::E_FLOATS;
+    return pipe > epi ? pipe : epi;
+}
+
+inline size_t winos_filter_bytes(int K, int C) { return (size_t)((C + 15) / 16) * 16 * ((K + 31) / 32) * 3072; }
+
+struct Split3 {
+    uint4 p[3];
+};
+// two fp32 values -> three pairs of bf16 that add up to them
+__device__ __forceinline__ void split3_pair(float a, float b, uint32_t& w0, uint32_t& w1, uint32_t& w2)
+{
+    w0 = Prec<CONV_BF16>::pack2_from_f32(a, b);
+    a -= __builtin_bit_cast(float, w0 << 16);
+    b -= __builtin_bit_cast(float, w0 & 0xffff0000u);
+    w1 = Prec<CONV_BF16>::pack2_from_f32(a, b);
+    a -= __builtin_bit_cast(float, w1 << 16);
+    b -= __builtin_bit_cast(float, w1 & 0xffff0000u);
+    w2 = Prec<CONV_BF16>::pack2_from_f32(a, b);
+}
+// eight fp32 values -> the three MFMA operands
+__device__ __forceinline__ Split3 split3(const float* x)
+{
+    Split3 s;
+    uint32_t w[3][4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) split3_pair(x[2 * j], x[2 * j + 1], w[0][j], w[1][j], w[2][j]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s.p[q] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+    return s;
+}
+
+// Filter transform: U[c / 16][xi][k / 32][part][lane][8], lane = k % 32 + 32 * (c % 16 / 8), 8 channels c % 8.  A
+// workgroup takes 32 filters x 16 channels: their values go to LDS as contiguous runs, then wave w computes planes 2w and
+// 2w+1 of its lanes' eight channels and stores each part as one contiguous kilobyte.
+__global__ __launch_bounds__(512) void winos_filter_kernel(const float* __restrict__ filt, uint4* __restrict__ U, int K, int C)
+{
+    constexpr int ROW = 16 * 9 + 1;  // odd pitch
+    __shared__ float g_s[32 * ROW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int mb = blockIdx.x, c16 = blockIdx.y;
+    const int have = (C - c16 * 16 < 16 ? C - c16 * 16 : 16) * 9;
+    float v[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        const int e = i * 512 + tid, kl = e / 144, j = e - kl * 144;
+        v[i] = (mb * 32 + kl < K && j < have) ? filt[((size_t)(mb * 32 + kl) * C + c16 * 16) * 9 + j] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        const int e = i * 512 + tid, kl = e / 144, j = e - kl * 144;
+        g_s[kl * ROW + j] = v[i];
+    }
+    __syncthreads();
+    const int kl = lane & 31, g8 = lane >> 5, row = wave >> 1;
+    float u[2][8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const float* g = g_s + kl * ROW + (g8 * 8 + c) * 9;
+        float t[3];  // row `row` of G g
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const float g0 = g[j], g1 = g[3 + j], g2 = g[6 + j];
+            t[j] = row == 0 ? g0 : row == 3 ? g2 : 0.5f * ((g0 + g2) + (row == 1 ? g1 : -g1));
+        }
+        const float s = t[0] + t[2];
+        u[0][c] = (wave & 1) ? 0.5f * (s - t[1]) : t[0];
+        u[1][c] = (wave & 1) ? t[2] : 0.5f * (s + t[1]);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const Split3 s = split3(u[j]);
+        uint4* dst = U + (((size_t)c16 * 16 + wave * 2 + j) * gridDim.x + mb) * 192 + lane;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) dst[q * 64] = s.p[q];
+    }
+}
+
+// a.dX, a.dY, a.dZ, a.dS, a.dRS divide by TW, IR, TH, W4, rows_max * W4; a.ws holds U
+template <class CFG>
+__global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
+{
+    constexpr int MB = CFG::MB, LBV = CFG::LBV, NT = CFG::NT, TM = CFG::TM, TT = CFG::TT, MP = CFG::MP;
+    constexpr uint32_t kFar = 0x80000000u;  // tensors stay below 2 GiB: this offset plus any scalar offset is out of range
+    typedef Mma<CONV_BF16, 32> mma_t;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+
+    const WinosGeom geo = winos_geom<CFG>(a.N, a.W, a.OH, a.OW);
+    const int PWL = geo.PWL, pitch = geo.pitch;
+    float* const Vs = smem;                  // [16][4][TT][4]
+    float* const Rs = smem + CFG::V_FLOATS;  // [16][pitch], then a spare vector per thread
+
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int C16 = (a.C + 15) >> 4, MBK = (a.K + 31) >> 5;
+    // one XCD's workgroups are a contiguous run of "groups of 3 channel tiles; within a group all tile groups"
+    int t0, m0;
+    {
+        const int KT = (a.K + TM - 1) / TM, TN = (geo.tiles + TT - 1) / TT, total = KT * TN;
+        const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+        const int s = x * (total >> 3) + (x < (total & 7) ? x : (total & 7)) + j;
+        const int per_group = 3 * TN;
+        const int gr = s / per_group, rem = s - gr * per_group;
+        const int gs = (KT - 3 * gr) < 3 ? (KT - 3 * gr) : 3;
+        const int tg = rem / gs, kk = rem - tg * gs;
+        t0 = tg * TT;
+        m0 = (3 * gr + kk) * TM;
+    }
+
+    // ---- transformed filters: ring of groups (plane of this wave, 32-channel block), three parts each ----------------
+    constexpr int GRP = 2 * MB, RING = CFG::RING;
+    const __amdgpu_buffer_rsrc_t ru = make_rsrc(a.ws, (uint32_t)C16 * 16u * (uint32_t)MBK * 3072u);
+    const uint32_t a_lane = (uint32_t)lane * 16u;
+    const uint32_t u_plane = (uint32_t)MBK * 3072u, u_step = u_plane * 16u;
+    const uint32_t u_base = (uint32_t)(wave * 2) * u_plane + (uint32_t)(m0 >> 5) * 3072u;
+    uint4 ar[RING][3];
+    auto load_a = [&](auto slot_c, auto grp_c, uint32_t step) {
+        constexpr int slot = decltype(slot_c)::value, grp = decltype(grp_c)::value;
+        const uint32_t soff = u_base + step * u_step + (uint32_t)(grp / MB) * u_plane + (uint32_t)(grp % MB) * 3072u;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(ru, (int)a_lane, (int)(soff + q * 1024u), 0);
+            ar[slot][q] = make_uint4(v.x, v.y, v.z, v.w);
+        }
+    };
+
+    // ---- input rows ----------------------------------------------------------------------------------------------------
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
+    auto stacked_row = [&](uint32_t tile_row) {
+        uint32_t n, ty;
+        a.dZ.divmod(tile_row, n, ty);
+        return (int)n * geo.IR + 2 * (int)ty;
+    };
+    uint32_t g_first, t_in_row;
+    a.dX.divmod((uint32_t)t0, g_first, t_in_row);
+    const int t_last = (t0 + TT < geo.tiles ? t0 + TT : geo.tiles) - 1;
+    const int s0 = __builtin_amdgcn_readfirstlane(stacked_row(g_first));
+    const int nrows = __builtin_amdgcn_readfirstlane(stacked_row(a.dX.div((uint32_t)t_last))) + 4 - s0;
+    // task = (channel of the step, staged row, 16-byte vector of the row): the loads of a wave are contiguous runs of rows
+    uint32_t r_goff[LBV];
+    int r_lds[LBV], r_c[LBV];
+#pragma unroll
+    for (int i = 0; i < LBV; ++i) {
+        uint32_t c, e, ri, xv, n, yy;
+        a.dRS.divmod((uint32_t)(i * NT + tid), c, e);
+        a.dS.divmod(e, ri, xv);
+        a.dY.divmod((uint32_t)s0 + ri, n, yy);
+        const int y = (int)yy - a.pad, x = (int)xv * 4 < a.W - 4 ? (int)xv * 4 : a.W - 4;
+        const bool ok = c < 16u && (int)ri < nrows && (unsigned)y < (unsigned)a.H && (int)n < a.N;
+        r_goff[i] = ok ? (uint32_t)((((int)n * a.C + (int)c) * a.H + y) * a.W + x) * 4u : kFar;
+        r_lds[i] = ok ? (int)ri * PWL + x + a.pad + (int)c * pitch : 16 * pitch + tid * 4;
+        r_c[i] = (int)c;
+    }
+    const uint32_t step_bytes = (uint32_t)a.HW * 64u;
+    struct Rows {
+        f32x4 v[LBV];
+    };
+    auto load_rows = [&](Rows& r, int step) {  // channels past the last one read as zero
+#pragma unroll
+        for (int i = 0; i < LBV; ++i)
+            r.v[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rin, (int)(step * 16 + r_c[i] < a.C ? r_goff[i] : kFar),
+                                                                                     (int)((uint32_t)step * step_bytes), 0));
+    };
+    auto store_rows = [&](const Rows& r) {
+#pragma unroll
+        for (int i = 0; i < LBV; ++i) {
+            float* dst = Rs + r_lds[i];  // (a task without a row writes to its own spare vector behind the rows)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dst[j] = r.v[i][j];
+        }
+    };
+
+    // ---- input transform: thread = (tile, channel) ---------------------------------------------------------------------
+    const int v_quad = wave & 3, v_sub = lane & 3, v_tile = (wave >> 2) * 16 + (lane >> 2);
+    int v_src;
+    {
+        const int t = (t0 + v_tile < geo.tiles) ? t0 + v_tile : t0;  // tiles past the end repeat the first one; never stored
+        uint32_t gr, tx;
+        a.dX.divmod((uint32_t)t, gr, tx);
+        v_src = (v_quad * 4 + v_sub) * pitch + (stacked_row(gr) - s0) * PWL + 2 * (int)tx;
+    }
+    float* const v_dst = Vs + (v_quad * TT + v_tile) * 4 + v_sub;
+    struct Tile {
+        float2 lo[4], hi[4];
+    };
+    auto read_tile = [&]() {
+        const float* src = Rs + v_src;
+        Tile d;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            d.lo[r] = *(const float2*)&src[r * PWL];
+            d.hi[r] = *(const float2*)&src[r * PWL + 2];
+        }
+        return d;
+    };
+    auto write_tile = [&](const Tile& b) {
+        float d[4][4], t[4][4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            d[r][0] = b.lo[r].x; d[r][1] = b.lo[r].y; d[r][2] = b.hi[r].x; d[r][3] = b.hi[r].y;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            t[0][j] = d[0][j] - d[2][j];
+            t[1][j] = d[1][j] + d[2][j];
+            t[2][j] = d[2][j] - d[1][j];
+            t[3][j] = d[1][j] - d[3][j];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v_dst[(4 * i + 0) * 16 * TT] = t[i][0] - t[i][2];
+            v_dst[(4 * i + 1) * 16 * TT] = t[i][1] + t[i][2];
+            v_dst[(4 * i + 2) * 16 * TT] = t[i][2] - t[i][1];
+            v_dst[(4 * i + 3) * 16 * TT] = t[i][1] - t[i][3];
+        }
+    };
+
+    typename mma_t::acc_t acc[2][MB];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[x][mb][v] = 0.0f;
+
+    // lane (li, g) feeds column li of a block with channels 8g .. 8g+7 of the step
+    struct Plane {
+        f32x4 lo, hi;
+    };
+    auto read_plane = [&](int x) {
+        const float* src = Vs + ((wave * 2 + x) * 4 + 2 * g) * TT * 4 + li * 4;
+        return Plane{*(const f32x4*)src, *(const f32x4*)&src[TT * 4]};
+    };
+    auto split_plane = [&](const Plane& p) {
+        const float x[8] = {p.lo[0], p.lo[1], p.lo[2], p.lo[3], p.hi[0], p.hi[1], p.hi[2], p.hi[3]};
+        return split3(x);
+    };
+    // the six partial products of plane x, smallest first; the filters of group grp + RING - 1 are fetched meanwhile
+    auto multiply = [&](auto xc, const Split3& b, uint32_t step) {
+        constexpr int x = decltype(xc)::value;
+        static_for<MB>([&](auto mbc) {
+            constexpr int mb = decltype(mbc)::value, grp = x * MB + mb, ahead = grp + RING - 1;
+            constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+            load_a(std::integral_constant<int, ahead % RING>{}, std::integral_constant<int, ahead % GRP>{}, step + ahead / GRP);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) acc[x][mb] = mma_t::run(ar[grp % RING][pa[q]], b.p[pb[q]], acc[x][mb]);
+        });
+    };
+    // asks for one MFMA, then LDS writes and vector work that fit beneath it, and so on through a stage
+    auto interleave = [&](auto valu_c, auto dsw_c) {
+        constexpr int valu = decltype(valu_c)::value, dsw = decltype(dsw_c)::value;
+        __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+        static_for<6 * MB>([&](auto ic) {
+            if constexpr (decltype(ic)::value % 6 == 0) __builtin_amdgcn_sched_group_barrier(0x020, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, valu, 0);
+            __builtin_amdgcn_sched_group_barrier(0x200, dsw, 0);
+        });
+    };
+    typedef std::integral_constant<int, 0> c0_t;
+    typedef std::integral_constant<int, 1> c1_t;
+
+    // ---- pipeline: entering step i, Vs holds the tiles of step i, `p0` the parts of this wave's first plane and `v1` its
+    // second plane, Rs the rows of step i+1, and the rows of step i+2 are in flight.  Every wave holds all it needs of Vs.
+    Rows rows, rows1;
+    load_rows(rows, 0);
+    static_for<RING - 1>([&](auto gc) { load_a(gc, gc, 0); });
+    load_rows(rows1, 1);
+    for (int i = tid; i < 4 * pitch; i += NT) *(f32x4*)&Rs[4 * i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};  // the border stays zero
+    __syncthreads();
+    store_rows(rows);
+    load_rows(rows, 2);
+    __syncthreads();
+    write_tile(read_tile());
+    __syncthreads();
+    Split3 p0 = split_plane(read_plane(0)), p1;
+    Plane v1 = read_plane(1);
+    store_rows(rows1);
+    __syncthreads();
+    for (int i = 0; i < C16; ++i) {
+        __builtin_amdgcn_sched_barrier(0);
+        const Tile d = read_tile();  // step i+1 (past the last step: nobody reads what becomes of it)
+        p1 = split_plane(v1);
+        multiply(c0_t{}, p0, (uint32_t)i);
+        write_tile(d);
+        interleave(std::integral_constant<int, (96 + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (8 + 6 * MB - 1) / (6 * MB)>{});
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        const Plane v0 = read_plane(0);
+        v1 = read_plane(1);
+        multiply(c1_t{}, p1, (uint32_t)i);
+        store_rows(rows);
+        p0 = split_plane(v0);
+        interleave(std::integral_constant<int, (48 + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (2 * LBV + 6 * MB - 1) / (6 * MB)>{});
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(rows, i + 3);
+        __syncthreads();
+    }
+
+    // ---- epilogue, 32 channels at a time: planes to LDS, inverse transform, bias + activation, 2x2 stores ---------------
+    float* const Ms = smem;  // [2][16][32][MP]
+    const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);
+    const __amdgpu_buffer_rsrc_t rout = make_rsrc(a.out, a.out_bytes);
+    const bool even = (a.OW & 1) == 0;  // a tile's two outputs of a row are 8-byte aligned and both inside
+    static_for<(MB + 1) / 2>([&](auto hc) {
+        constexpr int mb0 = decltype(hc)::value * 2, MB2 = MB - mb0 < 2 ? MB - mb0 : 2;
+        if constexpr (mb0 > 0) __syncthreads();
+#pragma unroll
+        for (int mb = 0; mb < MB2; ++mb)
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    Ms[((mb * 16 + wave * 2 + x) * 32 + acc_row<32>(v, lane)) * MP + li] = acc[x][mb0 + mb][v];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < MB2 * 32 * TT / NT; ++j) {
+            const int e = j * NT + tid, kk = e / TT, kl = kk % 32, tl = e % TT;
+            const int k = m0 + mb0 * 32 + kk, t = t0 + tl;
+            const bool ok = k < a.K && t < geo.tiles;
+            const float* src = Ms + ((kk / 32) * 16 * 32 + kl) * MP + tl;
+            float m[4][4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) m[i][jj] = src[(4 * i + jj) * 32 * MP];
+            float r0[4], r1[4];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                r0[jj] = (m[0][jj] + m[1][jj]) + m[2][jj];
+                r1[jj] = (m[1][jj] - m[2][jj]) - m[3][jj];
+            }
+            float y[4];
+            y[0] = (r0[0] + r0[1]) + r0[2];
+            y[1] = (r0[1] - r0[2]) - r0[3];
+            y[2] = (r1[0] + r1[1]) + r1[2];
+            y[3] = (r1[1] - r1[2]) - r1[3];
+            uint32_t gr, tx, n, ty;
+            a.dX.divmod(ok ? (uint32_t)t : 0u, gr, tx);
+            a.dZ.divmod(gr, n, ty);
+            const int oy = 2 * (int)ty, ox = 2 * (int)tx;
+            // a NaN or an infinity fails the first test; kTiny: parts of smaller operands may be below bf16's range
+            constexpr float kTiny = 0x1p-60f;
+            const float big = (__builtin_fabsf(y[0]) + __builtin_fabsf(y[1])) + (__builtin_fabsf(y[2]) + __builtin_fabsf(y[3]));
+            if (ok && (!(big < __builtin_inff()) || (big < kTiny && big != 0.0f))) {
+                const float* const in = (const float*)a.in + (size_t)n * a.C * a.HW;
+                const float* const f = (const float*)a.filt + (size_t)k * a.C * 9;
+#pragma unroll 1
+                for (int q = 0; q < 4; ++q) {
+                    const int iy = oy + (q >> 1) - a.pad, ix = ox + (q & 1) - a.pad;
+                    float s = 0.0f;
+#pragma unroll 1
+                    for (int c = 0; c < a.C; ++c)
+#pragma unroll 1
+                        for (int w = 0; w < 9; ++w) {
+                            const int yy = iy + w / 3, xx = ix + w % 3;
+                            if ((unsigned)yy < (unsigned)a.H && (unsigned)xx < (unsigned)a.W)
+                                s = __builtin_fmaf(in[(size_t)c * a.HW + yy * a.W + xx], f[c * 9 + w], s);
+                        }
+                    if (q == 0) y[0] = s;
+                    if (q == 1) y[1] = s;
+                    if (q == 2) y[2] = s;
+                    if (q == 3) y[3] = s;
+                }
+            }
+            const float b = buffer_load_elem<float>(rbias, ok ? (uint32_t)k * 4u : kOutOfRange);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                y[q] += b;
+                if (a.relu) y[q] = y[q] > 0.0f ? y[q] : 0.0f;
+            }
+            const uint32_t base = (uint32_t)(((int)n * a.K + k) * a.OHW + oy * a.OW + ox) * 4u;
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy) {
+                const bool in_row = ok && oy + dy < a.OH;
+                const uint32_t o = in_row ? base + (uint32_t)(dy * a.OW) * 4u : kOutOfRange;
+                if (even) {
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{__builtin_bit_cast(uint32_t, y[2 * dy]), __builtin_bit_cast(uint32_t, y[2 * dy + 1])},
+                                                          rout, (int)o, 0, 0);
+                } else {
+                    buffer_store_elem<float>(y[2 * dy], rout, o);
+                    buffer_store_elem<float>(y[2 * dy + 1], rout, in_row && ox + 1 < a.OW ? o + 4u : kOutOfRange);
+                }
+            }
+        }
+    });
+}
+
+template <class CFG>
+size_t winos_ws_bytes(const Variant&, const conv_desc& d, int, int)
+{
+    return winos_filter_bytes(d.K, d.C);
+}
+
+template <class CFG>
+hipError_t winos_launch(const Variant&, ConvArgs& a, hipStream_t s)
+{
+    const size_t lds = winos_lds_bytes<CFG>(a.N, a.W, a.OH, a.OW);
+    const hipError_t e = ensure_dynamic_lds((const void*)winos_kernel<CFG>, lds);
+    if (e != hipSuccess) return e;
+    const WinosGeom g = winos_geom<CFG>(a.N, a.W, a.OH, a.OW);
+    a.dX = make_fastdiv((uint32_t)g.TW);
+    a.dY = make_fastdiv((uint32_t)g.IR);
+    a.dZ = make_fastdiv((uint32_t)g.TH);
+    a.dS = make_fastdiv((uint32_t)g.W4);
+    a.dRS = make_fastdiv((uint32_t)(g.rows_max * g.W4));
+    hipLaunchKernelGGL(winos_filter_kernel, dim3((unsigned)((a.K + 31) / 32), (unsigned)((a.C + 15) / 16)), dim3(512), 0, s,
+                       (const float*)a.filt, (uint4*)a.ws, a.K, a.C);
+    const hipError_t e2 = hipGetLastError();
+    if (e2 != hipSuccess) return e2;
+    dim3 grid((unsigned)(((g.tiles + CFG::TT - 1) / CFG::TT) * ((a.K + CFG::TM - 1) / CFG::TM)));
+    hipLaunchKernelGGL(winos_kernel<CFG>, grid, dim3(CFG::NT), lds, s, a);
+    return hipGetLastError();
+}
+
+template <class CFG>
+bool winos_valid(const Variant&, const conv_desc& d, int OH, int OW)
+{
+    if (d.dtype != CONV_F32 || d.R != 3 || d.S != 3 || d.stride != 1 || d.pad > 1) return false;
+    if (d.flags & ~(uint32_t)CONV_FLAG_RELU) return false;  // plain formats and filters, no fused pool
+    // a step is 16 channels and a block 32 filters, neither worth it half empty; a row is at least one vector
+    if (d.C < 8 || d.K <= 16 || d.W < 4) return false;
+    // 32-bit byte offsets beside an out-of-range marker
+    const long long lim = 1LL << 31;
+    if (((long long)d.N * d.C + 64) * d.H * d.W * 4 >= lim || (long long)d.N * d.K * OH * OW * 4 >= lim) return false;
+    if ((long long)winos_filter_bytes(d.K, d.C) * 2 >= lim || (d.C + 15) / 16 > 65535) return false;
+    if ((long long)d.N * ((OH + 1) / 2 + 2) * ((OW + 1) / 2 + 1) >= (1LL << 28)) return false;
+    const WinosGeom g = winos_geom<CFG>(d.N, d.W, OH, OW);
+    if ((long long)g.rows_max * g.W4 * 16 > CFG::SLOTS) return false;  // every staged vector needs a slot
+    if (winos_lds_bytes<CFG>(d.N, d.W, OH, OW) > 160 * 1024) return false;
+    if ((long long)((d.K + CFG::TM - 1) / CFG::TM) * ((g.tiles + CFG::TT - 1) / CFG::TT) >= lim) return false;
+    return true;
+}
+
+template <class CFG>
+void winos_register(std::vector<Variant>& out)
+{
+    Variant v;
+    char buf[96];
+    snprintf(buf, sizeof buf, "winos_f32_M%dT%d_e%d_r%d", CFG::TM, CFG::TT, CFG::LBV, CFG::RING);
+    v.name = buf;
+    v.dtype = CONV_F32;
+    v.split = 1;
+    v.tm = CFG::TM;
+    v.tn = CFG::TT * 4;
+    v.tk = 16 * 9;
+    v.threads = CFG::NT;
+    v.family = FAM_WINOGRAD;
+    v.specificity = 5;
+    v.traits = TRAIT_SPLIT_PRODUCTS;
+    v.per_cu = CFG::WPS / 2;
+    v.valid = &winos_valid<CFG>;
+    v.launch = &winos_launch<CFG>;
+    v.ws_extra = &winos_ws_bytes<CFG>;
+    out.push_back(v);
+}
+
+}  // namespace convfwd

@@ -1,0 +1,77 @@
+"""GPU parity of the Winograd kernel on split products (fp32) where its tiles, staged rows and channel steps have their
+edges: bit for bit on small integers (the splits and every sum are exact), within the fp32 tolerance on random data, and
+on operands that the 16-bit parts cannot carry (infinities, overflowing transforms, tiny numbers), where the kernel sums
+the definition again."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1611_06945_amd import workloads as wl
+from paper_1611_06945_amd.workloads import ConvShape
+
+from gpu_util import TOL, DeviceCase, to_host_f64
+from test_gpu_parity import assert_bit_exact, int_case, random_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    ConvShape(1, 8, 16, 16, 32, 3, 3, 1, 1),    # half a channel step, 64 tiles exactly
+    ConvShape(3, 17, 13, 13, 33, 3, 3, 1, 1),   # one channel over a step, one filter over a block, odd outputs
+    ConvShape(5, 48, 7, 9, 130, 3, 3, 1, 0),    # no border, tiles across images
+    ConvShape(70, 16, 3, 4, 40, 3, 3, 1, 1),    # many images per workgroup
+    ConvShape(2, 40, 33, 35, 96, 3, 3, 1, 1),   # staged rows across an image boundary
+    ConvShape(1, 16, 5, 100, 64, 3, 3, 1, 1),   # long rows: only the narrow tiles fit
+    ConvShape(1, 32, 56, 56, 70, 3, 3, 1, 1),   # three staging slots per thread
+    ConvShape(1, 8, 4, 4, 17, 3, 3, 1, 0),      # one tile, rows of one vector
+]
+
+
+def variants_of(case):
+    return [(i, n) for i, n in enumerate(case.variant_names()) if n.startswith("winos_")]
+
+
+@pytest.mark.parametrize("si", range(len(SHAPES)))
+def test_shapes(si):
+    shape = SHAPES[si]
+    icase = int_case(shape, wl.F32, 4300 + si)
+    rcase = random_case(shape, wl.F32, 4350 + si, relu=bool(si % 2))
+    mine = variants_of(icase)
+    assert mine, shape
+    for vi, name in mine:
+        print(name, shape, flush=True)
+        assert_bit_exact(icase, icase.run(variant=vi), name)
+        err = rcase.error(rcase.run(variant=vi))
+        assert err <= TOL[wl.F32], "%s: %.3g" % (name, err)
+
+
+def special_case(kind):
+    shape = ConvShape(2, 24, 12, 12, 40, 3, 3, 1, 1)
+    x = wl.draw(("halfnormal", 1.0), shape.in_shape(), 4390).astype(np.float32)
+    f = wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), 4391).astype(np.float32)
+    if kind == "infinity":
+        x[1, 3, 5, 6] = np.inf
+    elif kind == "overflow":
+        x[0, 2, 4:8, 4:8] = 3.0e38  # finite, but not the transform's differences and sums
+        f *= np.float32(1e-3)
+    else:
+        x *= np.float32(1e-33)
+    bias = np.zeros(shape.K, dtype=np.float64)
+    return DeviceCase(shape, wl.F32, {"in": x, "filt": f, "bias": bias.astype(np.float32)}, relu=False)
+
+
+@pytest.mark.parametrize("kind", ["infinity", "overflow", "tiny"])
+def test_operands_outside_the_range_of_the_parts(kind):
+    case = special_case(kind)
+    with np.errstate(all="ignore"):
+        ref = case.ref()
+    inside = np.isfinite(ref) & (np.abs(ref) < 3e38)
+    for vi, name in variants_of(case):
+        got = to_host_f64(case.run(variant=vi), wl.F32)
+        if kind == "infinity":
+            assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+            assert (~inside).any()
+        assert np.isfinite(got[inside]).all(), name
+        if kind == "overflow":  # pixels the large values do not reach, and those they do, each against its own size
+            far = inside & (np.abs(ref) < 1e3)
+            assert oracle.max_normalised_error(got[far], ref[far]) <= TOL[wl.F32], name
+        assert oracle.max_normalised_error(got[inside], ref[inside]) <= TOL[wl.F32], name
