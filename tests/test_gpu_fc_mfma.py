@@ -1,0 +1,36 @@
+"""GPU parity of the matrix-unit kernel for fully-connected layers (more than eight images): ragged channel and image
+counts, reduction lengths that are no multiple of a step, one step and less, bit for bit on small integers and within the
+storage type's tolerance on random data."""
+import pytest
+
+from paper_1611_06945_amd import workloads as wl
+from paper_1611_06945_amd.workloads import ConvShape
+
+from gpu_util import TOL
+from test_gpu_parity import assert_bit_exact, int_case, random_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    ConvShape(9, 8, 1, 1, 1, 1, 1, 1, 0),       # one vector per row, one output channel
+    ConvShape(16, 24, 1, 1, 17, 1, 1, 1, 0),    # a row past a tile, part of a step
+    ConvShape(17, 40, 3, 5, 64, 3, 5, 1, 0),    # 600 elements: a step and a piece for some waves only
+    ConvShape(33, 64, 2, 4, 100, 2, 4, 1, 0),   # 512 elements: exactly one step per wave in 16 bits
+    ConvShape(64, 136, 6, 6, 40, 6, 6, 1, 0),   # 4896 elements: more steps than in flight
+    ConvShape(20, 256, 7, 7, 33, 7, 7, 1, 0),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.F32, wl.F16, wl.BF16])
+@pytest.mark.parametrize("si", range(len(SHAPES)))
+def test_shapes(si, dtype):
+    shape = SHAPES[si]
+    icase = int_case(shape, dtype, 4500 + si)
+    rcase = random_case(shape, dtype, 4550 + si, relu=bool(si % 2))
+    mine = [(i, n) for i, n in enumerate(icase.variant_names()) if "_mfma_rows16_" in n]
+    assert len(mine) == 1, shape
+    for vi, name in mine:
+        print(name, shape, flush=True)
+        assert_bit_exact(icase, icase.run(variant=vi, with_ws=False), name)
+        err = rcase.error(rcase.run(variant=vi, with_ws=False))
+        assert err <= TOL[dtype], "%s: %.3g" % (name, err)
