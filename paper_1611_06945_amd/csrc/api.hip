@@ -44,6 +44,8 @@ struct State {
         int pick_any = -2;       // cost model's pick with unlimited workspace (-2: not computed yet)
         size_t pick_any_ws = 0;  // workspace that pick needs
         int pick_nows = -2;      // cost model's pick among variants that need no workspace
+        int pick_lim = -2;       // ... and under the workspace limit `lim`
+        size_t lim = 0;
     };
     std::map<Key, Memo> memo;
 };
@@ -80,6 +82,8 @@ State& state()
         register_pwin_bf16(s->variants);
         register_bwin_f16(s->variants);
         register_bwin_bf16(s->variants);
+        register_pwb_f16(s->variants);
+        register_pwb_bf16(s->variants);
         for (size_t i = 0; i < s->variants.size(); ++i) s->by_name[s->variants[i].name] = (int)i;
         return s;
     }();
@@ -212,6 +216,17 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
 {
     const double P = (double)d.N * OH * OW, Q = (double)d.C * d.R * d.S;
     if (v.family == FAM_FC) return 1.0 + std::abs(v.tm - 4);  // weight streaming: always ahead of the MFMA tiles when valid
+    if (v.traits & TRAIT_PIXEL_STREAM) {
+        const double mt = std::ceil(d.K / (double)v.tm), wgs = mt * std::ceil(P / (double)v.tn);
+        const double per_cu = v.tm == 32 ? 3.0 : 2.0, rounds = std::ceil(wgs / (256.0 * per_cu));
+        // one workgroup: start, filters to LDS, groups, stores (46 images of 10x10x200 -> 352 with M128 13.6 us, with M32 8.2)
+        const double own = 1.5 + 0.02 * v.tm + d.C * (0.006 + 0.00016 * v.tm);
+        // the stream (input again from L2 for every further channel tile), faster with 8-byte loads and with two channel
+        // blocks per load; measured (model) on 64 images of 28x28x256 -> 128: M64 of 512 pixels 12.1 us (12.9), of 256 pixels
+        // 13.8 (16.4), M128 of 256 15.3 (15.7), M32 of 512 17.5 (17.6)
+        const double bytes = 2.0 * P * ((double)d.C * (1.0 + 0.1 * (mt - 1.0)) + d.K);
+        return 4.0 + std::max(bytes / (v.tn == 256 ? 3.3e6 : v.tm == 32 ? 3.4e6 : 4.6e6), rounds * own);
+    }
     if (v.traits & TRAIT_SPLIT_PRODUCTS) {
         // Winograd on split products: v.tm / 32 blocks of 32 channels; a workgroup costs its start, planes and stores and a
         // step per 16 channels.  v.per_cu of them share a CU, to no gain in time per workgroup.  Measured (model): 20 images
@@ -269,7 +284,10 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const bool f32 = d.dtype == CONV_F32;
         const double mfmas = std::ceil(d.C / (f32 ? 8.0 : 16.0) / kw) * (f32 ? 4.0 : 1.0) * (v.tm / 32.0) * (v.tn / 32.0);
         const double share = std::min(per_cu, std::max(1.0, tiles / 256.0)) * kw / 4.0;  // waves per SIMD
-        return 3.2 + rounds * (0.9 + mfmas * (f32 ? 0.027 : 0.030) * std::max(1.0, share)) + 0.3 + 0.02 * kw;
+        // (... which is what many tiles wait for: 32 clocks of the CU per load instruction, 64 images of 28x28x256 -> 128 take
+        // 32 us)
+        const double loads = f32 ? 0.0 : tiles / 256.0 * (d.C / 16.0) * (v.tn / 32.0) * 8.0 * 0.0135;
+        return std::max(3.5 + loads, 3.2 + rounds * (0.9 + mfmas * (f32 ? 0.027 : 0.030) * std::max(1.0, share)) + 0.3 + 0.02 * kw);
     }
     if (v.traits & TRAIT_CHANNEL_WAVES) {
         // one workgroup per (channel tile, run of v.tn pixels); its v.threads / 64 waves split the channels, so a SIMD
@@ -386,7 +404,11 @@ int select_variant(State& st, const conv_desc& d, int OH, int OW, size_t ws_limi
         if (m.pick_nows == -2) m.pick_nows = pick_heuristic(st, valid, d, OH, OW, 0);
         h = m.pick_nows;
     } else {
-        h = pick_heuristic(st, valid, d, OH, OW, ws_limit);
+        if (m.pick_lim == -2 || m.lim != ws_limit) {  // the last limit that excluded the unconstrained pick
+            m.pick_lim = pick_heuristic(st, valid, d, OH, OW, ws_limit);
+            m.lim = ws_limit;
+        }
+        h = m.pick_lim;
     }
     return h < 0 ? CONV_ENOVARIANT : h;
 }
@@ -558,7 +580,17 @@ int conv_fwd_static(const conv_desc* desc, const void* in, const void* filt, con
         idx = select_variant(st, *desc, OH, OW, SIZE_MAX);
     }
     if (idx < 0) return idx;
-    const size_t need = ws_bytes_of(st.variants[idx], *desc, OH, OW);
+    size_t need = ws_bytes_of(st.variants[idx], *desc, OH, OW);
+    if (need > (size_t)CONV_STATIC_SCRATCH_BYTES && (st.variants[idx].traits & (TRAIT_BIG_WINDOW | TRAIT_SPLIT_PRODUCTS))) {
+        // kernels that trade scratch for speed: where the array is too small for them, the pick that fits it (a forced
+        // variant stays, and is refused below)
+        std::lock_guard<std::mutex> g(st.mu);
+        const int fit = select_variant(st, *desc, OH, OW, (size_t)CONV_STATIC_SCRATCH_BYTES);
+        if (fit >= 0) {
+            idx = fit;
+            need = ws_bytes_of(st.variants[idx], *desc, OH, OW);
+        }
+    }
     if (need > (size_t)CONV_STATIC_SCRATCH_BYTES) {
         char msg[256];
         snprintf(msg, sizeof msg, "conv_fwd_static: variant %s needs %zu bytes of scratch, the library holds %zu",

@@ -125,6 +125,7 @@ enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no a
        TRAIT_WAVE_SPLIT = 1024u,       // the waves of a workgroup split the reduction of one tile (v.threads / 64 ways), operands from global memory
        TRAIT_BIG_WINDOW = 4096u,       // 16-bit window kernel whose waves own their outputs (many-pixel layers)
        TRAIT_SPLIT_PRODUCTS = 8192u,   // fp32 operands split into bf16 parts, products on the 16-bit matrix units
+       TRAIT_PIXEL_STREAM = 16384u,    // 16-bit pointwise kernel for many pixels, input transposed in registers
        TRAIT_CHANNEL_WAVES = 2048u };  // fp32 window kernel on linear pixel tiles whose waves split the channels of a chunk
 
 enum { FAM_IGEMM = 0, FAM_POINTWISE = 1, FAM_FIRSTLAYER = 2, FAM_WINDOW = 3, FAM_FC = 4, FAM_NHWC = 5, FAM_WINOGRAD = 6 };
@@ -149,6 +150,8 @@ void register_wconv_f32(std::vector<Variant>& out);
 void register_wconv_f16(std::vector<Variant>& out);
 void register_wconv_bf16(std::vector<Variant>& out);
 void register_wino_f32(std::vector<Variant>& out);
+void register_pwb_f16(std::vector<Variant>& out);
+void register_pwb_bf16(std::vector<Variant>& out);
 void register_winos_f32(std::vector<Variant>& out);
 void register_pwk_f32(std::vector<Variant>& out);
 void register_pwk_f16(std::vector<Variant>& out);

@@ -6,10 +6,11 @@ import numpy as np
 import pytest
 
 import oracle
+from paper_1611_06945_amd import binding as B
 from paper_1611_06945_amd import workloads as wl
 from paper_1611_06945_amd.workloads import ConvShape
 
-from gpu_util import TOL, DeviceCase, to_host_f64
+from gpu_util import TOL, DeviceCase, empty_out, to_host_f64, torch_mod
 from test_gpu_parity import assert_bit_exact, int_case, random_case
 
 pytestmark = pytest.mark.gpu
@@ -75,3 +76,25 @@ def test_operands_outside_the_range_of_the_parts(kind):
             far = inside & (np.abs(ref) < 1e3)
             assert oracle.max_normalised_error(got[far], ref[far]) <= TOL[wl.F32], name
         assert oracle.max_normalised_error(got[inside], ref[inside]) <= TOL[wl.F32], name
+
+
+@pytest.mark.parametrize("shape,dtype", [
+    (ConvShape(24, 640, 14, 14, 1024, 3, 3, 1, 1), wl.F32),   # split filters of 63 MB
+    (ConvShape(40, 128, 64, 56, 32, 3, 3, 1, 1), wl.BF16),    # an input copy of 38 MB
+])
+def test_static_scratch_serves_layers_whose_fastest_kernel_wants_more(shape, dtype):
+    torch = torch_mod()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4400)
+    tdt = torch.float32 if dtype == wl.F32 else torch.bfloat16
+    x = torch.randn(shape.in_shape(), generator=g, device="cuda").abs_().to(tdt)
+    f = torch.randn(shape.filt_shape(), generator=g, device="cuda").mul_(wl.he_sigma(shape)).to(tdt)
+    desc = B.desc_of(shape, dtype, relu=True)
+    pick = B.conv_variant_name(desc, -1)
+    idx = [i for i in range(B.conv_variant_count(desc)) if B.conv_variant_name(desc, i) == pick][0]
+    assert B.conv_variant_workspace(desc, idx) > B.CONV_STATIC_SCRATCH_BYTES, pick
+    want, got = empty_out(shape.out_shape(), dtype), empty_out(shape.out_shape(), dtype)
+    B.conv_fwd(desc, x, f, None, want)
+    B.conv_fwd_static(desc, x, f, None, got)
+    torch.cuda.synchronize()
+    assert B.conv_compare_outputs(dtype, got, want, got.numel()) <= (TOL[dtype] if dtype != wl.BF16 else 1e-2)
