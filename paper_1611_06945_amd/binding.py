@@ -149,20 +149,42 @@ def desc_of(shape, dtype=CONV_F32, relu=True, in_nhwc=False, out_nhwc=False, fil
 def _ptr(x) -> Optional[int]:
     if x is None:
         return None
+    data_ptr = getattr(x, "data_ptr", None)
+    if data_ptr is not None:
+        return int(data_ptr())
     if isinstance(x, int):
         return x
-    if hasattr(x, "data_ptr"):
-        return int(x.data_ptr())
     raise TypeError("expected a torch tensor, an int device address or None, got %r" % type(x))
+
+
+_raw_stream = None  # () -> handle of torch's current stream, once torch has initialised the GPU
+
+
+def _find_raw_stream():
+    """torch's current stream of its current device as a raw handle, without the availability check and the Stream object
+    that torch.cuda.current_stream() makes on every call: those took 3 of the 8 us a small layer's call did.  None where this
+    torch has no such accessors or has not initialised the GPU yet."""
+    global _raw_stream
+    import torch
+
+    get_device, get_stream = (getattr(torch._C, n, None) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
+    if get_device is None or get_stream is None or not torch.cuda.is_initialized():
+        return None
+    _raw_stream = lambda: get_stream(get_device())  # noqa: E731
+    return _raw_stream
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream() or None
         try:
             import torch
 
             if torch.cuda.is_available():
-                return int(torch.cuda.current_stream().cuda_stream) or None
+                handle = int(torch.cuda.current_stream().cuda_stream) or None
+                _find_raw_stream()
+                return handle
         except ImportError:
             pass
         return None
