@@ -215,7 +215,14 @@ size_t ws_bytes_of(const Variant& v, const conv_desc& d, int OH, int OW)
 double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
 {
     const double P = (double)d.N * OH * OW, Q = (double)d.C * d.R * d.S;
-    if (v.family == FAM_FC) return 1.0 + std::abs(v.tm - 4);  // weight streaming: always ahead of the MFMA tiles when valid
+    if (v.family == FAM_FC) {
+        // weight streaming: always ahead of the MFMA tiles when valid; split over four workgroups where the rows alone leave
+        // CUs without one
+        // (51 images, 18032 -> 1000 in fp32: 37 us against 106 whole; small layers lose the second launch: 12 images, 576 -> 1000
+        // take 4.4 us whole)
+        if (v.tm == 16) return (v.split > 1) == (d.K <= 16 * 128 && (double)d.K * Q > 4.0e6) ? 1.0 : 2.0;
+        return 1.0 + std::abs(v.tm - 4);
+    }
     if (v.traits & TRAIT_PIXEL_STREAM) {
         const double mt = std::ceil(d.K / (double)v.tm), wgs = mt * std::ceil(P / (double)v.tn);
         const double per_cu = v.tm == 32 ? 3.0 : 2.0, rounds = std::ceil(wgs / (256.0 * per_cu));

@@ -194,7 +194,7 @@ void fc_register_dtype(std::vector<Variant>& out)
     fc_register_rows<DT, 8>(out);
 }
 
-// More than eight images: the vector-ALU kernel above would multiply for longer than the weights take to arrive, and the
+// More than eight images (or, TAIL, rows that do not start on 16-byte boundaries): the vector-ALU kernel above would multiply for longer than the weights take to arrive, and the
 // MFMA tiles of the general kernels are too few to keep the memory busy (128 of 32 rows, each a serial chain of steps).
 // Here a workgroup owns 16 output channels and all images; its 16 waves take every 16th step of the reduction (a step is
 // 64 bytes of every row, so together they read 1 KB runs), each with DEPTH steps of loads in flight, both operands straight
@@ -203,7 +203,9 @@ void fc_register_dtype(std::vector<Variant>& out)
 // Bound by the stream of the weights (the images come from L2, NB times the weights' traffic at most): 6x6x256 -> 4096 at
 // batch 20 in fp16 (75.5 MB) takes 24 us, 16.6 us of which remain without the image loads (16 segments of 64 bytes cost a
 // load instruction twice what a contiguous kilobyte does); the best split of the general kernels took 31.9 us, the best
-// without a workspace 163.  3 to 9 steps in flight and a start that differs per workgroup make no difference.
+// without a workspace 163.  Layers of few rows split the reduction over four workgroups as well (fp32 partial sums, second
+// launch): 51 images, 18032 -> 1000 in fp32 101 -> 37 us.  3 images, 9506 -> 4096 (rows of 38024 bytes) 52 -> 31 us, without a
+// workspace 346 -> 31.  3 to 9 steps in flight and a start that differs per workgroup make no difference.
 template <int DT, int NB>
 struct FcmCfg {
     static constexpr int WAVES = 16, NT = 64 * WAVES;
@@ -211,7 +213,7 @@ struct FcmCfg {
     static constexpr int DEPTH = 4;
 };
 
-template <int DT, int NB>
+template <int DT, int NB, bool TAIL>
 __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
 {
     typedef FcmCfg<DT, NB> CFG;
@@ -234,25 +236,38 @@ __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) b_off[nb] = nb * 16 + li < a.N ? ((uint32_t)(nb * 16 + li) * (uint32_t)a.Q + (uint32_t)q0) * ES : kOutOfRange;
 
-    constexpr int STRIDE = WAVES * CFG::STEP;
+    constexpr int STRIDE = WAVES * CFG::STEP, kPast = 0x40000000;
     uint4 av[DEPTH], bv[DEPTH][NB];
     auto load = [&](int slot, int i) {
-        const bool live = q0 + i * STRIDE < a.Q;
+        const bool live = i != kPast && q0 + i * STRIDE < a.Q;
         const uint32_t d = (uint32_t)(i * STRIDE) * ES;
         av[slot] = buffer_load_vec(rfilt, live && a_off != kOutOfRange ? a_off + d : kOutOfRange);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) bv[slot][nb] = buffer_load_vec(rin, live && b_off[nb] != kOutOfRange ? b_off[nb] + d : kOutOfRange);
     };
+    auto cut = [](uint4 v, int elems) {  // keeps the first `elems` elements (rows hold whole words)
+        const int words = elems * (int)ES / 4;
+        return make_uint4(words > 0 ? v.x : 0u, words > 1 ? v.y : 0u, words > 2 ? v.z : 0u, words > 3 ? v.w : 0u);
+    };
     typename mma_t::acc_t acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = typename mma_t::acc_t{0.0f, 0.0f, 0.0f, 0.0f};
-    const int steps = (a.Q + STRIDE - 1) / STRIDE;
+    const int first = (int)blockIdx.y * a.steps_per_split;
+    const int steps = (a.Q + STRIDE - 1) / STRIDE, last = first + a.steps_per_split < steps ? first + a.steps_per_split : steps;
 #pragma unroll
-    for (int j = 0; j < DEPTH; ++j) load(j, j);
-    for (int i = 0; i < steps; i += DEPTH) {
+    for (int j = 0; j < DEPTH; ++j) load(j, first + j < last ? first + j : kPast);
+    for (int i = first; i < last; i += DEPTH) {
 #pragma unroll
         for (int j = 0; j < DEPTH; ++j) {
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (TAIL) {  // the vector that holds a row's end goes on with the next row: cut both operands there
+                const int left = a.Q - (q0 + (i + j) * STRIDE);
+                if (left > 0 && left < CFG::VEC) {
+                    av[j] = cut(av[j], left);
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) bv[j][nb] = cut(bv[j][nb], left);
+                }
+            }
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 if constexpr (DT == CONV_F32) {
@@ -264,7 +279,7 @@ __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
                     acc[nb] = mma_t::run(av[j], bv[j][nb], acc[nb]);
                 }
             }
-            load(j, i + DEPTH + j);
+            load(j, i + DEPTH + j < last ? i + DEPTH + j : kPast);
         }
     }
     // lane (li, g): image nb*16 + li, rows 4g .. 4g+3
@@ -279,6 +294,10 @@ __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
             float x = red[0][n][r];
 #pragma unroll
             for (int w = 1; w < WAVES; ++w) x += red[w][n][r];
+            if (a.nsplit > 1) {
+                a.ws[((size_t)blockIdx.y * a.K + k) * a.P + n] = x;
+                return;
+            }
             if (a.bias) x += a.bias[k];
             if (a.relu) x = x > 0.0f ? x : 0.0f;
             ((elem_t*)a.out)[(size_t)n * a.K + k] = Prec<DT>::from_f32(x);
@@ -286,51 +305,62 @@ __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
     }
 }
 
-template <int DT, int NB>
-hipError_t fcm_launch(const Variant&, ConvArgs& a, hipStream_t s)
+template <int DT, int NB, bool TAIL>
+hipError_t fcm_launch(const Variant& v, ConvArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL((fcm_kernel<DT, NB>), dim3((unsigned)((a.K + 15) / 16)), dim3(1024), 0, s, a);
+    constexpr int STRIDE = FcmCfg<DT, NB>::WAVES * FcmCfg<DT, NB>::STEP;
+    const int steps = (a.Q + STRIDE - 1) / STRIDE;
+    a.nsplit = v.split;
+    a.steps_per_split = (steps + v.split - 1) / v.split;
+    hipLaunchKernelGGL((fcm_kernel<DT, NB, TAIL>), dim3((unsigned)((a.K + 15) / 16), (unsigned)v.split), dim3(1024), 0, s, a);
     return hipGetLastError();
 }
 
-template <int DT, int NB>
-bool fcm_valid(const Variant&, const conv_desc& d, int OH, int OW)
+template <int DT, int NB, bool TAIL>
+bool fcm_valid(const Variant& v, const conv_desc& d, int OH, int OW)
 {
     if (d.dtype != DT) return false;
     if (OH != 1 || OW != 1 || d.pad != 0 || d.R != d.H || d.S != d.W) return false;  // the window is the whole image
     const long long Q = (long long)d.C * d.R * d.S;
-    if (Q % FcVec<DT>::VEC != 0) return false;  // rows and images start on 16-byte boundaries
-    // offsets run DEPTH steps past a row's end before they are masked
-    if (Q > 0x7fffffffLL - 16 * 1024) return false;
-    return d.N > 8 && d.N <= NB * 16 && d.N > (NB - 1) * 16;
+    // rows and images start on 16-byte boundaries, or (TAIL) at least on 4-byte ones
+    if ((Q % FcVec<DT>::VEC != 0) != TAIL || Q * dtype_size(DT) % 4 != 0) return false;
+    constexpr int STRIDE = FcmCfg<DT, NB>::WAVES * FcmCfg<DT, NB>::STEP;
+    if (Q > 0x3fffffffLL || (v.split > 1 && (Q + STRIDE - 1) / STRIDE < 4 * v.split)) return false;
+    return (TAIL || d.N > 8) && d.N <= NB * 16 && d.N > (NB - 1) * 16;
 }
 
-template <int DT, int NB>
-void fcm_register_one(std::vector<Variant>& out)
+template <int DT, int NB, bool TAIL>
+void fcm_register_one(std::vector<Variant>& out, int split)
 {
     Variant v;
     char buf[96];
-    snprintf(buf, sizeof buf, "fc_%s_mfma_rows16_n%d", dtype_name(DT), NB * 16);
+    snprintf(buf, sizeof buf, "fc_%s_mfma_rows16_n%d%s%s", dtype_name(DT), NB * 16, TAIL ? "_t" : "", split > 1 ? "_sk4" : "");
     v.name = buf;
     v.dtype = DT;
-    v.split = 1;
+    v.split = split;
     v.tm = 16;
     v.tn = NB * 16;
     v.tk = 16 * FcmCfg<DT, NB>::STEP;
     v.threads = 1024;
     v.family = FAM_FC;
     v.specificity = 6;
-    v.valid = &fcm_valid<DT, NB>;
-    v.launch = &fcm_launch<DT, NB>;
+    v.valid = &fcm_valid<DT, NB, TAIL>;
+    v.launch = &fcm_launch<DT, NB, TAIL>;
     out.push_back(v);
 }
 template <int DT>
 void fcm_register_dtype(std::vector<Variant>& out)
 {
-    fcm_register_one<DT, 1>(out);
-    fcm_register_one<DT, 2>(out);
-    fcm_register_one<DT, 3>(out);
-    fcm_register_one<DT, 4>(out);
+    for (int split : {1, 4}) {
+        fcm_register_one<DT, 1, false>(out, split);
+        fcm_register_one<DT, 2, false>(out, split);
+        fcm_register_one<DT, 3, false>(out, split);
+        fcm_register_one<DT, 4, false>(out, split);
+        fcm_register_one<DT, 1, true>(out, split);
+        fcm_register_one<DT, 2, true>(out, split);
+        fcm_register_one<DT, 3, true>(out, split);
+        fcm_register_one<DT, 4, true>(out, split);
+    }
 }
 
 }  // namespace
