@@ -218,8 +218,8 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
     if (v.family == FAM_FC) {
         // weight streaming: always ahead of the MFMA tiles when valid; split over four workgroups where the rows alone leave
         // CUs without one
-        // (51 images, 18032 -> 1000 in fp32: 37 us against 106 whole; small layers lose the second launch: 12 images, 576 -> 1000
-        // take 4.4 us whole)
+        // (51 images, 18032 -> 1000 in fp32: 35 us against 85 whole; small layers lose the second launch: 12 images, 576 -> 1000
+        // take 5 us whole)
         if (v.tm == 16) return (v.split > 1) == (d.K <= 16 * 128 && (double)d.K * Q > 4.0e6) ? 1.0 : 2.0;
         return 1.0 + std::abs(v.tm - 4);
     }

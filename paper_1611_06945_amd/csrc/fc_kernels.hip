@@ -197,31 +197,36 @@ void fc_register_dtype(std::vector<Variant>& out)
 // More than eight images (or, TAIL, rows that do not start on 16-byte boundaries): the vector-ALU kernel above would multiply for longer than the weights take to arrive, and the
 // MFMA tiles of the general kernels are too few to keep the memory busy (128 of 32 rows, each a serial chain of steps).
 // Here a workgroup owns 16 output channels and all images; its 16 waves take every 16th step of the reduction (a step is
-// 64 bytes of every row, so together they read 1 KB runs), each with DEPTH steps of loads in flight, both operands straight
-// from memory into 16x16 MFMA registers: a lane's 16 bytes are 8 (fp32: 4) consecutive reduction elements of one filter row
-// or image.  The waves' sums meet in LDS and are added in wave order: deterministic, no workspace, one launch.
-// Bound by the stream of the weights (the images come from L2, NB times the weights' traffic at most): 6x6x256 -> 4096 at
-// batch 20 in fp16 (75.5 MB) takes 24 us, 16.6 us of which remain without the image loads (16 segments of 64 bytes cost a
-// load instruction twice what a contiguous kilobyte does); the best split of the general kernels took 31.9 us, the best
-// without a workspace 163.  Layers of few rows split the reduction over four workgroups as well (fp32 partial sums, second
-// launch): 51 images, 18032 -> 1000 in fp32 101 -> 37 us.  3 images, 9506 -> 4096 (rows of 38024 bytes) 52 -> 31 us, without a
-// workspace 346 -> 31.  3 to 9 steps in flight and a start that differs per workgroup make no difference.
-template <int DT, int NB>
+// 128 bytes of every row), each with DEPTH steps of loads in flight.  The filters go straight from memory into 16x16 MFMA
+// registers.  The images come from L2 in whole lines and change lanes in a piece of LDS that only this wave uses, without a
+// barrier: loaded as the MFMA wants them (16 rows of 64 bytes an instruction) they cost 33 clocks an instruction, as much
+// time as the filters.  The waves' sums meet in LDS and are added in wave order: deterministic, no workspace, one launch.
+// Bound by the stream of the weights.  6x6x256 -> 4096 at batch 20 in fp16 (75.5 MB): 16.5 us = 4.6 TB/s (23.5 with the
+// images in MFMA order); the best split of the general kernels took 31.9 us, the best without a workspace 163.  Layers of few rows split the reduction over four workgroups as
+// well (fp32 partial sums, second launch): 51 images, 18032 -> 1000 in fp32 101 -> 35 us.  3 images, 9506 -> 4096 (rows of
+// 38024 bytes), without a workspace 346 -> 29.5 us.
+template <int DT, int R8>
 struct FcmCfg {
     static constexpr int WAVES = 16, NT = 64 * WAVES;
-    static constexpr int VEC = FcVec<DT>::VEC, STEP = 4 * VEC;  // reduction elements per step: 4 lane groups x 16 bytes
-    static constexpr int DEPTH = 4;
+    static constexpr int NB = (R8 + 1) / 2;                     // blocks of 16 images
+    static constexpr int VEC = FcVec<DT>::VEC, STEP = 8 * VEC;  // reduction elements per step: 128 bytes of a row
+    static constexpr int DEPTH = R8 <= 4 ? 3 : 2;               // steps in flight
+    static constexpr int PITCH = 128 + 16;                      // bytes of an image's piece in LDS: 8 rows on distinct banks
+    static constexpr size_t X_BYTES = (size_t)WAVES * NB * 16 * PITCH, RED_BYTES = sizeof(float) * WAVES * NB * 16 * 17;
+    static constexpr size_t LDS_BYTES = X_BYTES > RED_BYTES ? X_BYTES : RED_BYTES;
 };
 
-template <int DT, int NB, bool TAIL>
+template <int DT, int R8, bool TAIL>
 __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
 {
-    typedef FcmCfg<DT, NB> CFG;
+    typedef FcmCfg<DT, R8> CFG;
     typedef typename Prec<DT>::elem_t elem_t;
     typedef Mma<DT, 16> mma_t;
-    constexpr int DEPTH = CFG::DEPTH, WAVES = CFG::WAVES;
+    constexpr int DEPTH = CFG::DEPTH, WAVES = CFG::WAVES, NB = CFG::NB, VEC = CFG::VEC, STEP = CFG::STEP, PITCH = CFG::PITCH;
     constexpr uint32_t ES = sizeof(elem_t);
-    __shared__ float red[WAVES][NB * 16][17];
+    extern __shared__ __attribute__((aligned(16))) unsigned char fcm_lds[];
+    typedef float red_t[NB * 16][17];
+    red_t* const red = (red_t*)fcm_lds;
 
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -229,25 +234,47 @@ __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
     const __amdgpu_buffer_rsrc_t rfilt = make_rsrc(a.filt, a.filt_bytes);
 
-    // byte offsets at this lane's first step; rows past K, images past N and elements past the row's end read as zero
-    const int q0 = wave * CFG::STEP + g * CFG::VEC;
-    const uint32_t a_off = k0 + li < a.K ? ((uint32_t)(k0 + li) * (uint32_t)a.Q + (uint32_t)q0) * ES : kOutOfRange;
-    uint32_t b_off[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) b_off[nb] = nb * 16 + li < a.N ? ((uint32_t)(nb * 16 + li) * (uint32_t)a.Q + (uint32_t)q0) * ES : kOutOfRange;
+    // A step of a wave is 128 bytes of every row.  Filters: lane (li, g) takes vectors g and 4 + g of row li, as the MFMA
+    // wants them.  Images: lane l takes vector l % 8 of image 8j + l / 8, whole lines; they change lanes in LDS.  Rows past
+    // K, images past N and elements past the row's end read as zero.
+    const int w0 = wave * STEP;
+    const int qa = w0 + g * VEC, qx = w0 + (lane & 7) * VEC;
+    // (both tensors stay below 2 GiB: kFar plus any scalar offset is out of range)
+    constexpr uint32_t kFar = 0x80000000u;
+    const uint32_t a_off = k0 + li < a.K ? ((uint32_t)(k0 + li) * (uint32_t)a.Q + (uint32_t)qa) * ES : kFar;
+    const uint32_t x_off = ((uint32_t)(lane >> 3) * (uint32_t)a.Q + (uint32_t)qx) * ES, x_rows = (uint32_t)a.Q * 8u * ES;
+    const bool x_last = (R8 - 1) * 8 + (lane >> 3) < a.N;  // the other groups of eight images are whole
 
-    constexpr int STRIDE = WAVES * CFG::STEP, kPast = 0x40000000;
-    uint4 av[DEPTH], bv[DEPTH][NB];
-    auto load = [&](int slot, int i) {
-        const bool live = i != kPast && q0 + i * STRIDE < a.Q;
-        const uint32_t d = (uint32_t)(i * STRIDE) * ES;
-        av[slot] = buffer_load_vec(rfilt, live && a_off != kOutOfRange ? a_off + d : kOutOfRange);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) bv[slot][nb] = buffer_load_vec(rin, live && b_off[nb] != kOutOfRange ? b_off[nb] + d : kOutOfRange);
+    constexpr int STRIDE = WAVES * STEP, kPast = 0x40000000;
+    uint4 av[DEPTH][2], xv[DEPTH][R8];
+    auto fetch = [](__amdgpu_buffer_rsrc_t r, uint32_t off, uint32_t soff) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)soff, 0);
+        return make_uint4(v.x, v.y, v.z, v.w);
     };
-    auto cut = [](uint4 v, int elems) {  // keeps the first `elems` elements (rows hold whole words)
-        const int words = elems * (int)ES / 4;
-        return make_uint4(words > 0 ? v.x : 0u, words > 1 ? v.y : 0u, words > 2 ? v.z : 0u, words > 3 ? v.w : 0u);
+    auto load = [&](int slot, int i) {
+        const bool some = i != kPast;
+        const uint32_t d = some ? (uint32_t)(i * STRIDE) * ES : 0u;
+        const int left = some ? a.Q - i * STRIDE : 0;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) av[slot][u] = fetch(rfilt, qa + u * 4 * VEC < left ? a_off : kFar, d + u * 64u);
+#pragma unroll
+        for (int j = 0; j < R8; ++j)
+            xv[slot][j] = fetch(rin, qx < left && (j + 1 < R8 || x_last) ? x_off : kFar, d + (uint32_t)j * x_rows);
+    };
+    // the vector that holds a row's end goes on with the next row: keeps the elements before index a.Q (rows hold whole words)
+    auto cut = [&](uint4 v, int q) {
+        const int left = a.Q - q;
+        if (left <= 0 || left >= VEC) return v;
+        const int words = left * (int)ES / 4;
+        return make_uint4(v.x, words > 1 ? v.y : 0u, words > 2 ? v.z : 0u, words > 3 ? v.w : 0u);
+    };
+    unsigned char* const xs = fcm_lds + (size_t)wave * NB * 16 * PITCH;  // this wave's own piece
+    unsigned char* const x_dst = xs + (lane >> 3) * PITCH + (lane & 7) * 16;
+    const unsigned char* const x_src = xs + li * PITCH + g * 16;
+    // lanes read what other lanes of the wave wrote: LDS serves a wave's accesses in order, the compiler must keep theirs
+    auto wave_order = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     };
     typename mma_t::acc_t acc[NB];
 #pragma unroll
@@ -255,33 +282,40 @@ __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
     const int first = (int)blockIdx.y * a.steps_per_split;
     const int steps = (a.Q + STRIDE - 1) / STRIDE, last = first + a.steps_per_split < steps ? first + a.steps_per_split : steps;
 #pragma unroll
-    for (int j = 0; j < DEPTH; ++j) load(j, first + j < last ? first + j : kPast);
+    for (int s = 0; s < DEPTH; ++s) load(s, first + s < last ? first + s : kPast);
     for (int i = first; i < last; i += DEPTH) {
 #pragma unroll
-        for (int j = 0; j < DEPTH; ++j) {
+        for (int s = 0; s < DEPTH; ++s) {
+            if constexpr (TAIL) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) av[s][u] = cut(av[s][u], qa + u * 4 * VEC + (i + s) * STRIDE);
+#pragma unroll
+                for (int j = 0; j < R8; ++j) xv[s][j] = cut(xv[s][j], qx + (i + s) * STRIDE);
+            }
+            wave_order();
+#pragma unroll
+            for (int j = 0; j < R8; ++j) *(uint4*)(x_dst + j * 8 * PITCH) = xv[s][j];
+            wave_order();
+            const uint4 f[2] = {av[s][0], av[s][1]};
+            load(s, i + DEPTH + s < last ? i + DEPTH + s : kPast);
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (TAIL) {  // the vector that holds a row's end goes on with the next row: cut both operands there
-                const int left = a.Q - (q0 + (i + j) * STRIDE);
-                if (left > 0 && left < CFG::VEC) {
-                    av[j] = cut(av[j], left);
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) bv[j][nb] = cut(bv[j][nb], left);
-                }
-            }
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                if constexpr (DT == CONV_F32) {
-                    acc[nb] = mma_t::run(__builtin_bit_cast(float, av[j].x), __builtin_bit_cast(float, bv[j][nb].x), acc[nb]);
-                    acc[nb] = mma_t::run(__builtin_bit_cast(float, av[j].y), __builtin_bit_cast(float, bv[j][nb].y), acc[nb]);
-                    acc[nb] = mma_t::run(__builtin_bit_cast(float, av[j].z), __builtin_bit_cast(float, bv[j][nb].z), acc[nb]);
-                    acc[nb] = mma_t::run(__builtin_bit_cast(float, av[j].w), __builtin_bit_cast(float, bv[j][nb].w), acc[nb]);
-                } else {
-                    acc[nb] = mma_t::run(av[j], bv[j][nb], acc[nb]);
+                for (int nb = 0; nb < NB; ++nb) {
+                    const uint4 x = *(const uint4*)(x_src + nb * 16 * PITCH + u * 64);
+                    if constexpr (DT == CONV_F32) {
+                        acc[nb] = mma_t::run(__builtin_bit_cast(float, f[u].x), __builtin_bit_cast(float, x.x), acc[nb]);
+                        acc[nb] = mma_t::run(__builtin_bit_cast(float, f[u].y), __builtin_bit_cast(float, x.y), acc[nb]);
+                        acc[nb] = mma_t::run(__builtin_bit_cast(float, f[u].z), __builtin_bit_cast(float, x.z), acc[nb]);
+                        acc[nb] = mma_t::run(__builtin_bit_cast(float, f[u].w), __builtin_bit_cast(float, x.w), acc[nb]);
+                    } else {
+                        acc[nb] = mma_t::run(f[u], x, acc[nb]);
+                    }
                 }
-            }
-            load(j, i + DEPTH + j < last ? i + DEPTH + j : kPast);
         }
     }
+    __syncthreads();  // the images' pieces are dead: the sums overlay them
     // lane (li, g): image nb*16 + li, rows 4g .. 4g+3
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
@@ -305,18 +339,21 @@ __global__ __launch_bounds__(1024) void fcm_kernel(ConvArgs a)
     }
 }
 
-template <int DT, int NB, bool TAIL>
+template <int DT, int R8, bool TAIL>
 hipError_t fcm_launch(const Variant& v, ConvArgs& a, hipStream_t s)
 {
-    constexpr int STRIDE = FcmCfg<DT, NB>::WAVES * FcmCfg<DT, NB>::STEP;
+    const hipError_t e = ensure_dynamic_lds((const void*)fcm_kernel<DT, R8, TAIL>, FcmCfg<DT, R8>::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    constexpr int STRIDE = FcmCfg<DT, R8>::WAVES * FcmCfg<DT, R8>::STEP;
     const int steps = (a.Q + STRIDE - 1) / STRIDE;
     a.nsplit = v.split;
     a.steps_per_split = (steps + v.split - 1) / v.split;
-    hipLaunchKernelGGL((fcm_kernel<DT, NB, TAIL>), dim3((unsigned)((a.K + 15) / 16), (unsigned)v.split), dim3(1024), 0, s, a);
+    constexpr size_t lds = FcmCfg<DT, R8>::LDS_BYTES;
+    hipLaunchKernelGGL((fcm_kernel<DT, R8, TAIL>), dim3((unsigned)((a.K + 15) / 16), (unsigned)v.split), dim3(1024), lds, s, a);
     return hipGetLastError();
 }
 
-template <int DT, int NB, bool TAIL>
+template <int DT, int R8, bool TAIL>
 bool fcm_valid(const Variant& v, const conv_desc& d, int OH, int OW)
 {
     if (d.dtype != DT) return false;
@@ -324,42 +361,50 @@ bool fcm_valid(const Variant& v, const conv_desc& d, int OH, int OW)
     const long long Q = (long long)d.C * d.R * d.S;
     // rows and images start on 16-byte boundaries, or (TAIL) at least on 4-byte ones
     if ((Q % FcVec<DT>::VEC != 0) != TAIL || Q * dtype_size(DT) % 4 != 0) return false;
-    constexpr int STRIDE = FcmCfg<DT, NB>::WAVES * FcmCfg<DT, NB>::STEP;
-    if (Q > 0x3fffffffLL || (v.split > 1 && (Q + STRIDE - 1) / STRIDE < 4 * v.split)) return false;
-    return (TAIL || d.N > 8) && d.N <= NB * 16 && d.N > (NB - 1) * 16;
+    if ((long long)d.K * Q * dtype_size(DT) >= (1LL << 31) || (long long)d.N * Q * dtype_size(DT) >= (1LL << 31)) return false;
+    constexpr int STRIDE = FcmCfg<DT, R8>::WAVES * FcmCfg<DT, R8>::STEP;
+    if (Q > 0x3fffffffLL || (v.split > 1 && (Q + STRIDE - 1) / STRIDE < 2 * v.split)) return false;
+    return (TAIL || d.N > 8) && d.N <= R8 * 8 && d.N > (R8 - 1) * 8;
 }
 
-template <int DT, int NB, bool TAIL>
+template <int DT, int R8, bool TAIL>
 void fcm_register_one(std::vector<Variant>& out, int split)
 {
     Variant v;
     char buf[96];
-    snprintf(buf, sizeof buf, "fc_%s_mfma_rows16_n%d%s%s", dtype_name(DT), NB * 16, TAIL ? "_t" : "", split > 1 ? "_sk4" : "");
+    snprintf(buf, sizeof buf, "fc_%s_mfma_rows16_n%d%s%s", dtype_name(DT), R8 * 8, TAIL ? "_t" : "", split > 1 ? "_sk4" : "");
     v.name = buf;
     v.dtype = DT;
     v.split = split;
     v.tm = 16;
-    v.tn = NB * 16;
-    v.tk = 16 * FcmCfg<DT, NB>::STEP;
+    v.tn = R8 * 8;
+    v.tk = 16 * FcmCfg<DT, R8>::STEP;
     v.threads = 1024;
     v.family = FAM_FC;
     v.specificity = 6;
-    v.valid = &fcm_valid<DT, NB, TAIL>;
-    v.launch = &fcm_launch<DT, NB, TAIL>;
+    v.valid = &fcm_valid<DT, R8, TAIL>;
+    v.launch = &fcm_launch<DT, R8, TAIL>;
     out.push_back(v);
 }
 template <int DT>
 void fcm_register_dtype(std::vector<Variant>& out)
 {
     for (int split : {1, 4}) {
-        fcm_register_one<DT, 1, false>(out, split);
         fcm_register_one<DT, 2, false>(out, split);
         fcm_register_one<DT, 3, false>(out, split);
         fcm_register_one<DT, 4, false>(out, split);
+        fcm_register_one<DT, 5, false>(out, split);
+        fcm_register_one<DT, 6, false>(out, split);
+        fcm_register_one<DT, 7, false>(out, split);
+        fcm_register_one<DT, 8, false>(out, split);
         fcm_register_one<DT, 1, true>(out, split);
         fcm_register_one<DT, 2, true>(out, split);
         fcm_register_one<DT, 3, true>(out, split);
         fcm_register_one<DT, 4, true>(out, split);
+        fcm_register_one<DT, 5, true>(out, split);
+        fcm_register_one<DT, 6, true>(out, split);
+        fcm_register_one<DT, 7, true>(out, split);
+        fcm_register_one<DT, 8, true>(out, split);
     }
 }
 
