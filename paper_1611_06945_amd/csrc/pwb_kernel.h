@@ -11,7 +11,8 @@
 //   * A lane ends with NPX neighbouring pixels of each channel: stores of 4 or 8 bytes, runs of 128 or 256 bytes.
 // Measured: 64 images of 28x28x256 -> 128 in fp16 (38.5 MB) 12.1 us = 3.2 TB/s, of the 4.7 a large copy reaches, with 64 x 512
 // tiles (17.2 us for the best of the other kernels, 32.5 for the one the cost model took).  What is left is start-up: the
-// filters' latency, the first groups' latency and the tail of a launch that is little more than one round.
+// filters' latency, the first groups' latency and the tail of a launch that is little more than one round (two waves or one
+// per workgroup, for more workgroups: 13.1 and 13.2 us).
 #pragma once
 
 #include "pwin_kernel.h"
