@@ -111,11 +111,13 @@ __global__ __launch_bounds__(CFG::NT, 2) void pwb_kernel(ConvArgs a)
     __syncthreads();
 
     const uint16_t* frag = Fs + li * pitch + g * 8;
-    for (int grp = 0; grp < G; grp += GD) {
+    // one pass over the ring; in the last, partial one the spare slots are left out (their input is zero, but an infinite
+    // filter value times zero would not be)
+    auto pass = [&](auto last_c, int grp) {
+        constexpr bool LAST = decltype(last_c)::value;
         static_for<GD>([&](auto sc) {
             constexpr int slot = decltype(sc)::value;
-            // groups past the last one were loaded as zeros; their filters are not in LDS: any finite row will do
-            const int ga = grp + slot < G ? grp + slot : 0;
+            if (LAST && grp + slot >= G) return;
             uint4 b[NPX];
 #pragma unroll
             for (int nb = 0; nb < NPX; ++nb) {
@@ -125,16 +127,19 @@ __global__ __launch_bounds__(CFG::NT, 2) void pwb_kernel(ConvArgs a)
                 for (int j = 0; j < 4; ++j) w[j] = __builtin_amdgcn_perm(xr[slot][2 * j + 1][nb / 2], xr[slot][2 * j][nb / 2], sel);
                 b[nb] = make_uint4(w[0], w[1], w[2], w[3]);
             }
-            load_group(sc, grp + GD + slot);
+            if constexpr (!LAST) load_group(sc, grp + GD + slot);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int mb = 0; mb < TMB; ++mb) {
-                const uint4 f = *(const uint4*)(frag + mb * 32 * pitch + ga * 16);
+                const uint4 f = *(const uint4*)(frag + mb * 32 * pitch + (grp + slot) * 16);
 #pragma unroll
                 for (int nb = 0; nb < NPX; ++nb) acc[mb][nb] = mma_t::run(f, b[nb], acc[mb][nb]);
             }
         });
-    }
+    };
+    int grp = 0;
+    for (; grp + GD <= G; grp += GD) pass(std::false_type{}, grp);
+    if (grp < G) pass(std::true_type{}, grp);
 
     // ---- bias + activation + rounding; lane (li, g) holds channels 8i + 4g .. +3 of a block at its NPX pixels -----------
     const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);
