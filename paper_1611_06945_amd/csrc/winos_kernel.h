@@ -25,9 +25,12 @@
 // where 96 x 32 takes 218), and two workgroups of 32 x 32 per CU (vector work per product doubles: 350).
 // Measured (us per call, filter transform included, kernel before -> this one): 20 images of 13x13x256 -> 384 46.0 -> 37.1,
 // 64 of 56x56x64 -> 192 340 -> 218.
-// bf16 has fp32's exponent range, but not its infinities' arithmetic: an overflow or infinity in a split gives NaN, and
-// parts of numbers below 2^-110 can vanish.  An output tile that is not finite, or whose largest value is tiny and not
-// zero, is therefore summed again in fp32 from the definition (a loop that no ordinary layer enters).
+// Range: the parts of x reach 24 bits below x, which for |x| < 2^-102 is below bf16's normal numbers.  Both operands are
+// therefore scaled by 2^24 ahead of the splits: every part of every fp32 number, subnormal ones included, is then a normal
+// bf16 number or zero, whatever the other operand is.  Sums carry 2^48 and are scaled back behind the inverse transform.
+// What this can lose is at the upper end, and shows: an operand above 2^103, a sum above 2^79 or an infinity gives an
+// infinity or a NaN in every output that it reaches.  An output tile that is not finite is summed again in fp32 from the
+// definition.
 #pragma once
 
 #include "pwin_kernel.h"
@@ -47,6 +50,9 @@ struct WinosCfg {
     static constexpr int MP = TT + 4;     // row pitch of the plane buffer of the epilogue
     static constexpr int E_FLOATS = (MB < 2 ? MB : 2) * 16 * 32 * MP;  // two 32-channel blocks at a time
     static constexpr int SLOTS = NT * LBV;  // 16-byte vectors of input rows staged per step
+    // the inputs are scaled where that takes fewer instructions: staged rows 4 * LBV, transform 8 per thread and step (at
+    // equal counts the rows are better, beneath the stage with less vector work)
+    static constexpr bool SCALE_ROWS = LBV <= 2;
 };
 
 struct WinosGeom {
@@ -87,6 +93,8 @@ size_t winos_lds_bytes(int N, int W, int OH, int OW)
 
 inline size_t winos_filter_bytes(int K, int C) { return (size_t)((C + 15) / 16) * 16 * ((K + 31) / 32) * 3072; }
 
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;  // of either operand, and of the sum of their products
+
 struct Split3 {
     uint4 p[3];
 };
@@ -113,7 +121,7 @@ __device__ __forceinline__ Split3 split3(const float* x)
     return s;
 }
 
-// Filter transform: U[c / 16][xi][k / 32][part][lane][8], lane = k % 32 + 32 * (c % 16 / 8), 8 channels c % 8.  A
+// Filter transform, scaled: U[c / 16][xi][k / 32][part][lane][8], lane = k % 32 + 32 * (c % 16 / 8), 8 channels c % 8.  A
 // workgroup takes 32 filters x 16 channels: their values go to LDS as contiguous runs, then wave w computes planes 2w and
 // 2w+1 of its lanes' eight channels and stores each part as one contiguous kilobyte.
 __global__ __launch_bounds__(512) void winos_filter_kernel(const float* __restrict__ filt, uint4* __restrict__ U, int K, int C)
@@ -140,11 +148,11 @@ __global__ __launch_bounds__(512) void winos_filter_kernel(const float* __restri
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         const float* g = g_s + kl * ROW + (g8 * 8 + c) * 9;
-        float t[3];  // row `row` of G g
+        float t[3];  // row `row` of G g, scaled (here and not at the loads, which would each be waited for: 1.3 us more)
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const float g0 = g[j], g1 = g[3 + j], g2 = g[6 + j];
-            t[j] = row == 0 ? g0 : row == 3 ? g2 : 0.5f * ((g0 + g2) + (row == 1 ? g1 : -g1));
+            t[j] = row == 0 || row == 3 ? kSplitScale * (row == 0 ? g0 : g2) : 0.5f * kSplitScale * ((g0 + g2) + (row == 1 ? g1 : -g1));
         }
         const float s = t[0] + t[2];
         u[0][c] = (wave & 1) ? 0.5f * (s - t[1]) : t[0];
@@ -249,7 +257,7 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
         for (int i = 0; i < LBV; ++i) {
             float* dst = Rs + r_lds[i];  // (a task without a row writes to its own spare vector behind the rows)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) dst[j] = r.v[i][j];
+            for (int j = 0; j < 4; ++j) dst[j] = CFG::SCALE_ROWS ? r.v[i][j] * kSplitScale : r.v[i][j];
         }
     };
 
@@ -284,10 +292,12 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            t[0][j] = d[0][j] - d[2][j];
-            t[1][j] = d[1][j] + d[2][j];
-            t[2][j] = d[2][j] - d[1][j];
-            t[3][j] = d[1][j] - d[3][j];
+            constexpr float sc = CFG::SCALE_ROWS ? 1.0f : kSplitScale;
+            const float d1 = d[1][j] * sc, d2 = d[2][j] * sc;
+            t[0][j] = __builtin_fmaf(d[0][j], sc, -d2);
+            t[1][j] = d1 + d2;
+            t[2][j] = d2 - d1;
+            t[3][j] = __builtin_fmaf(d[3][j], -sc, d1);
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -366,7 +376,7 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
         p1 = split_plane(v1);
         multiply(c0_t{}, p0, (uint32_t)i);
         write_tile(d);
-        interleave(std::integral_constant<int, (96 + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (8 + 6 * MB - 1) / (6 * MB)>{});
+        interleave(std::integral_constant<int, ((CFG::SCALE_ROWS ? 96 : 104) + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (8 + 6 * MB - 1) / (6 * MB)>{});
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
         const Plane v0 = read_plane(0);
@@ -422,10 +432,10 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
             a.dX.divmod(ok ? (uint32_t)t : 0u, gr, tx);
             a.dZ.divmod(gr, n, ty);
             const int oy = 2 * (int)ty, ox = 2 * (int)tx;
-            // a NaN or an infinity fails the first test; kTiny: parts of smaller operands may be below bf16's range
-            constexpr float kTiny = 0x1p-60f;
             const float big = (__builtin_fabsf(y[0]) + __builtin_fabsf(y[1])) + (__builtin_fabsf(y[2]) + __builtin_fabsf(y[3]));
-            if (ok && (!(big < __builtin_inff()) || (big < kTiny && big != 0.0f))) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) y[q] *= kSplitUnscale;
+            if (ok && !(big < __builtin_inff())) {  // a NaN or an infinity in any of the four
                 const float* const in = (const float*)a.in + (size_t)n * a.C * a.HW;
                 const float* const f = (const float*)a.filt + (size_t)k * a.C * 9;
 #pragma unroll 1
