@@ -78,6 +78,35 @@ def test_operands_outside_the_range_of_the_parts(kind):
         assert oracle.max_normalised_error(got[inside], ref[inside]) <= TOL[wl.F32], name
 
 
+def again_case(shape, kind):
+    """Data of which one tile, a few of a wave's entries, all of one filter's or all of them are summed again."""
+    x = wl.draw(("halfnormal", 1.0), shape.in_shape(), 4394).astype(np.float32)
+    f = wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), 4395).astype(np.float32)
+    if kind == "corners":
+        x[0, 0, 0, 0], x[-1, -1, -1, -1], x[-1, 3, 0, -1], x[0, 5, -1, 0] = np.nan, np.inf, -np.inf, np.nan
+    elif kind == "filter":
+        f[shape.K // 2, 1, 2, 0], f[-1, -1, 0, 1] = np.nan, -np.inf
+    elif kind == "huge":  # finite, every sum beyond what the scaled products can hold
+        x *= np.float32(1e26)
+    else:
+        x[:] = np.inf
+    return DeviceCase(shape, wl.F32, {"in": x, "filt": f, "bias": np.full(shape.K, 0.25, dtype=np.float32)}, relu=False)
+
+
+@pytest.mark.parametrize("kind", ["corners", "filter", "huge", "infinities"])
+@pytest.mark.parametrize("si", [1, 2, 3, 4, 7])
+def test_tiles_summed_again(si, kind):
+    case = again_case(SHAPES[si], kind)
+    with np.errstate(all="ignore"):
+        ref = case.ref()
+    finite = np.isfinite(ref)
+    for vi, name in variants_of(case):
+        got = to_host_f64(case.run(variant=vi), wl.F32)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        if finite.any():
+            assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
+
+
 # (scale of the inputs, of the filters): parts of one operand below bf16's normal numbers or below its range, the other large
 # enough for ordinary results; both small; subnormal inputs
 SCALES = [(2.0**-120, 2.0**80), (2.0**-124, 2.0**100), (2.0**60, 2.0**-118), (2.0**-140, 2.0**100), (2.0**-60, 2.0**-52), (2.0**-100, 1.0)]
