@@ -216,11 +216,20 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
 {
     const double P = (double)d.N * OH * OW, Q = (double)d.C * d.R * d.S;
     if (v.family == FAM_FC) {
-        // weight streaming: always ahead of the MFMA tiles when valid; split over four workgroups where the rows alone leave
-        // CUs without one
-        // (51 images, 18032 -> 1000 in fp32: 35 us against 85 whole; small layers lose the second launch: 12 images, 576 -> 1000
-        // take 5 us whole)
-        if (v.tm == 16) return (v.split > 1) == (d.K <= 16 * 128 && (double)d.K * Q > 4.0e6) ? 1.0 : 2.0;
+        if (v.tm == 16) {
+            // matrix-unit kernel: workgroups of 16 rows, a step per 2 KB of a row (v.tk elements), or the stream of the weights;
+            // 782 measured calls (rms 10 %).  51 images, 18032 -> 1000 in fp32: 35 us split over four workgroups, 85 whole
+            const double es = (double)dtype_size(d.dtype), groups = std::ceil(d.N / 8.0), blocks = std::ceil(groups / 2.0);
+            const double steps = std::ceil(std::ceil(Q / v.tk) / v.split), rounds = std::ceil(std::ceil(d.K / 16.0) * v.split / 256.0);
+            const double own = 0.85 + 0.47 * blocks + steps * (0.51 + 0.146 * groups + (d.dtype == CONV_F32 ? 0.18 * blocks : 0.0));
+            double t = 3.0 + std::max(rounds * own, d.K * Q * es / 4.6e6);
+            if (v.split > 1) t += 2.0 + 1.6e-5 * v.split * d.K * d.N;
+            // long rows: ahead of the other kernels' tiles, few and a serial chain each, whatever those are rated at; short rows
+            // are ready sooner without 16 waves' sums to add up (62 images, 48 -> 50 in bf16 3.7 against 7.5 us), and the tiles
+            // that serve them are rated 1.4-fold
+            const double row = Q * es, lng = d.dtype == CONV_F32 ? 14336.0 : 320.0, shrt = d.dtype == CONV_F32 ? 640.0 : 320.0;
+            return row >= lng ? 0.1 * t : row >= shrt ? 1.1 * t : 1.4 * t;
+        }
         return 1.0 + std::abs(v.tm - 4);
     }
     if (v.traits & TRAIT_PIXEL_STREAM) {
@@ -294,7 +303,10 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         // (... which is what many tiles wait for: 32 clocks of the CU per load instruction, 64 images of 28x28x256 -> 128 take
         // 32 us)
         const double loads = f32 ? 0.0 : tiles / 256.0 * (d.C / 16.0) * (v.tn / 32.0) * 8.0 * 0.0135;
-        return std::max(3.5 + loads, 3.2 + rounds * (0.9 + mfmas * (f32 ? 0.027 : 0.030) * std::max(1.0, share)) + 0.3 + 0.02 * kw);
+        // (one pixel an image: a load's lanes are a whole image apart, and memory serves them one by one; 9, 20 and 40 images of 2048
+        // channels take 18, 24 and 33 us)
+        const double apart = d.H * d.W == 1 ? d.C * 0.0155 * (0.25 + 0.75 * std::min(P, 32.0) / 32.0) : 0.0;
+        return apart + std::max(3.5 + loads, 3.2 + rounds * (0.9 + mfmas * (f32 ? 0.027 : 0.030) * std::max(1.0, share)) + 0.3 + 0.02 * kw);
     }
     if (v.traits & TRAIT_CHANNEL_WAVES) {
         // one workgroup per (channel tile, run of v.tn pixels); its v.threads / 64 waves split the channels, so a SIMD
