@@ -233,15 +233,23 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         return 1.0 + std::abs(v.tm - 4);
     }
     if (v.traits & TRAIT_PIXEL_STREAM) {
-        const double mt = std::ceil(d.K / (double)v.tm), wgs = mt * std::ceil(P / (double)v.tn);
-        const double per_cu = v.tm == 32 ? 3.0 : 2.0, rounds = std::ceil(wgs / (256.0 * per_cu));
-        // one workgroup: start, filters to LDS, groups, stores (46 images of 10x10x200 -> 352 with M128 13.6 us, with M32 8.2)
-        const double own = 1.5 + 0.02 * v.tm + d.C * (0.006 + 0.00016 * v.tm);
-        // the stream (input again from L2 for every further channel tile), faster with 8-byte loads and with two channel
-        // blocks per load; measured (model) on 64 images of 28x28x256 -> 128: M64 of 512 pixels 12.1 us (12.9), of 256 pixels
-        // 13.8 (16.4), M128 of 256 15.3 (15.7), M32 of 512 17.5 (17.6)
-        const double bytes = 2.0 * P * ((double)d.C * (1.0 + 0.1 * (mt - 1.0)) + d.K);
-        return 4.0 + std::max(bytes / (v.tn == 256 ? 3.3e6 : v.tm == 32 ? 3.4e6 : 4.6e6), rounds * own);
+        // workgroups that pass filters and groups of 16 channels one after another, as many to a CU as LDS and registers
+        // hold (which gains the larger tiles more than the smaller), against the stream, its input partly again from
+        // memory for every further channel tile.  Per tile: us of a call, a workgroup and a group, TB/s, share of the input
+        // and growth of a round with the workgroups on a CU; 1480 measured calls (rms 8 to 14 %)
+        static const struct { int tm, tn; double call, own, group, rate, again, grow; } tiles[] = {
+            {32, 512, 3.3, 2.44, 0.218, 6.96, 0.50, 0.85}, {32, 256, 2.5, 2.74, 0.136, 5.56, 0.41, 0.65},
+            {64, 512, 4.4, 1.53, 0.251, 6.15, 0.42, 0.93}, {64, 256, 2.8, 3.68, 0.197, 5.74, 0.56, 0.39},
+            {128, 256, 4.6, 3.91, 0.315, 4.24, 0.54, 0.31}};
+        for (const auto& c : tiles) {
+            if (c.tm != v.tm || c.tn != v.tn) continue;
+            const double groups = std::ceil(d.C / 16.0), mt = std::ceil(d.K / (double)v.tm), wgs = mt * std::ceil(P / (double)v.tn);
+            const double fit = std::floor(160.0 * 1024.0 / (v.tm * (groups * 16.0 + 8.0) * 2.0));
+            const double per_cu = std::max(1.0, std::min(v.tm == 32 ? 3.0 : 2.0, fit)), rounds = std::ceil(wgs / (256.0 * per_cu));
+            const double busy = rounds * std::pow(std::min(per_cu, std::max(1.0, wgs / 256.0)), c.grow) * (c.own + groups * c.group);
+            const double stream = 2.0 * P * ((double)d.C * (1.0 + c.again * (mt - 1.0)) + d.K) / (c.rate * 1e6);
+            return c.call + std::cbrt(busy * busy * busy + stream * stream * stream);
+        }
     }
     if (v.traits & TRAIT_SPLIT_PRODUCTS) {
         // Winograd on split products: v.tm / 32 blocks of 32 channels; a workgroup costs its start, planes and stores and a
@@ -296,17 +304,20 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double kw = v.threads / 64.0, tiles = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn);
         const double per_cu = std::max(1.0, std::floor(16.0 / kw));
         const double rounds = std::ceil(tiles / (256.0 * per_cu));
-        // (16-bit storage: one 32x32x16 MFMA of 16 ns per group of 16 channels, fed by eight 2-byte loads per lane)
-        const bool f32 = d.dtype == CONV_F32;
-        const double mfmas = std::ceil(d.C / (f32 ? 8.0 : 16.0) / kw) * (f32 ? 4.0 : 1.0) * (v.tm / 32.0) * (v.tn / 32.0);
-        const double share = std::min(per_cu, std::max(1.0, tiles / 256.0)) * kw / 4.0;  // waves per SIMD
-        // (... which is what many tiles wait for: 32 clocks of the CU per load instruction, 64 images of 28x28x256 -> 128 take
-        // 32 us)
-        const double loads = f32 ? 0.0 : tiles / 256.0 * (d.C / 16.0) * (v.tn / 32.0) * 8.0 * 0.0135;
         // (one pixel an image: a load's lanes are a whole image apart, and memory serves them one by one; 9, 20 and 40 images of 2048
         // channels take 18, 24 and 33 us)
         const double apart = d.H * d.W == 1 ? d.C * 0.0155 * (0.25 + 0.75 * std::min(P, 32.0) / 32.0) : 0.0;
-        return apart + std::max(3.5 + loads, 3.2 + rounds * (0.9 + mfmas * (f32 ? 0.027 : 0.030) * std::max(1.0, share)) + 0.3 + 0.02 * kw);
+        const double mb = v.tm / 32.0, nb = v.tn / 32.0;
+        if (d.dtype != CONV_F32) {
+            // 16-bit storage, eight 2-byte loads per lane for an MFMA: either the waves of a SIMD wait for memory, group after
+            // group, or the CU for its load instructions and the exchange of many tiles; 2400 measured calls (rms 17 %)
+            const double groups = std::ceil(d.C / 16.0), mine = std::ceil(groups / kw);
+            const double chain = rounds * (0.8 + 0.2 * kw + mine * (0.25 * nb + 0.02 * mb));
+            return apart + 3.5 + std::max(chain, tiles / 256.0 * (0.6 + 0.2 * kw + 0.063 * groups * nb + 0.077 * mb * nb * kw));
+        }
+        const double mfmas = std::ceil(d.C / 8.0 / kw) * 4.0 * mb * nb;
+        const double share = std::min(per_cu, std::max(1.0, tiles / 256.0)) * kw / 4.0;  // waves per SIMD
+        return apart + 3.2 + rounds * (0.9 + mfmas * 0.027 * std::max(1.0, share)) + 0.3 + 0.02 * kw;
     }
     if (v.traits & TRAIT_CHANNEL_WAVES) {
         // one workgroup per (channel tile, run of v.tn pixels); its v.threads / 64 waves split the channels, so a SIMD
@@ -356,6 +367,9 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
     const double rounds = std::ceil(tiles / (256.0 * wg_per_cu));
     const double sharing = std::min(wg_per_cu, std::max(1.0, tiles / 256.0));
     double t = 4.0 + rounds * steps * t_step * std::pow(sharing, 0.4);
+    // (16-bit pointwise layers of one row of tiles: no faster than half the rate of a copy; 48 images of 40x38x1024 -> 8 take 59 us)
+    if (v.family != FAM_NHWC && d.dtype != CONV_F32 && d.R * d.S == 1 && d.C % 8 == 0 && d.K <= 32)
+        t = std::max(t, 2.0 + 4.0 / 4.7e6 * ((double)d.N * d.C * d.H * d.W + d.K * P) + 0.1 * t);
     if (v.split > 1) t += 2.0 + (double)v.split * d.K * P * 4.0 / 2.0e6;
     // a conversion launch ahead of the kernel: its launch plus input and filters read and written once
     if (v.traits & TRAIT_CONVERTS_FIRST) t += 3.0 + 2.0 * ((double)d.N * d.C * d.H * d.W + (double)d.K * Q) * 2.0 / 2.0e6;

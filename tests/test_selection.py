@@ -38,3 +38,22 @@ def test_long_fully_connected_rows_go_to_the_matrix_unit_kernel(shape, dtype, sp
     name, nows = picks(shape, dtype)
     assert "_mfma_rows16_" in name and name.endswith("_sk4") == split, name
     assert "_mfma_rows16_" in nows and not nows.endswith("_sk4"), nows
+
+
+# 16-bit pointwise layers: what was taken, its us, what may be taken, its us
+@pytest.mark.parametrize("shape,dtype,slow,slow_us,fast_us", [
+    (ConvShape(2, 128, 125, 125, 64, 1, 1, 1, 0), wl.F16, ("pwk_f16_M64N32_w8", "pwk_f16_M32N32"), 20.8, 12.1),
+    (ConvShape(14, 128, 30, 28, 112, 1, 1, 1, 0), wl.F16, ("pwk_f16_M64N32_w8", "pwk_f16_M32N32"), 16.2, 9.7),
+    (ConvShape(12, 208, 15, 15, 320, 1, 1, 1, 0), wl.BF16, ("pwk_bf16_M64N32_w8", "pwk_bf16_M32"), 11.5, 7.4),
+    (ConvShape(48, 1024, 40, 38, 8, 1, 1, 1, 0), wl.F16, ("ug_", "igemm_"), 59.0, 39.0),
+    (ConvShape(21, 880, 58, 58, 10, 1, 1, 1, 0), wl.F16, ("ug_", "igemm_"), 52.0, 35.6),
+    (ConvShape(14, 448, 47, 47, 16, 1, 1, 1, 0), wl.BF16, ("ug_", "igemm_"), 14.7, 12.4),
+])
+def test_pointwise_layers_keep_the_faster_kernel(shape, dtype, slow, slow_us, fast_us):
+    for name in picks(shape, dtype):
+        assert not name.startswith(slow), (name, slow_us, fast_us)
+
+
+def test_many_pixels_of_a_pointwise_layer_go_to_the_streaming_kernel():
+    for name in picks(ConvShape(64, 256, 28, 28, 128, 1, 1, 1, 0), wl.F16):  # us: 12.4, of the wave-split kernel 33
+        assert name.startswith("pwb_f16_M64N512"), name
