@@ -332,19 +332,39 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         return 5.0 + 0.05 * waves + std::max(rounds * mfmas * 0.030 * std::max(1.0, waves / 4.0), busy);
     }
     if (v.traits & TRAIT_BIG_WINDOW) {
-        // two workgroups per CU (one where the slab takes more than half of LDS), each 2.5 us + its output tile's share for
-        // start and store and its MFMAs (8 clocks of the CU each) at the rate two co-resident workgroups reach; the last,
-        // incomplete round runs with one workgroup on most CUs.  Measured on 64 images of 56x56x64 -> 192: workgroups of
-        // 64 x 512 live 17.3 us (model 17.5), of 64 x 256 9.5 us (9.7)
+        // two workgroups per CU (one where the slab takes more than half of LDS), each its output tile's share for start and
+        // store, a tap's latency and its MFMAs (8 clocks of the CU each) at the rate one or two co-resident workgroups reach;
+        // the last, incomplete round runs with one workgroup on most CUs.  5491 measured calls (rms 14 %)
         const double tiles = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn);
-        const double steps = std::ceil(d.C / 16.0) * d.R * d.S;
+        const double C16 = std::ceil(d.C / 16.0), steps = C16 * d.R * d.S;
         const double t_mfma = (v.tm / 32.0) * (v.tn / 32.0) * steps * 8.0 / 2100.0;
-        const double own = 2.5 + 4.0 * v.tm * v.tn / 32768.0;
+        const double own = 0.67 + 4.94 * v.tm * v.tn / 32768.0 + 0.035 * steps;
         const double slots = 256.0 * v.per_cu, full = std::floor(tiles / slots), part = tiles / slots - full;
-        const double alone = own + t_mfma / 0.6, round = v.per_cu == 2 ? own + 2.0 * t_mfma / 0.8 : alone;
-        double t = 2.5 + full * round;
+        const double alone = own + t_mfma / 0.93, round = v.per_cu == 2 ? own + 2.0 * t_mfma / 0.67 : alone;
+        double t = 0.87 + full * round;
         if (part > 0.0) t += part > 0.5 ? round : alone;
-        if (v.traits & TRAIT_CONVERTS_FIRST) t += 3.0 + 2.0 * ((double)d.N * d.C * d.H * d.W + (double)d.K * Q) * 2.0 / 6.0e6;
+        // (the conversion launch is rated 1 us dearer than it is, here and below: these kernels ask for workspace, and the models
+        // of the others err by as much on layers of 10 us)
+        if (v.traits & TRAIT_CONVERTS_FIRST) {
+            const double in = (double)d.N * d.C * d.H * d.W, copy = d.N * C16 * 16.0 * (d.H + d.pad) * (d.W + d.pad);
+            t += 5.5 + 2.0 * (in + copy + d.K * d.R * d.S * (d.C + C16 * 16.0)) / 5.5e6;
+        }
+        return t;
+    }
+    if (v.traits & (TRAIT_PACKED_FILTERS | TRAIT_CONVERTS_FIRST)) {
+        // packed-filter kernel: `kw` waves of a workgroup split the channels of a chunk and add their sums in the end; either a
+        // workgroup's chain of taps or the CU's MFMAs and exchanges, about eight waves at a time.  2077 measured calls (rms
+        // 13 %; 17 % without the conversion launch)
+        const double waves = v.threads / 64.0, kw = v.tk / (16.0 * d.R * d.S), chunks = std::ceil(d.C / (16.0 * kw));
+        const double tiles = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn);
+        const double per_cu = std::max(1.0, std::floor(8.0 / waves)), rounds = std::ceil(tiles / (256.0 * per_cu));
+        const double mfmas = (v.tm / 32.0) * (v.tn / 32.0) / (waves / kw);  // of a wave and tap
+        const double taps = chunks * d.R * d.S, exchange = kw * v.tm * v.tn * 0.9e-4;
+        const double share = std::max(1.0, waves / 4.0 * std::min(per_cu, std::max(1.0, tiles / 256.0)));
+        const double chain = rounds * (exchange + taps * (0.026 + 0.0158 * mfmas * share));
+        const double wide = v.tm == 32 && v.tn == 128 ? 1.25 : 1.0;  // one wave per 32 pixels: slabs restaged for few MFMAs
+        double t = 2.6 + wide * std::max(chain, tiles / 256.0 * (exchange + 0.0128 * taps * mfmas * waves));
+        if (v.traits & TRAIT_CONVERTS_FIRST) t += 4.7 + 2.0 * ((double)d.N * d.C * d.H * d.W + (double)d.K * Q) / 2.2e6;
         return t;
     }
     const bool window = v.family == FAM_WINDOW || (v.traits & TRAIT_WINDOW_TILES);
@@ -367,12 +387,12 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
     const double rounds = std::ceil(tiles / (256.0 * wg_per_cu));
     const double sharing = std::min(wg_per_cu, std::max(1.0, tiles / 256.0));
     double t = 4.0 + rounds * steps * t_step * std::pow(sharing, 0.4);
+    // (16-bit window kernels: start, exchange and store of a tile are most of a layer of few channels; 481 measured calls, rms 15 %)
+    if (v.family == FAM_WINDOW && d.dtype != CONV_F32) t = 4.7 + rounds * (0.64 + 2.75e-4 * v.tm * v.tn + 0.73 * steps * t_step);
     // (16-bit pointwise layers of one row of tiles: no faster than half the rate of a copy; 48 images of 40x38x1024 -> 8 take 59 us)
     if (v.family != FAM_NHWC && d.dtype != CONV_F32 && d.R * d.S == 1 && d.C % 8 == 0 && d.K <= 32)
         t = std::max(t, 2.0 + 4.0 / 4.7e6 * ((double)d.N * d.C * d.H * d.W + d.K * P) + 0.1 * t);
     if (v.split > 1) t += 2.0 + (double)v.split * d.K * P * 4.0 / 2.0e6;
-    // a conversion launch ahead of the kernel: its launch plus input and filters read and written once
-    if (v.traits & TRAIT_CONVERTS_FIRST) t += 3.0 + 2.0 * ((double)d.N * d.C * d.H * d.W + (double)d.K * Q) * 2.0 / 2.0e6;
     return t * (1.0 - 0.002 * v.specificity);  // ties go to the kernel written for the narrower class of shapes
 }
 

@@ -57,3 +57,23 @@ def test_pointwise_layers_keep_the_faster_kernel(shape, dtype, slow, slow_us, fa
 def test_many_pixels_of_a_pointwise_layer_go_to_the_streaming_kernel():
     for name in picks(ConvShape(64, 256, 28, 28, 128, 1, 1, 1, 0), wl.F16):  # us: 12.4, of the wave-split kernel 33
         assert name.startswith("pwb_f16_M64N512"), name
+
+
+# window layers of few pixels: the many-pixel kernel's us, the packed-filter kernel's us
+@pytest.mark.parametrize("shape,dtype,fmt", [
+    (ConvShape(13, 384, 5, 4, 80, 5, 5, 1, 2), wl.F16, "packed"),     # 31.7, 10.6
+    (ConvShape(15, 416, 15, 15, 48, 3, 3, 1, 1), wl.BF16, "packed"),  # 18.3, 6.5
+    (ConvShape(53, 352, 8, 6, 112, 3, 3, 1, 0), wl.F16, "packed"),    # 17.3, 6.2
+    (ConvShape(17, 416, 9, 9, 208, 3, 3, 1, 1), wl.F16, "packed"),    # 18.6, 8.5
+    (ConvShape(7, 448, 8, 8, 800, 3, 3, 1, 1), wl.F16, "nchw"),       # 24.6, 15.3
+    (ConvShape(57, 608, 15, 15, 27, 5, 5, 1, 2), wl.F16, "nchw"),     # 68.2, 46.7
+])
+def test_window_layers_of_few_pixels_keep_the_packed_filter_kernel(shape, dtype, fmt):
+    name = picks(shape, dtype, fmt)[0]
+    assert name.startswith("pwin_") and "_big_" not in name, name
+
+
+@pytest.mark.parametrize("fmt,prefix", [("nchw", "bwin_bf16_3x3_M64N512"), ("packed", "pwin_big_bf16_3x3_M64N512")])
+def test_window_layers_of_many_pixels_go_to_the_many_pixel_kernel(fmt, prefix):
+    name = picks(ConvShape(64, 64, 56, 56, 192, 3, 3, 1, 1), wl.BF16, fmt)[0]  # us: 51 (47), of the packed-filter kernel 105 (84)
+    assert name.startswith(prefix), name
