@@ -1,6 +1,6 @@
-"""GPU parity of the matrix-unit kernel for fully-connected layers (more than eight images): ragged channel and image
-counts, reduction lengths that are no multiple of a step, one step and less, bit for bit on small integers and within the
-storage type's tolerance on random data."""
+"""GPU parity of the matrix-unit kernel for fully-connected layers: ragged channel counts, every count of eight-image groups,
+reduction lengths that are no multiple of a step, one step and less, bit for bit on small integers and within the storage
+type's tolerance on random data."""
 import pytest
 
 from paper_1611_06945_amd import workloads as wl
@@ -20,6 +20,19 @@ SHAPES = [
     ConvShape(20, 256, 7, 7, 33, 7, 7, 1, 0),
     ConvShape(3, 194, 7, 7, 50, 7, 7, 1, 0),    # 9506 elements: rows on 4-byte boundaries only, split and whole
     ConvShape(18, 3, 6, 5, 20, 6, 5, 1, 0),     # 90 elements: one cut vector per row
+    # every other count of eight-image groups (each is an instantiation with its own loads in flight; an odd one leaves half of
+    # its last LDS block unwritten), whole rows ...
+    ConvShape(25, 136, 6, 6, 33, 6, 6, 1, 0),
+    ConvShape(32, 72, 4, 4, 17, 4, 4, 1, 0),
+    ConvShape(41, 136, 6, 6, 20, 6, 6, 1, 0),
+    ConvShape(56, 264, 4, 4, 40, 4, 4, 1, 0),
+    # ... and rows whose end is cut, most of them long enough for the four-way split
+    ConvShape(16, 194, 7, 7, 20, 7, 7, 1, 0),
+    ConvShape(48, 7, 3, 6, 17, 3, 6, 1, 0),
+    ConvShape(32, 194, 7, 7, 18, 7, 7, 1, 0),
+    ConvShape(40, 2, 5, 9, 33, 5, 9, 1, 0),
+    ConvShape(49, 338, 7, 7, 19, 7, 7, 1, 0),
+    ConvShape(64, 194, 7, 7, 16, 7, 7, 1, 0),
 ]
 
 
