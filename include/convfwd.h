@@ -113,7 +113,8 @@ double conv_flops(const conv_desc* desc);
 /*
  * Bytes of device workspace with which every variant valid for `desc` can run
  * (split-reduction variants keep fp32 partial sums there, the Winograd variants
- * the transformed filters).  conv_fwd() needs none.  Returns 0 for an invalid
+ * the transformed filters, 16-bit window variants a copy of the input and the
+ * filters in the order their kernel reads).  conv_fwd() needs none.  Returns 0 for an invalid
  * descriptor.
  */
 size_t conv_workspace_bytes(const conv_desc* desc);
@@ -134,7 +135,10 @@ int conv_fwd(const conv_desc* desc, const void* in, const void* filt, const floa
  * reduced in a fixed order, or, for fp32 3x3 stride-1 layers, a Winograd
  * F(2x2,3x3) variant (the algorithm the paper names as its main open topic,
  * Section 4 "Experimental Results"), which first writes the transformed filters
- * there.  Results are bit-reproducible either way.  If `workspace_bytes` is too small for the selected variant
+ * there.  One of those (winos_*) multiplies on the 16-bit matrix units, each fp32 operand split into three parts that
+ * together hold all of it; results that are infinite, NaN or beyond about 2^79 it sums once more the direct way, so that a
+ * call with such data can take several times as long (up to about 20 times where every result is beyond that size).
+ * Results are bit-reproducible either way.  If `workspace_bytes` is too small for the selected variant
  * the best variant that fits is used instead; CONV_EWORKSPACE only if a forced
  * variant does not fit.
  */

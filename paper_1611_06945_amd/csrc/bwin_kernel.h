@@ -18,12 +18,10 @@
 // Measured (us per call, autotuned, before -> with this kernel): 64 images of 56x56x64 -> 192 in bf16 on the plain formats
 // 115.6 -> 55.1 (conversion launch 7.5, this kernel 47 = 0.94 PFLOP/s of the 1.4 a large library product reaches), with
 // packed filters 84 -> 47; 8 of 33x35x100 -> 130 (fp16) 35.2 -> 15.5; 16 of 112x112x64 -> 128 88 -> 46; 64 of 13x13x256 ->
-// 384 32.7 -> 28.0.  A workgroup of 64 x 512 outputs lives 17.3 us, two to a CU: start 3.4 (index arithmetic, first slab from
-// memory), 36 taps 10.5, rounding and turning 1.7, stores 1.7.  With its MFMAs taken out the same call takes 26 us, with any
-// one of stores, slab loads or filter loads taken out 46: no single path bounds it, the matrix units under load (1.4
-// PFLOP/s = 32 us for this layer) and the start and end of the workgroups add up.  A persistent form of the kernel, whose
-// first slab and filters of the next tile were fetched during the previous tile, needed 20 more registers and was slower
-// (49.9).
+// 384 32.7 -> 28.0.  Traced on the first layer: conversion launch 11 us (8 back to back), this kernel 43, the matrix units busy
+// for 47 % of it (they reach 1.4 PFLOP/s under load, 32 us for this layer); the start and end of a workgroup, in which it does not
+// multiply, are covered only as far as the other one on the CU does.  A persistent form of the kernel, whose first slab and
+// filters of the next tile were fetched during the previous tile, needed 20 more registers and was slower (49.9).
 //
 // The input slab comes either from a channel-innermost tensor (BLK = false), or (BLK = true: layers in the plain formats)
 // from a copy in the workspace that one conversion launch has written in exactly the order the slabs have: [16-channel

@@ -202,10 +202,10 @@ void fc_register_dtype(std::vector<Variant>& out)
 // registers.  The images come from L2 in whole lines and change lanes in a piece of LDS that only this wave uses, without a
 // barrier: loaded as the MFMA wants them (16 rows of 64 bytes an instruction) they cost 33 clocks an instruction, as much
 // time as the filters.  The waves' sums meet in LDS and are added in wave order: deterministic, no workspace, one launch.
-// Bound by the stream of the weights.  6x6x256 -> 4096 at batch 20 in fp16 (75.5 MB): 16.5 us = 4.6 TB/s (23.5 with the
-// images in MFMA order); the best split of the general kernels took 31.9 us, the best without a workspace 163.  Layers of few
-// rows split the reduction over four workgroups as well (fp32 partial sums, second launch): 51 images, 18032 -> 1000 in fp32 101 -> 35 us.  3 images, 9506 -> 4096 (rows of
-// 38024 bytes), without a workspace 346 -> 29.5 us.
+// Bound by the stream of the weights.  6x6x256 -> 4096 at batch 20 in fp16 (75.5 MB): 16.1 us = 4.7 TB/s (23.5 with the
+// images in MFMA order); the best split of the general kernels took 32, the best without a workspace 163.  Layers of few rows
+// split the reduction over four workgroups as well (fp32 partial sums, second launch): 51 images, 18032 -> 1000 in fp32 84 ->
+// 34 us.  3 images, 9506 -> 4096 (rows of 38024 bytes), without a workspace 346 -> 29.5 us.
 template <int DT, int R8>
 struct FcmCfg {
     static constexpr int WAVES = 16, NT = 64 * WAVES;

@@ -22,9 +22,10 @@
 // What bounds it: 64 channels x 32 tiles multiply for 1540 of the ~3000 clocks a step takes (LDS traffic ~1000, vector work
 // ~1400 of a SIMD, not all of it underneath); the start (5000 clocks) and the inverse transform (7000) of a workgroup are
 // exposed, with one workgroup per CU.  Tiles of 64 were tried (twice the registers, no room for the two-stage mix: 238 us
-// where 96 x 32 takes 218), and two workgroups of 32 x 32 per CU (vector work per product doubles: 350).
-// Measured (us per call, filter transform included, kernel before -> this one): 20 images of 13x13x256 -> 384 46.0 -> 37.1,
-// 64 of 56x56x64 -> 192 340 -> 218.
+// where 96 x 32 took 218), and two workgroups of 32 x 32 per CU (vector work per product doubles: 350).
+// Measured (us per call back to back, filter transform included, kernel before -> this one; boxes differ by up to 10 %): 20
+// images of 13x13x256 -> 384 46 -> 36, 64 of 56x56x64 -> 192 340 -> 198 .. 222.  With other inputs from call to call 32.8 and 217;
+// traced, in which a launch takes longer, 31.3 + 8.8 for the filter transform and 237 + 6.2.
 // Range: the parts of x reach 24 bits below x, which for |x| < 2^-102 is below bf16's normal numbers.  Both operands are
 // therefore scaled by 2^24 ahead of the splits: every part of every fp32 number, subnormal ones included, is then a normal
 // bf16 number or zero, whatever the other operand is.  Sums carry 2^48 and are scaled back behind the inverse transform.
