@@ -152,7 +152,8 @@ int conv_fwd_ws(const conv_desc* desc, const void* in, const void* filt, const f
  * nothing.  The variant is selected as conv_fwd_ws selects it with unlimited workspace (forced > autotuned/cached >
  * cost model); when that variant needs more than CONV_STATIC_SCRATCH_BYTES the call is rejected with CONV_EWORKSPACE
  * (conv_strerror names the variant and both sizes) and nothing is enqueued -- use conv_fwd or conv_fwd_ws then.  (The
- * kernels that keep a copy of the input or split filters in scratch, bwin_* and winos_*, give way to the pick that fits.)
+ * kernels that keep a copy of the input or split filters in scratch, bwin_*, pwin_*_prep and winos_*, give way to the pick
+ * that fits.)
  * Results are bit-identical to conv_fwd_ws running the same variant.  Nothing in the array has to start at zero
  * (every partial sum and every transformed filter is written before it is read), and its contents are undefined
  * afterwards.  Every call on one GPU shares that GPU's array: calls that overlap in time on one GPU (different

@@ -175,6 +175,7 @@ def test_operands_at_the_lower_end_of_the_range(xs, fs):
 @pytest.mark.parametrize("shape,dtype", [
     (ConvShape(24, 640, 14, 14, 1024, 3, 3, 1, 1), wl.F32),   # split filters of 63 MB
     (ConvShape(40, 128, 64, 56, 32, 3, 3, 1, 1), wl.BF16),    # an input copy of 38 MB
+    (ConvShape(39, 944, 28, 26, 10, 3, 3, 1, 1), wl.BF16),    # one of 54 MB, of the packed-filter kernel
 ])
 def test_static_scratch_serves_layers_whose_fastest_kernel_wants_more(shape, dtype):
     torch = torch_mod()
