@@ -363,7 +363,8 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double taps = chunks * d.R * d.S, exchange = kw * v.tm * v.tn * 0.9e-4;
         const double share = std::max(1.0, waves / 4.0 * std::min(per_cu, std::max(1.0, tiles / 256.0)));
         const double chain = rounds * (exchange + taps * (0.026 + 0.0158 * mfmas * share));
-        const double wide = v.tm == 32 && v.tn == 128 ? 1.25 : 1.0;  // one wave per 32 pixels: slabs restaged for few MFMAs
+        // (one wave per 32 pixels restages slabs for few MFMAs; the fit is 0.9 of the measured time on 5x5 windows)
+        const double wide = (v.tm == 32 && v.tn == 128 ? 1.25 : 1.0) * (d.R == 5 ? 1.1 : 1.0);
         double t = 2.6 + wide * std::max(chain, tiles / 256.0 * (exchange + 0.0128 * taps * mfmas * waves));
         if (v.traits & TRAIT_CONVERTS_FIRST) t += 4.7 + 2.0 * ((double)d.N * d.C * d.H * d.W + (double)d.K * Q) / 2.2e6;
         return t;
@@ -390,9 +391,9 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
     double t = 4.0 + rounds * steps * t_step * std::pow(sharing, 0.4);
     // (16-bit window kernels: start, exchange and store of a tile are most of a layer of few channels; 481 measured calls, rms 15 %)
     if (v.family == FAM_WINDOW && d.dtype != CONV_F32) t = 4.7 + rounds * (0.64 + 2.75e-4 * v.tm * v.tn + 0.73 * steps * t_step);
-    // (16-bit pointwise layers of one row of tiles: no faster than half the rate of a copy; 48 images of 40x38x1024 -> 8 take 59 us)
+    // (16-bit pointwise layers of one row of tiles: no faster than 0.55 of the rate of a copy; 48 images of 40x38x1024 -> 8 take 59 us)
     if (v.family != FAM_NHWC && d.dtype != CONV_F32 && d.R * d.S == 1 && d.C % 8 == 0 && d.K <= 32)
-        t = std::max(t, 2.0 + 4.0 / 4.7e6 * ((double)d.N * d.C * d.H * d.W + d.K * P) + 0.1 * t);
+        t = std::max(t, 2.0 + 3.6 / 4.7e6 * ((double)d.N * d.C * d.H * d.W + d.K * P) + 0.1 * t);
     if (v.split > 1) t += 2.0 + (double)v.split * d.K * P * 4.0 / 2.0e6;
     return t * (1.0 - 0.002 * v.specificity);  // ties go to the kernel written for the narrower class of shapes
 }
