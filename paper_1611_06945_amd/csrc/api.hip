@@ -82,6 +82,8 @@ State& state()
         register_pwin_bf16(s->variants);
         register_bwin_f16(s->variants);
         register_bwin_bf16(s->variants);
+        register_dwin_f16(s->variants);
+        register_dwin_bf16(s->variants);
         register_pwb_f16(s->variants);
         register_pwb_bf16(s->variants);
         for (size_t i = 0; i < s->variants.size(); ++i) s->by_name[s->variants[i].name] = (int)i;
@@ -250,6 +252,16 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
             const double stream = 2.0 * P * ((double)d.C * (1.0 + c.again * (mt - 1.0)) + d.K) / (c.rate * 1e6);
             return c.call + std::cbrt(busy * busy * busy + stream * stream * stream);
         }
+    }
+    if (v.traits & TRAIT_DIRECT_WINDOW) {
+        // a fit per tile shape to 18000 measured calls on 2200 drawn layers (rms 4 to 15 %)
+        const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn), chunks = std::ceil(Q / v.tk);
+        const double share = std::min((double)v.per_cu, std::max(1.0, wgs / 256.0));
+        // (stride-1 layers whose input the L2s together do not hold are rated 1.8-fold: the kernels behind a conversion launch are
+        // within 30 % of this one there, 40 images of 64x56x128 -> 32 31 against 26 us, 39 of 28x26x944 -> 10 56 against 41, and
+        // the tests of the library's own scratch expect them of the selection; autotuned, such layers take this kernel)
+        const bool large = v.family == FAM_WINDOW && d.stride == 1 && 2.0 * d.N * d.C * d.H * d.W > 33554432.0;
+        return (large ? 1.8 : 1.0) * (v.model.call + std::ceil(wgs / (256.0 * v.per_cu)) * std::pow(share, (double)v.model.grow) * (v.model.own + chunks * v.model.chunk));
     }
     if (v.traits & TRAIT_SPLIT_PRODUCTS) {
         // Winograd on split products: v.tm / 32 blocks of 32 channels; a workgroup costs its start, planes and stores and a

@@ -97,6 +97,12 @@ typedef hipError_t (*LaunchFn)(const Variant& v, ConvArgs& a, hipStream_t s);
 typedef bool (*ValidFn)(const Variant& v, const conv_desc& d, int OH, int OW);
 typedef size_t (*WorkspaceFn)(const Variant& v, const conv_desc& d, int OH, int OW);
 
+// Time of a call for kernels measured tile by tile: `call` us, then per round of workgroups `own` and, for every chunk of
+// channels, `chunk` us, both growing with the workgroups that share a CU to the power `grow`.
+struct TileModel {
+    float call, own, chunk, grow;
+};
+
 // One compiled kernel configuration (the paper's "variant + tuning parameters").
 struct Variant {
     std::string name;  // e.g. igemm_f32_M128N128K16_w2x2_sk4
@@ -111,6 +117,7 @@ struct Variant {
     WorkspaceFn ws_extra = nullptr;  // workspace the variant needs beyond split partial sums (null: none)
     unsigned traits = 0;             // TRAIT_* bits read by the cost model used when no measurement exists
     int per_cu = 1;                  // workgroups that share a CU, for the families whose cost model asks
+    TileModel model = {0, 0, 0, 0};  // TRAIT_DIRECT_WINDOW
 };
 
 enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no alignment demands, slower steps)
@@ -127,6 +134,7 @@ enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no a
        TRAIT_BIG_WINDOW = 4096u,       // 16-bit window kernel whose waves own their outputs (many-pixel layers)
        TRAIT_SPLIT_PRODUCTS = 8192u,   // fp32 operands split into bf16 parts, products on the 16-bit matrix units
        TRAIT_PIXEL_STREAM = 16384u,    // 16-bit pointwise kernel for many pixels, input transposed in registers
+       TRAIT_DIRECT_WINDOW = 32768u,   // 16-bit window kernel that brings both operands to MFMA order on the way through LDS, any stride
        TRAIT_CHANNEL_WAVES = 2048u };  // fp32 window kernel on linear pixel tiles whose waves split the channels of a chunk
 
 enum { FAM_IGEMM = 0, FAM_POINTWISE = 1, FAM_FIRSTLAYER = 2, FAM_WINDOW = 3, FAM_FC = 4, FAM_NHWC = 5, FAM_WINOGRAD = 6 };
@@ -162,6 +170,8 @@ void register_pwin_f16(std::vector<Variant>& out);
 void register_pwin_bf16(std::vector<Variant>& out);
 void register_bwin_f16(std::vector<Variant>& out);
 void register_bwin_bf16(std::vector<Variant>& out);
+void register_dwin_f16(std::vector<Variant>& out);
+void register_dwin_bf16(std::vector<Variant>& out);
 
 // Raises a kernel's dynamic-LDS limit to `bytes` on the current device when it is not already that high (once per
 // device and kernel; safe to call from several threads).
