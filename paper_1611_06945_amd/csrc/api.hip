@@ -68,6 +68,7 @@ State& state()
         register_wconv_f32(s->variants);
         register_wino_f32(s->variants);
         register_winos_f32(s->variants);
+        register_swins_f32(s->variants);
         register_swin_f16(s->variants);
         register_swin_bf16(s->variants);
         register_swinp_f16(s->variants);
@@ -262,6 +263,13 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         // the tests of the library's own scratch expect them of the selection; autotuned, such layers take this kernel)
         const bool large = v.family == FAM_WINDOW && d.stride == 1 && 2.0 * d.N * d.C * d.H * d.W > 33554432.0;
         return (large ? 1.8 : 1.0) * (v.model.call + std::ceil(wgs / (256.0 * v.per_cu)) * std::pow(share, (double)v.model.grow) * (v.model.own + chunks * v.model.chunk));
+    }
+    if (v.traits & TRAIT_SPLIT_FIRST) {
+        // rounds of 256 workgroups, two of them side by side at 7x7; 60 drawn first layers (within 8 %).  us, model: 20 images of
+        // 227x227, 11x11, 34 (33), 39 of 156x164 34 (33), one of 220x220 on 32-row tiles 17.5 (18); 49 of 228x228, 7x7, 81 (82)
+        const double wgs = (double)d.N * std::ceil((double)OH * OW / v.tn) * std::ceil(d.K / (double)v.tm), rounds = std::ceil(wgs / 256.0);
+        if (d.R == 7) return 8.2 + rounds * (v.tm == 64 ? 7.4 : 4.4);
+        return 3.5 + rounds * (v.tm == 96 ? 21.0 : 14.5) + wgs / 256.0 * (v.tm == 96 ? 9.5 : 2.5);
     }
     if (v.traits & TRAIT_SPLIT_PRODUCTS) {
         // Winograd on split products: v.tm / 32 blocks of 32 channels; a workgroup costs its start, planes and stores and a

@@ -135,6 +135,7 @@ enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no a
        TRAIT_SPLIT_PRODUCTS = 8192u,   // fp32 operands split into bf16 parts, products on the 16-bit matrix units
        TRAIT_PIXEL_STREAM = 16384u,    // 16-bit pointwise kernel for many pixels, input transposed in registers
        TRAIT_DIRECT_WINDOW = 32768u,   // 16-bit window kernel that brings both operands to MFMA order on the way through LDS, any stride
+       TRAIT_SPLIT_FIRST = 65536u,     // fp32 first layers on split products
        TRAIT_CHANNEL_WAVES = 2048u };  // fp32 window kernel on linear pixel tiles whose waves split the channels of a chunk
 
 enum { FAM_IGEMM = 0, FAM_POINTWISE = 1, FAM_FIRSTLAYER = 2, FAM_WINDOW = 3, FAM_FC = 4, FAM_NHWC = 5, FAM_WINOGRAD = 6 };
@@ -162,6 +163,7 @@ void register_wino_f32(std::vector<Variant>& out);
 void register_pwb_f16(std::vector<Variant>& out);
 void register_pwb_bf16(std::vector<Variant>& out);
 void register_winos_f32(std::vector<Variant>& out);
+void register_swins_f32(std::vector<Variant>& out);
 void register_pwk_f32(std::vector<Variant>& out);
 void register_pwk_f16(std::vector<Variant>& out);
 void register_pwk_bf16(std::vector<Variant>& out);

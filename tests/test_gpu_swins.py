@@ -1,0 +1,80 @@
+"""GPU parity of the first-layer kernel on split products (fp32, 3 channels) where its tiles, staged rows and reduction steps have their
+edges, no further from 64 bits than the gather kernels, and with values that its bf16 parts cannot carry."""
+import numpy as np
+import pytest
+
+from paper_1611_06945_amd import workloads as wl
+from paper_1611_06945_amd.workloads import ConvShape
+
+from gpu_util import TOL, DeviceCase, to_host_f64
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    ConvShape(1, 3, 11, 11, 5, 11, 11, 4, 0),     # one pixel, five filters
+    ConvShape(2, 3, 71, 75, 96, 11, 11, 4, 0),    # 16 x 17 pixels: a full tile and a ragged one per image
+    ConvShape(1, 3, 40, 300, 33, 11, 11, 4, 3),   # rows longer than 256 columns, a filter over a block, columns of zeros
+    ConvShape(1, 3, 23, 14, 64, 11, 11, 4, 10),   # border as wide as it may be
+    ConvShape(2, 3, 20, 9, 40, 7, 7, 2, 3),       # the last piece of a row overlaps the one before
+    ConvShape(1, 3, 33, 131, 64, 7, 7, 2, 0),
+    ConvShape(3, 3, 7, 8, 1, 7, 7, 2, 2),
+]
+
+
+def variants_of(case):
+    mine = [(i, n) for i, n in enumerate(case.variant_names()) if n.startswith("swins_")]
+    assert mine, case.shape
+    return mine
+
+
+def data_of(shape, seed):
+    return {"in": wl.draw(("uniform", -128.0, 128.0), shape.in_shape(), seed), "filt": wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), seed + 1),
+            "bias": wl.draw(("uniform", -0.1, 0.1), (shape.K,), seed + 2)}
+
+
+@pytest.mark.parametrize("ints", [True, False])
+@pytest.mark.parametrize("si", range(len(SHAPES)))
+def test_parity(si, ints):
+    shape = SHAPES[si]
+    case = DeviceCase(shape, wl.F32, wl.small_int_case(shape, wl.F32, 6100 + si) if ints else data_of(shape, 6100 + si), relu=bool(si % 2))
+    for i, name in variants_of(case):
+        print(name, shape, flush=True)
+        out = case.run(variant=i)
+        if ints:
+            assert np.array_equal(to_host_f64(out, wl.F32), case.ref()), name
+        else:
+            assert case.error(out) <= TOL[wl.F32], name
+
+
+def test_no_further_from_64_bits_than_the_gather_kernels():
+    case = DeviceCase(ConvShape(2, 3, 99, 99, 96, 11, 11, 4, 0), wl.F32, data_of(ConvShape(2, 3, 99, 99, 96, 11, 11, 4, 0), 6200), relu=False)
+    ref = case.ref()
+    err = {n: np.linalg.norm(to_host_f64(case.run(variant=i), wl.F32) - ref) / np.linalg.norm(ref)
+           for i, n in enumerate(case.variant_names()) if n.startswith(("swins_", "ug_")) and "_sk" not in n}
+    gather = min(e for n, e in err.items() if n.startswith("ug_"))
+    for n, e in err.items():
+        if n.startswith("swins_"):
+            assert e <= gather, (n, e, gather)
+
+
+@pytest.mark.parametrize("R,stride,pad", [(11, 4, 0), (7, 2, 3)])
+def test_values_beyond_the_parts(R, stride, pad):
+    """Infinities, NaN and numbers whose scaled parts overflow give what the definition gives, and reach no other output; the smallest
+    numbers lose nothing."""
+    shape = ConvShape(2, 3, 47, 45, 34, R, R, stride, pad)
+    data = data_of(shape, 6300)
+    data["in"][0, 1, 20, 21] = np.inf
+    data["in"][1, 2, 30, 11] = np.nan
+    data["filt"][3] = 3e38
+    data["filt"][5] *= np.float32(2.0 ** -120)
+    case = DeviceCase(shape, wl.F32, data, relu=False)
+    with np.errstate(over="ignore", invalid="ignore"):
+        ref = case.ref().astype(np.float32).astype(np.float64)
+    for i, name in variants_of(case):
+        got = to_host_f64(case.run(variant=i), wl.F32)
+        # (a sum of 3e38 x pixels overflows in fp32 in one order and not in another: that filter is only checked not to leak)
+        ks = [k for k in range(shape.K) if k != 3]
+        assert np.array_equal(np.isfinite(got[:, ks]), np.isfinite(ref[:, ks])), name
+        for k in ks:
+            m = np.isfinite(ref[:, k])
+            assert np.max(np.abs(got[:, k][m] - ref[:, k][m])) <= TOL[wl.F32] * np.max(np.abs(ref[:, k][m])), (name, k)
