@@ -53,6 +53,12 @@ __global__ __launch_bounds__(CFG::NT) void nhwc_kernel(ConvArgs a)
     elem_t* const As0 = (elem_t*)smem_raw;                    // [2][A_ELEMS]
     elem_t* const Bs0 = As0 + 2 * CFG::A_ELEMS;               // [2][B_ELEMS]
 
+    // the arguments together: left to their first uses, each line of them is waited for by itself
+    // (2 images of 28x28x64 -> 64, 1x1, 3.17 -> 2.95 us; 4 of 7x7x512 -> 512 5.30 -> 5.15)
+    asm volatile("" ::"s"(a.C), "s"(a.H), "s"(a.K), "s"(a.P), "s"(a.Q), "s"(a.R), "s"(a.S),
+                 "s"(a.W), "s"(a.bias), "s"(a.dC.mul), "s"(a.dOHW.mul), "s"(a.dOW.mul));
+    asm volatile("" ::"s"(a.dS.mul), "s"(a.filt), "s"(a.filt_bytes), "s"(a.in), "s"(a.in_bytes), "s"(a.out), "s"(a.out_bytes),
+                 "s"(a.out_nhwc), "s"(a.pad), "s"(a.relu), "s"(a.stride));
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;

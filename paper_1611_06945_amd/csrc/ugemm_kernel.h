@@ -48,6 +48,12 @@ __global__ __launch_bounds__(CFG::NT) void ugemm_kernel(ConvArgs a)
     __shared__ __attribute__((aligned(16))) elem_t As[2][CFG::A_ELEMS];
     __shared__ __attribute__((aligned(16))) elem_t Bs[2][CFG::B_ELEMS];
 
+    // the arguments together: left to their first uses, each line of them is waited for by itself
+    // (8 images of 28x28x128 -> 64, 1x1, 6.07 -> 5.83 us; nothing where the layer is the bound)
+    asm volatile("" ::"s"(a.C), "s"(a.H), "s"(a.HW), "s"(a.K), "s"(a.P), "s"(a.Q), "s"(a.QP),
+                 "s"(a.R), "s"(a.RS), "s"(a.S), "s"(a.SP4), "s"(a.W), "s"(a.dOHW.mul));
+    asm volatile("" ::"s"(a.dOW.mul), "s"(a.dRS.mul), "s"(a.dRSP.mul), "s"(a.dRSP4.mul), "s"(a.dS.mul), "s"(a.dSP.mul), "s"(a.dSP4.mul),
+                 "s"(a.filt), "s"(a.filt_bytes), "s"(a.in), "s"(a.in_bytes), "s"(a.pad), "s"(a.stride));
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
