@@ -93,12 +93,6 @@ __global__ __launch_bounds__(CFG::NT) void pwin32_kernel(ConvArgs a)
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     float* const buf0 = (float*)smem_raw;  // [2][ filter slab TM*LDA | input slab CB*SP ]
 
-    // the arguments together: left to their first uses, each line of them is waited for by itself
-    // (5 images of 28x28x64 -> 96, 3x3, 10.2 -> 10.0 us)
-    asm volatile("" ::"s"(a.C), "s"(a.H), "s"(a.HW), "s"(a.K), "s"(a.N), "s"(a.OHW), "s"(a.P),
-                 "s"(a.W), "s"(a.bias), "s"(a.dOHW.mul), "s"(a.dOW.mul));
-    asm volatile("" ::"s"(a.dX.mul), "s"(a.dY.mul), "s"(a.dZ.mul), "s"(a.filt), "s"(a.filt_bytes), "s"(a.in), "s"(a.in_bytes),
-                 "s"(a.out), "s"(a.out_bytes), "s"(a.pad), "s"(a.relu));
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kw = wave % KW, wn = wave / KW;
