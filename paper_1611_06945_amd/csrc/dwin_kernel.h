@@ -9,6 +9,7 @@
 //     neighbouring positions for every tap, whatever the stride;
 //   * [N][C][H][W]: a thread loads four neighbouring pixels of eight channels (8 bytes each), puts the channels of a pixel
 //     together with byte permutes and writes 16 bytes per pixel; the slab's borders are cleared once;
+//     (a row may start on an odd element: such loads are slower, but one of them replaces four);
 //     [N][H][W][C]: 16-byte copies;
 //   * [K][C][R][S]: the rows of a tile go to LDS as they are (whole 16-byte runs); a lane reads its 8 channels x R*S taps,
 //     consecutive in memory, into registers and picks each tap's operand with byte permutes.  Rows that start on an odd

@@ -24,7 +24,7 @@
 // exposed, with one workgroup per CU.  Tiles of 64 were tried (twice the registers, no room for the two-stage mix: 238 us
 // where 96 x 32 took 218), and two workgroups of 32 x 32 per CU (vector work per product doubles: 350).
 // Measured (us per call back to back, filter transform included, kernel before -> this one; boxes differ by up to 10 %): 20
-// images of 13x13x256 -> 384 46 -> 36, 64 of 56x56x64 -> 192 340 -> 198 .. 222.  With other inputs from call to call 32.8 and 217;
+// images of 13x13x256 -> 384 46 -> 35.5, 64 of 56x56x64 -> 192 340 -> 198 .. 222.  With other inputs from call to call 32.8 and 217;
 // traced, in which a launch takes longer, 31.3 + 8.8 for the filter transform and 237 + 6.2.
 // Range: the parts of x reach 24 bits below x, which for |x| < 2^-102 is below bf16's normal numbers.  Both operands are
 // therefore scaled by 2^24 ahead of the splits: every part of every fp32 number, subnormal ones included, is then a normal
