@@ -135,8 +135,8 @@ int conv_fwd(const conv_desc* desc, const void* in, const void* filt, const floa
  * reduced in a fixed order, or, for fp32 3x3 stride-1 layers, a Winograd
  * F(2x2,3x3) variant (the algorithm the paper names as its main open topic,
  * Section 4 "Experimental Results"), which first writes the transformed filters
- * there.  One of those (winos_*) multiplies on the 16-bit matrix units, each fp32 operand split into three parts that
- * together hold all of it; results that are infinite, NaN or beyond about 2^79 it sums once more the direct way, so that a
+ * there.  One of those (winos_*), and one for fp32 first layers (swins_*), multiply on the 16-bit matrix units, each fp32 operand split into three parts that
+ * together hold all of it; results that are infinite, NaN or beyond about 2^79 they sum once more the direct way, so that a
  * call with such data can take several times as long (up to about 20 times where every result is beyond that size).
  * Results are bit-reproducible either way.  If `workspace_bytes` is too small for the selected variant
  * the best variant that fits is used instead; CONV_EWORKSPACE only if a forced
@@ -152,7 +152,7 @@ int conv_fwd_ws(const conv_desc* desc, const void* in, const void* filt, const f
  * nothing.  The variant is selected as conv_fwd_ws selects it with unlimited workspace (forced > autotuned/cached >
  * cost model); when that variant needs more than CONV_STATIC_SCRATCH_BYTES the call is rejected with CONV_EWORKSPACE
  * (conv_strerror names the variant and both sizes) and nothing is enqueued -- use conv_fwd or conv_fwd_ws then.  (The
- * kernels that keep a copy of the input or split filters in scratch, bwin_*, pwin_*_prep and winos_*, give way to the pick
+ * kernels that keep a copy of the input or split filters in scratch, bwin_*, pwin_*_prep, winos_* and swins_*, give way to the pick
  * that fits.)
  * Results are bit-identical to conv_fwd_ws running the same variant.  Nothing in the array has to start at zero
  * (every partial sum and every transformed filter is written before it is read), and its contents are undefined

@@ -656,7 +656,7 @@ int conv_fwd_static(const conv_desc* desc, const void* in, const void* filt, con
     }
     if (idx < 0) return idx;
     size_t need = ws_bytes_of(st.variants[idx], *desc, OH, OW);
-    if (need > (size_t)CONV_STATIC_SCRATCH_BYTES && (st.variants[idx].traits & (TRAIT_CONVERTS_FIRST | TRAIT_SPLIT_PRODUCTS))) {
+    if (need > (size_t)CONV_STATIC_SCRATCH_BYTES && (st.variants[idx].traits & (TRAIT_CONVERTS_FIRST | TRAIT_SPLIT_PRODUCTS | TRAIT_SPLIT_FIRST))) {
         // kernels that trade scratch for speed (a copy of the input, split filters): where the array is too small for them, the pick that fits it (a forced
         // variant stays, and is refused below)
         std::lock_guard<std::mutex> g(st.mu);
