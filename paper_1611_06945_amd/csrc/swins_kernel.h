@@ -104,7 +104,7 @@ __global__ __launch_bounds__(CFG::NT, 1) void swins_kernel(ConvArgs a, SwinsGeom
     const __amdgpu_buffer_rsrc_t ru = make_rsrc(a.ws, (uint32_t)KSTEPS * (uint32_t)blocks * 3072u);
     const uint32_t u_step = (uint32_t)blocks * 3072u, u_base = (uint32_t)(m0 >> 5) * 3072u;
     uint4 af[2][TMB][3];
-    auto load_a = [&](int set, uint32_t step) {  // (steps past the last one are out of range and fetch nothing)
+    auto load_a = [&](int set, uint32_t step) {  // (blocks past the last one read filters of the step after, or nothing: sums nobody stores)
 #pragma unroll
         for (int mb = 0; mb < TMB; ++mb)
 #pragma unroll
@@ -429,6 +429,8 @@ bool swins_valid(const Variant&, const conv_desc& d, int OH, int OW)
     if (swins_lds(g) > 160 * 1024) return false;
     const long long lim = 1LL << 31;
     if ((long long)d.N * d.C * d.H * d.W * 4 >= lim || (long long)d.N * d.K * OH * OW * 4 >= lim) return false;
+    // split filters and their offsets, a tile's spare blocks behind the last one among them
+    if ((long long)CFG::KSTEPS * ((d.K + 31) / 32 + CFG::TMB) * 3072 >= lim) return false;
     return (long long)d.N * g.tpi < lim && (d.K + CFG::TM - 1) / CFG::TM < 65536;
 }
 
