@@ -428,7 +428,8 @@ bool swins_valid(const Variant&, const conv_desc& d, int OH, int OW)
     const SwinsGeom g = swins_geom(CFG::TN, CFG::R, CFG::ST, d.W, d.pad, OH, OW);
     if (swins_lds(g) > 160 * 1024) return false;
     const long long lim = 1LL << 31;
-    if ((long long)d.N * d.C * d.H * d.W * 4 >= lim || (long long)d.N * d.K * OH * OW * 4 >= lim) return false;
+    // (a channel that does not exist is stored at 2 GiB plus the offset of its row, which must not pass 4 GiB)
+    if ((long long)d.N * d.C * d.H * d.W * 4 >= lim || ((long long)d.N * d.K + CFG::TM) * OH * OW * 4 >= lim) return false;
     // split filters and their offsets, a tile's spare blocks behind the last one among them
     if ((long long)CFG::KSTEPS * ((d.K + 31) / 32 + CFG::TMB) * 3072 >= lim) return false;
     return (long long)d.N * g.tpi < lim && (d.K + CFG::TM - 1) / CFG::TM < 65536;

@@ -30,3 +30,18 @@ def test_split_filters_stay_within_32_bit_offsets(H, R, stride, steps, tm):
     name = "M%dN256" % tm
     assert split_variants(ConvShape(1, 3, H, H, blocks * 32, R, R, stride, 0))[name] == blocks * steps * 3072
     assert name not in split_variants(ConvShape(1, 3, H, H, blocks * 32 + 1, R, R, stride, 0))
+
+
+# a store of a channel that does not exist has to miss the output: 2 GiB plus the offset of its row must not pass 4 GiB
+@pytest.mark.parametrize("N,H,K,R,stride,pad,tm", [
+    (1828, 227, 97, 11, 4, 0, 96),  # one channel of the last tile exists, 95 do not
+    (613, 227, 289, 11, 4, 0, 32),
+    (657, 224, 65, 7, 2, 3, 64),
+    (1295, 224, 33, 7, 2, 3, 32),
+])
+def test_spare_channels_of_the_last_tile_stay_out_of_range(N, H, K, R, stride, pad, tm):
+    inside, beyond = ConvShape(N, 3, H, H, K, R, R, stride, pad), ConvShape(N + 1, 3, H, H, K, R, R, stride, pad)
+    plane, lim = 4 * inside.OH * inside.OW, 1 << 31
+    assert (N * K + tm) * plane < lim <= ((N + 1) * K + tm) * plane and (N + 1) * K * plane < lim
+    assert "M%dN256" % tm in split_variants(inside)
+    assert "M%dN256" % tm not in split_variants(beyond)

@@ -3,10 +3,11 @@ edges, no further from 64 bits than the gather kernels, and with values that its
 import numpy as np
 import pytest
 
+from paper_1611_06945_amd import binding as B
 from paper_1611_06945_amd import workloads as wl
 from paper_1611_06945_amd.workloads import ConvShape
 
-from gpu_util import TOL, DeviceCase, to_host_f64
+from gpu_util import TOL, DeviceCase, to_host_f64, torch_mod
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +79,38 @@ def test_values_beyond_the_parts(R, stride, pad):
         for k in ks:
             m = np.isfinite(ref[:, k])
             assert np.max(np.abs(got[:, k][m] - ref[:, k][m])) <= TOL[wl.F32] * np.max(np.abs(ref[:, k][m])), (name, k)
+
+
+def test_output_close_to_the_size_limit():
+    """1828 images, the most that the 96-channel tile accepts: 95 of the last tile's channels do not exist, and their stores aim past
+    2 GiB.  Small integers: bit for bit what a gather kernel gives, and nothing written behind the output."""
+    torch = torch_mod()
+    shape = ConvShape(1828, 3, 227, 227, 97, 11, 11, 4, 0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6400)
+
+    def ints(dims, r):
+        return torch.randint(-r, r + 1, dims, generator=g, device="cuda", dtype=torch.int32).float()
+
+    x, f, b = ints(shape.in_shape(), 3), ints(shape.filt_shape(), 2), ints((shape.K,), 4)
+    desc = B.desc_of(shape, wl.F32, relu=True)
+    names = [B.conv_variant_name(desc, i) for i in range(B.conv_variant_count(desc))]
+    gather = [n for n in names if not n.startswith("swins_") and "_sk" not in n][-1]
+    mine = [n for n in names if n.startswith("swins_")]
+    assert any(n.endswith("_M96N256") for n in mine)
+    n_out, spare = shape.N * shape.K * shape.OH * shape.OW, 1 << 20
+    want = None
+    for name in [gather] + mine:
+        print(name, shape, flush=True)
+        buf = torch.full((n_out + spare,), float("nan"), device="cuda")
+        i = names.index(name)
+        ws = torch.empty(max(256, B.conv_variant_workspace(desc, i)), dtype=torch.uint8, device="cuda")
+        B.conv_force_variant(desc, i)
+        try:
+            B.conv_fwd_ws(desc, x, f, b, buf[:n_out], ws, ws.numel())
+            torch.cuda.synchronize()
+        finally:
+            B.conv_force_variant(desc, -1)
+        assert bool(torch.isnan(buf[n_out:]).all()), name
+        want = buf[:n_out] if want is None else want
+        assert torch.equal(buf[:n_out], want), name
