@@ -255,14 +255,13 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         }
     }
     if (v.traits & TRAIT_DIRECT_WINDOW) {
-        // a fit per tile shape to 18000 measured calls on 2200 drawn layers (rms 4 to 15 %)
+        // A fit per tile shape to the measured calls of 700 drawn layers (rms 3 to 11 %, 3 to 9 % on 360 others).  The last round is
+        // as long as its fullest CU makes it: rated by the average CU, the tiles of which several share one missed by 9 to 15 %.  us,
+        // pick of that form and of this one: 63 images of 32x35x64 -> 56 20.4, 16.6; 40 of 64x56x128 -> 32, 37 MB of input, 31.4, 24.8
         const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn), chunks = std::ceil(Q / v.tk);
-        const double share = std::min((double)v.per_cu, std::max(1.0, wgs / 256.0));
-        // (stride-1 layers whose input the L2s together do not hold are rated 1.8-fold: the kernels behind a conversion launch are
-        // within 30 % of this one there, 40 images of 64x56x128 -> 32 31 against 26 us, 39 of 28x26x944 -> 10 56 against 41, and
-        // the tests of the library's own scratch expect them of the selection; autotuned, such layers take this kernel)
-        const bool large = v.family == FAM_WINDOW && d.stride == 1 && 2.0 * d.N * d.C * d.H * d.W > 33554432.0;
-        return (large ? 1.8 : 1.0) * (v.model.call + std::ceil(wgs / (256.0 * v.per_cu)) * std::pow(share, (double)v.model.grow) * (v.model.own + chunks * v.model.chunk));
+        const double slots = 256.0 * v.per_cu, full = std::floor(wgs / slots), rest = std::ceil((wgs - full * slots) / 256.0);
+        const double rounds = full * std::pow((double)v.per_cu, (double)v.model.grow) + (rest > 0.0 ? std::pow(rest, (double)v.model.grow) : 0.0);
+        return v.model.call + rounds * (v.model.own + chunks * v.model.chunk);
     }
     if (v.traits & TRAIT_SPLIT_FIRST) {
         // rounds of 256 workgroups, two of them side by side at 7x7; 60 drawn first layers (within 8 %).  us, model: 20 images of
@@ -361,9 +360,13 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double t_mfma = (v.tm / 32.0) * (v.tn / 32.0) * steps * 8.0 / 2100.0;
         const double own = 0.67 + 4.94 * v.tm * v.tn / 32768.0 + 0.035 * steps;
         const double slots = 256.0 * v.per_cu, full = std::floor(tiles / slots), part = tiles / slots - full;
-        const double alone = own + t_mfma / 0.93, round = v.per_cu == 2 ? own + 2.0 * t_mfma / 0.67 : alone;
+        // (5x5 behind the conversion launch, 220 calls: a tap's latency lies under the other workgroup's MFMAs, and the call takes 0.87 of
+        // the sum; 97 images of 30x30x600 -> 16 131 us, rated 164 without, 155 on the one-launch kernel)
+        const bool prep5 = d.R == 5 && (v.traits & TRAIT_CONVERTS_FIRST);
+        const double alone = own + t_mfma / 0.93, round = v.per_cu == 2 ? own - (prep5 ? 0.035 * steps : 0.0) + 2.0 * t_mfma / 0.67 : alone;
         double t = 0.87 + full * round;
         if (part > 0.0) t += part > 0.5 ? round : alone;
+        if (prep5) t *= 0.87;
         // (the conversion launch is rated 1 us dearer than it is, here and below: these kernels ask for workspace, and the models
         // of the others err by as much on layers of 10 us)
         if (v.traits & TRAIT_CONVERTS_FIRST) {

@@ -98,7 +98,7 @@ typedef bool (*ValidFn)(const Variant& v, const conv_desc& d, int OH, int OW);
 typedef size_t (*WorkspaceFn)(const Variant& v, const conv_desc& d, int OH, int OW);
 
 // Time of a call for kernels measured tile by tile: `call` us, then per round of workgroups `own` and, for every chunk of
-// channels, `chunk` us, both growing with the workgroups that share a CU to the power `grow`.
+// channels, `chunk` us, both growing with the workgroups that share the fullest CU to the power `grow`.
 struct TileModel {
     float call, own, chunk, grow;
 };

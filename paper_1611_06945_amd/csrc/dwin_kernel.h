@@ -669,34 +669,34 @@ void dwin_register_all(std::vector<Variant>& out)
 {
     //          DT  R  MB WM WN WK TMB NBW CG SLOTS DB     call  own   chunk  grow
     dwin_planar<DT, 3, 16, 1, 1, 8, 1, 2, 32, 128, false>(out, {1.60, 3.09, 2.628, 0.80});  // M16  N32
-    dwin_planar<DT, 3, 16, 1, 1, 4, 1, 2, 16, 128, false>(out, {3.41, 1.28, 1.668, 0.55});  // M16  N32
+    dwin_planar<DT, 3, 16, 1, 1, 4, 1, 2, 16, 128, false>(out, {2.63, 1.68, 1.661, 0.45});  // M16  N32
     dwin_planar<DT, 3, 16, 1, 1, 4, 1, 2, 16, 256, false>(out, {1.86, 3.12, 2.489, 0.80});  // M16  N32
-    dwin_planar<DT, 3, 16, 1, 4, 1, 1, 2, 4, 512, false>(out, {2.43, 1.44, 1.382, 0.57});  // M16  N128
+    dwin_planar<DT, 3, 16, 1, 4, 1, 1, 2, 4, 512, false>(out, {2.23, 1.36, 1.316, 0.67});  // M16  N128
     dwin_planar<DT, 3, 32, 1, 1, 4, 1, 1, 8, 128, true>(out, {1.73, 2.48, 1.125, 0.30});  // M32  N32
-    dwin_planar<DT, 3, 32, 1, 1, 4, 1, 1, 8, 256, false>(out, {2.70, 1.90, 1.621, 0.36});  // M32  N32
-    dwin_planar<DT, 3, 32, 1, 2, 2, 1, 1, 4, 256, false>(out, {2.77, 1.27, 1.034, 0.46});  // M32  N64
-    dwin_planar<DT, 3, 32, 1, 2, 2, 1, 1, 4, 256, true>(out, {2.30, 1.66, 0.951, 0.36});  // M32  N64
-    dwin_planar<DT, 3, 32, 1, 2, 2, 1, 1, 4, 768, false>(out, {2.55, 2.24, 1.730, 0.32});  // M32  N64
-    dwin_planar<DT, 3, 32, 1, 4, 1, 1, 1, 2, 512, true>(out, {2.66, 1.34, 0.829, 0.47});  // M32  N128
-    dwin_planar<DT, 3, 32, 2, 2, 1, 1, 2, 2, 512, true>(out, {2.69, 2.24, 1.024, 0.48});  // M64  N128
+    dwin_planar<DT, 3, 32, 1, 1, 4, 1, 1, 8, 256, false>(out, {2.29, 1.95, 1.602, 0.38});  // M32  N32
+    dwin_planar<DT, 3, 32, 1, 2, 2, 1, 1, 4, 256, false>(out, {2.51, 1.23, 0.998, 0.48});  // M32  N64
+    dwin_planar<DT, 3, 32, 1, 2, 2, 1, 1, 4, 256, true>(out, {2.26, 1.55, 0.905, 0.40});  // M32  N64
+    dwin_planar<DT, 3, 32, 1, 2, 2, 1, 1, 4, 768, false>(out, {2.30, 2.22, 1.703, 0.36});  // M32  N64
+    dwin_planar<DT, 3, 32, 1, 4, 1, 1, 1, 2, 512, true>(out, {2.58, 1.30, 0.789, 0.55});  // M32  N128
+    dwin_planar<DT, 3, 32, 2, 2, 1, 1, 2, 2, 512, true>(out, {2.23, 2.33, 1.021, 0.49});  // M64  N128
     dwin_planar<DT, 3, 32, 2, 2, 1, 1, 2, 2, 1024, true>(out, {1.34, 4.13, 1.286, 0.80});  // M64  N128
-    dwin_planar<DT, 3, 32, 2, 2, 1, 1, 2, 2, 1024, false>(out, {3.28, 1.75, 1.540, 0.64});  // M64  N128
+    dwin_planar<DT, 3, 32, 2, 2, 1, 1, 2, 2, 1024, false>(out, {2.38, 2.37, 1.527, 0.60});  // M64  N128
     dwin_planar<DT, 3, 32, 2, 2, 2, 1, 2, 4, 512, true>(out, {1.52, 3.62, 1.455, 0.80});  // M64  N128
     dwin_planar<DT, 5, 16, 1, 1, 4, 1, 2, 16, 128, false>(out, {1.05, 4.53, 3.479, 0.30});  // M16  N32
-    dwin_planar<DT, 5, 32, 1, 2, 2, 1, 1, 4, 256, false>(out, {3.29, 1.23, 2.835, 0.44});  // M32  N64
-    dwin_planar<DT, 5, 32, 1, 4, 1, 1, 1, 2, 512, false>(out, {2.62, 1.48, 1.693, 0.59});  // M32  N128
+    dwin_planar<DT, 5, 32, 1, 2, 2, 1, 1, 4, 256, false>(out, {0.50, 2.96, 2.807, 0.39});  // M32  N64
+    dwin_planar<DT, 5, 32, 1, 4, 1, 1, 1, 2, 512, false>(out, {1.99, 2.06, 1.573, 0.68});  // M32  N128
     dwin_planar<DT, 5, 32, 1, 4, 1, 1, 1, 2, 512, true>(out, {1.43, 2.67, 1.447, 0.80});  // M32  N128
-    dwin_planar<DT, 5, 32, 1, 4, 1, 1, 2, 2, 768, false>(out, {3.65, 0.86, 4.507, 0.91});  // M32  N256
-    dwin_inner<DT, 3, 16, 1, 4, 1, 1, 2, 4, 512, true, 1>(out, {2.50, 1.14, 0.703, 0.60});  // M16  N128
+    dwin_planar<DT, 5, 32, 1, 4, 1, 1, 2, 2, 768, false>(out, {1.19, 2.91, 4.510, 0.73});  // M32  N256
+    dwin_inner<DT, 3, 16, 1, 4, 1, 1, 2, 4, 512, true, 1>(out, {2.78, 0.99, 0.650, 0.74});  // M16  N128
     dwin_inner<DT, 3, 32, 1, 1, 4, 1, 1, 8, 128, true>(out, {1.92, 1.78, 0.575, 0.30});  // M32  N32
     dwin_inner<DT, 3, 32, 1, 1, 4, 1, 1, 8, 256, true, 1>(out, {1.96, 1.87, 0.762, 0.30});  // M32  N32
-    dwin_inner<DT, 3, 32, 1, 2, 2, 1, 1, 4, 256, true, 1>(out, {3.29, 0.34, 0.543, 0.85});  // M32  N64
-    dwin_inner<DT, 3, 32, 1, 2, 2, 1, 2, 4, 512, true, 1>(out, {2.92, 1.29, 0.817, 0.67});  // M32  N128
+    dwin_inner<DT, 3, 32, 1, 2, 2, 1, 1, 4, 256, true, 1>(out, {3.29, 0.55, 0.473, 0.85});  // M32  N64
+    dwin_inner<DT, 3, 32, 1, 2, 2, 1, 2, 4, 512, true, 1>(out, {2.47, 1.48, 0.809, 0.67});  // M32  N128
     dwin_inner<DT, 3, 32, 2, 1, 2, 1, 2, 4, 512, true, 1>(out, {1.75, 2.46, 0.889, 0.30});  // M64  N64
     dwin_inner<DT, 3, 32, 2, 2, 2, 1, 2, 4, 512, true, 1>(out, {1.28, 2.63, 1.125, 0.80});  // M64  N128
     dwin_inner<DT, 3, 32, 2, 2, 2, 2, 2, 4, 832, true, 1>(out, {0.83, 4.13, 1.730, 0.30});  // M128 N128
     dwin_inner<DT, 5, 16, 1, 1, 4, 1, 2, 16, 128, false>(out, {1.79, 1.63, 3.108, 0.80});  // M16  N32
-    dwin_inner<DT, 5, 32, 1, 2, 2, 1, 1, 4, 256, true, 1>(out, {3.30, 0.39, 1.201, 0.90});  // M32  N64
+    dwin_inner<DT, 5, 32, 1, 2, 2, 1, 1, 4, 256, true, 1>(out, {2.83, 0.63, 1.147, 0.90});  // M32  N64
     dwin_inner<DT, 5, 32, 2, 2, 2, 1, 2, 4, 512, true, 1>(out, {1.28, 2.76, 2.720, 0.30});  // M64  N128
 }
 

@@ -1,5 +1,7 @@
 """The library's own selection (no measurement at hand) against measured times: layers for which the kernel named first took
 clearly longer than one the selection had before or has now.  CPU only: the cost model is host code."""
+import dataclasses
+
 import pytest
 
 from paper_1611_06945_amd import binding as B
@@ -77,3 +79,40 @@ def test_window_layers_of_few_pixels_keep_the_packed_filter_kernel(shape, dtype,
 def test_window_layers_of_many_pixels_go_to_the_many_pixel_kernel(fmt, prefix):
     name = picks(ConvShape(64, 64, 56, 56, 192, 3, 3, 1, 1), wl.BF16, fmt)[0]  # us: 51 (47), of the packed-filter kernel 105 (84)
     assert name.startswith(prefix), name
+
+
+# layers on either side of 32 MiB of input, which nothing in these kernels depends on: us of the one-launch kernel with one image more, of
+# the window kernel that was taken there while the other was held back behind that line
+@pytest.mark.parametrize("shape", [
+    ConvShape(40, 256, 40, 40, 64, 3, 3, 1, 1),   # 44, 64
+    ConvShape(83, 256, 28, 28, 256, 3, 3, 1, 1),  # 124, 214
+])
+def test_picks_without_a_workspace_do_not_flip_with_one_image_more(shape):
+    more = dataclasses.replace(shape, N=shape.N + 1)
+    names = [picks(s, wl.F16)[1] for s in (shape, more)]
+    assert names[0] == names[1] and names[0].startswith("dwin_"), names
+
+
+# us of the one-launch kernel, of the kernels behind a conversion launch
+@pytest.mark.parametrize("shape", [
+    ConvShape(40, 128, 64, 56, 32, 3, 3, 1, 1),  # 25, 31
+    ConvShape(39, 944, 28, 26, 10, 3, 3, 1, 1),  # 44, 57
+])
+def test_layers_with_large_inputs_go_to_the_one_launch_kernel_where_it_is_faster(shape):
+    assert all(name.startswith("dwin_") for name in picks(shape, wl.BF16)), picks(shape, wl.BF16)
+
+
+# 5x5 layers of many pixels: us of the kernel behind a conversion launch, of the one-launch kernel
+@pytest.mark.parametrize("shape,dtype", [
+    (ConvShape(97, 600, 30, 30, 16, 5, 5, 1, 2), wl.BF16),   # 131, 155
+    (ConvShape(83, 160, 45, 43, 16, 5, 5, 1, 2), wl.F16),    # 62, 73
+    (ConvShape(156, 192, 32, 30, 16, 5, 5, 1, 2), wl.F16),   # 70, 82
+])
+def test_5x5_layers_of_many_pixels_keep_the_many_pixel_kernel(shape, dtype):
+    assert picks(shape, dtype)[0].startswith("bwin_"), picks(shape, dtype)
+
+
+def test_a_last_round_is_rated_by_its_fullest_cu():
+    # 560 workgroups of 64 x 128 outputs, three to a CU on 48 of 256 CUs: 20.4 us; tiles of 32 x 128 16.6
+    name = picks(ConvShape(63, 64, 32, 35, 56, 3, 3, 1, 1), wl.F16)[0]
+    assert name.startswith("dwin_f16_3x3_M32N128"), name
