@@ -360,13 +360,14 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double t_mfma = (v.tm / 32.0) * (v.tn / 32.0) * steps * 8.0 / 2100.0;
         const double own = 0.67 + 4.94 * v.tm * v.tn / 32768.0 + 0.035 * steps;
         const double slots = 256.0 * v.per_cu, full = std::floor(tiles / slots), part = tiles / slots - full;
-        // (5x5 behind the conversion launch, 220 calls: a tap's latency lies under the other workgroup's MFMAs, and the call takes 0.87 of
-        // the sum; 97 images of 30x30x600 -> 16 131 us, rated 164 without, 155 on the one-launch kernel)
+        // (5x5 behind the conversion launch, 220 calls: a tap's latency lies under the other workgroup's MFMAs, and the call takes 0.82 of
+        // the sum; 97 images of 30x30x600 -> 16 131 us, rated 169 without, 155 on the one-launch kernel.  Filter rows of channels that
+        // do not fill a group of 16 are packed 5 us slower: 6 of 19x22x61 -> 448 20, 15 on the one-launch kernel)
         const bool prep5 = d.R == 5 && (v.traits & TRAIT_CONVERTS_FIRST);
         const double alone = own + t_mfma / 0.93, round = v.per_cu == 2 ? own - (prep5 ? 0.035 * steps : 0.0) + 2.0 * t_mfma / 0.67 : alone;
         double t = 0.87 + full * round;
         if (part > 0.0) t += part > 0.5 ? round : alone;
-        if (prep5) t *= 0.87;
+        if (prep5) t = 0.82 * t + (d.C % 16 ? 5.0 : 0.0);
         // (the conversion launch is rated 1 us dearer than it is, here and below: these kernels ask for workspace, and the models
         // of the others err by as much on layers of 10 us)
         if (v.traits & TRAIT_CONVERTS_FIRST) {

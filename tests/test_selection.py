@@ -112,6 +112,15 @@ def test_5x5_layers_of_many_pixels_keep_the_many_pixel_kernel(shape, dtype):
     assert picks(shape, dtype)[0].startswith("bwin_"), picks(shape, dtype)
 
 
+# ... unless their filters' channels fill no groups of 16
+@pytest.mark.parametrize("shape", [
+    ConvShape(6, 61, 19, 22, 448, 5, 5, 1, 2),   # 20, 15
+    ConvShape(29, 68, 17, 17, 112, 5, 5, 1, 2),  # 21, 16
+])
+def test_5x5_layers_of_ragged_channels_go_to_the_one_launch_kernel(shape):
+    assert picks(shape, wl.F16)[0].startswith("dwin_"), picks(shape, wl.F16)
+
+
 def test_a_last_round_is_rated_by_its_fullest_cu():
     # 560 workgroups of 64 x 128 outputs, three to a CU on 48 of 256 CUs: 20.4 us; tiles of 32 x 128 16.6
     name = picks(ConvShape(63, 64, 32, 35, 56, 3, 3, 1, 1), wl.F16)[0]
