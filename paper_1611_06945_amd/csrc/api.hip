@@ -419,6 +419,11 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
     if (v.family != FAM_NHWC && d.dtype != CONV_F32 && d.R * d.S == 1 && d.C % 8 == 0 && d.K <= 32)
         t = std::max(t, 2.0 + 3.6 / 4.7e6 * ((double)d.N * d.C * d.H * d.W + d.K * P) + 0.1 * t);
     if (v.split > 1) t += 2.0 + (double)v.split * d.K * P * 4.0 / 2.0e6;
+    // (channel-innermost windows gathered piece by piece take half of that, 0.6 on tiles of 32 or 96 channels, two thirds where the reduction is
+    // split; 9000 measured calls of 350 drawn layers.  With these factors 2 of 350 picks are more than 5 % slower than the best that the
+    // selection had before the one-launch kernel, 10 without; us, gathered, on the one-launch kernel that was taken: 29 images of
+    // 20x23x480 -> 48 at stride 2 14.1, 19.6; one of 56x59x104 -> 352 at stride 2 8.4, 11.6)
+    if (v.family == FAM_NHWC && !window && d.R * d.S > 1) t *= v.split > 1 ? 0.9 : v.tm % 64 ? 0.8 : 0.65;
     return t * (1.0 - 0.002 * v.specificity);  // ties go to the kernel written for the narrower class of shapes
 }
 

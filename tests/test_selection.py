@@ -125,3 +125,16 @@ def test_a_last_round_is_rated_by_its_fullest_cu():
     # 560 workgroups of 64 x 128 outputs, three to a CU on 48 of 256 CUs: 20.4 us; tiles of 32 x 128 16.6
     name = picks(ConvShape(63, 64, 32, 35, 56, 3, 3, 1, 1), wl.F16)[0]
     assert name.startswith("dwin_f16_3x3_M32N128"), name
+
+
+# channel-innermost layers, with (-1) or without (-2) a workspace: us of the gathering kernel, of the one-launch window kernel (or of the
+# tile of it) that was taken
+@pytest.mark.parametrize("shape,dtype,which,slow", [
+    (ConvShape(29, 480, 20, 23, 48, 3, 3, 2, 1), wl.BF16, -1, "nhwc_dwin_"),                # 14.1, 19.6
+    (ConvShape(3, 256, 16, 19, 248, 3, 3, 2, 1), wl.BF16, -1, "nhwc_dwin_bf16_3x3_M64N64"),  # 9.1, 11.2
+    (ConvShape(56, 16, 37, 37, 48, 3, 3, 1, 1), wl.F16, -2, "nhwc_dwin_f16_3x3_M32N"),      # 10.1, 11.7
+    (ConvShape(1, 104, 56, 59, 352, 3, 3, 2, 1), wl.BF16, -2, "nhwc_dwin_bf16_3x3_M128"),   # 8.4, 11.6
+])
+def test_channel_innermost_layers_keep_the_faster_kernel(shape, dtype, which, slow):
+    d = B.desc_of(shape, dtype, relu=True, in_nhwc=True, out_nhwc=True, filt_krsc=True)
+    assert not B.conv_variant_name(d, which).startswith(slow), B.conv_variant_name(d, which)
