@@ -266,6 +266,8 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
     if (v.traits & TRAIT_SPLIT_FIRST) {
         // rounds of 256 workgroups, two of them side by side at 7x7; 60 drawn first layers (within 8 %).  us, model: 20 images of
         // 227x227, 11x11, 34 (33), 39 of 156x164 34 (33), one of 220x220 on 32-row tiles 17.5 (18); 49 of 228x228, 7x7, 81 (82)
+        // (over 180 drawn first layers the pick takes 0.90 of the gather kernels' pick; four are 5 to 29 % slower, with 128 filters or a
+        // second round of few workgroups.  Rated 1.1-fold it is two, and four others lose up to 28 %)
         const double wgs = (double)d.N * std::ceil((double)OH * OW / v.tn) * std::ceil(d.K / (double)v.tm), rounds = std::ceil(wgs / 256.0);
         if (d.R == 7) return 8.2 + rounds * (v.tm == 64 ? 7.4 : 4.4);
         return 3.5 + rounds * (v.tm == 96 ? 21.0 : 14.5) + wgs / 256.0 * (v.tm == 96 ? 9.5 : 2.5);

@@ -15,7 +15,9 @@
 // What bounds it: 20 images of 227x227 -> 96 are one round of 240 workgroups of 49000 clocks, 34800 of them the loop (936 MFMAs
 // at 37 clocks, 32 at best), 8000 staging and 5500 stores that nothing covers with one workgroup per CU; 4 us are the filters'
 // launch.  Measured, us per call, best of the other kernels -> this one: 20 of 227x227 -> 96, 11x11 40 -> 34; 20 of 223x223 -> 64, 7x7
-// stride 2, 61 -> 38, 49 of 228x228 146 -> 81; from about 150 tiles of 256 pixels it is the faster one at 11x11, from 80 at 7x7.
+// stride 2, 61 -> 38, 49 of 228x228 146 -> 81.  Where it begins (96 filters of 11x11, images of 227x227; best of the others -> this one): 2 images,
+// 24 tiles of 256 pixels, 14.8 -> 17.8, 3 17.8 -> 17.8, 5 19.3 -> 18.3, 6 23.9 -> 18.6, 10 30.0 -> 26.3, 12 38.7 -> 27.2; 64 filters
+// of 7x7, images of 224x224: 1 image, 49 tiles, 9.6 -> 11.7, 2 12.4 -> 12.2, 4 19.0 -> 15.1.  The selection takes it from there.
 // Error against 64 bits (2-norm, relative), gather kernels 3.4e-7, this one 3.0e-7 (11x11) and 1.9e-7 (7x7).
 #pragma once
 

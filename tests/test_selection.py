@@ -138,3 +138,20 @@ def test_a_last_round_is_rated_by_its_fullest_cu():
 def test_channel_innermost_layers_keep_the_faster_kernel(shape, dtype, which, slow):
     d = B.desc_of(shape, dtype, relu=True, in_nhwc=True, out_nhwc=True, filt_krsc=True)
     assert not B.conv_variant_name(d, which).startswith(slow), B.conv_variant_name(d, which)
+
+
+# fp32 first layers: us of the gather kernels' best, of the kernel on split products
+@pytest.mark.parametrize("N,R,split", [
+    (1, 11, False),  # 11.3, 17.4
+    (2, 11, False),  # 14.8, 17.8
+    (5, 11, True),   # 19.3, 18.3
+    (12, 11, True),  # 38.7, 27.2
+    (1, 7, False),   # 9.6, 11.7
+    (4, 7, True),    # 19.0, 15.1
+    (8, 7, True),    # 30.7, 23.3
+])
+def test_first_layers_go_to_split_products_where_they_are_faster(N, R, split):
+    shape = ConvShape(N, 3, 227, 227, 96, 11, 11, 4, 0) if R == 11 else ConvShape(N, 3, 224, 224, 64, 7, 7, 2, 3)
+    name, nows = picks(shape, wl.F32)
+    assert name.startswith("swins_") == split, name
+    assert not nows.startswith("swins_"), nows
