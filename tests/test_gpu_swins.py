@@ -3,6 +3,7 @@ edges, no further from 64 bits than the gather kernels, and with values that its
 import numpy as np
 import pytest
 
+import oracle
 from paper_1611_06945_amd import binding as B
 from paper_1611_06945_amd import workloads as wl
 from paper_1611_06945_amd.workloads import ConvShape
@@ -114,3 +115,74 @@ def test_output_close_to_the_size_limit():
         assert bool(torch.isnan(buf[n_out:]).all()), name
         want = buf[:n_out] if want is None else want
         assert torch.equal(buf[:n_out], want), name
+
+
+def test_7x7_no_further_from_64_bits_than_the_gather_kernels():
+    shape = ConvShape(2, 3, 75, 71, 64, 7, 7, 2, 3)
+    case = DeviceCase(shape, wl.F32, data_of(shape, 6210), relu=False)
+    ref = case.ref()
+    err = {n: np.linalg.norm(to_host_f64(case.run(variant=i), wl.F32) - ref) / np.linalg.norm(ref)
+           for i, n in enumerate(case.variant_names()) if n.startswith(("swins_", "ug_")) and "_sk" not in n}
+    gather = min(e for n, e in err.items() if n.startswith("ug_"))
+    mine = [n for n in err if n.startswith("swins_")]
+    assert mine
+    for n in mine:
+        assert err[n] <= gather, (n, err[n], gather)
+
+
+def absolute_sums(case):
+    """Sum of |in * filt| + |bias| of every output: what the rounding errors of a sum are measured against."""
+    s = case.shape
+    return oracle.conv_fwd(np.abs(case.data["in"]).astype(np.float64), np.abs(case.data["filt"]).astype(np.float64),
+                           np.abs(case.data["bias"]).astype(np.float64), stride=s.stride, pad=s.pad, relu=False)
+
+
+@pytest.mark.parametrize("relu", [False, True])
+@pytest.mark.parametrize("R,stride,pad", [(11, 4, 0), (7, 2, 3)])
+def test_finite_results_beyond_the_scaled_range(R, stride, pad, relu):
+    """Operands that overflow once scaled by 2^24 (above about 2^103) and sums that overflow once scaled by 2^48 (above 2^79), in a call whose
+    results are all finite: every one is what the definition gives, the ordinary ones beside them too.  Ragged tiles: 100 pixels
+    of 256 and 528 of 768, 34 and 97 filters."""
+    for K in (34, 97):
+        shape = ConvShape(2, 3, 47, 47 - 4 * (R == 7), K, R, R, stride, pad)
+        data = data_of(shape, 6500 + K)
+        x, f = data["in"], data["filt"]
+        f[3] = 0.0
+        f[3, 1, R // 2, 2] = np.float32(2.0 ** 110)   # one tap: its products are finite, its parts are not
+        f[K - 1] = 0.0
+        f[K - 1, 2, 0, R - 1] = -np.float32(2.0 ** 104)
+        f[5] = np.abs(f[5]) * np.float32(2.0 ** 80)   # sums of about 2^86 from parts that are all finite
+        x[1, :, 20:24, :] = 0.0
+        x[1, 0, 9, 9] = np.float32(1.5 * 2.0 ** 105)  # a pixel beyond it, beside ordinary filters: results of about 2^103
+        f[5, 0] = f[3, 0] = f[K - 1, 0] = 0.0         # (times the large filters it would be beyond fp32)
+        case = DeviceCase(shape, wl.F32, data, relu=relu)
+        ref, size = case.ref(), absolute_sums(case)
+        assert np.abs(ref).max() < 2.0 ** 126 and np.abs(ref[:, 5]).max() > 2.0 ** 82 and np.abs(ref[0, 3]).max() > 2.0 ** 110
+        for i, name in variants_of(case):
+            print(name, shape, relu, flush=True)
+            got = to_host_f64(case.run(variant=i), wl.F32)
+            assert np.all(np.isfinite(got)), name
+            # (a sum of n terms in fp32, whatever the order: n + 1 roundings of 2^-24 of the terms' sizes)
+            bound = (3 * R * R + 1) * 2.0 ** -24 * size
+            assert np.all(np.abs(got - ref) <= bound), (name, np.max(np.abs(got - ref) / bound))
+
+
+@pytest.mark.parametrize("R,stride,pad", [(11, 4, 0), (7, 2, 3)])
+def test_infinities_keep_their_sign_and_nan_stays_nan(R, stride, pad):
+    shape = ConvShape(2, 3, 47, 45, 34, R, R, stride, pad)
+    data = data_of(shape, 6600)
+    data["in"][0, 1, 20, 21] = np.inf
+    data["in"][0, 2, 40, 40] = -np.inf
+    data["in"][1, 2, 30, 11] = np.nan
+    data["filt"][4] = np.abs(data["filt"][4])
+    data["filt"][4, 0, 0, 0] = -np.inf
+    case = DeviceCase(shape, wl.F32, data, relu=False)
+    with np.errstate(invalid="ignore"):
+        ref = case.ref()
+    assert np.isnan(ref).any() and (ref == np.inf).any() and (ref == -np.inf).any()
+    for i, name in variants_of(case):
+        got = to_host_f64(case.run(variant=i), wl.F32)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), name
+        assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        finite = np.isfinite(ref)
+        assert np.max(np.abs(got[finite] - ref[finite])) <= TOL[wl.F32] * np.max(np.abs(ref[finite])), name
