@@ -8,7 +8,7 @@
 //     row apart by their remainder, column c at (c mod stride)*hp + c / stride, so that neighbouring pixels read
 //     neighbouring positions for every tap, whatever the stride;
 //   * [N][C][H][W]: a thread loads four neighbouring pixels of eight channels (8 bytes each), puts the channels of a pixel
-//     together with byte permutes and writes 16 bytes per pixel; the slab's borders are cleared once;
+//     together with byte permutes and writes 16 bytes per pixel into a slab cleared once, borders and all;
 //     (a row may start on an odd element: such loads are slower, but one of them replaces four);
 //     [N][H][W][C]: 16-byte copies;
 //   * [K][C][R][S]: the rows of a tile go to LDS as they are (whole 16-byte runs); a lane reads its 8 channels x R*S taps,
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void dwin_kernel(ConvArgs a, Dwi
         }
     } else {
         // four neighbouring pixels of one row and 8 channels; the last four of a row end with the row.  Only pixels are
-        // written to the slab, chunk after chunk: its borders are cleared once
+        // written to the slab, chunk after chunk: it is cleared once, whole, and its borders stay zero
         const int rows = Yl - Y0 + R;
         const int swap = (tid >> 2) & 1;
 #pragma unroll
@@ -631,9 +631,9 @@ template <class CFG>
 void dwin_register_one(std::vector<Variant>& out, const TileModel& model)
 {
     Variant v;
-    char buf[160];
+    char buf[160];  // (without the rows of a stage: no two tiles differ in them alone, and a test holds the names apart)
     snprintf(buf, sizeof buf, "%sdwin_%s_%dx%d_M%dN%d_w%dx%dx%d_b%d_c%d_s%d%s", CFG::NHWC ? "nhwc_" : "", dtype_name(CFG::DT), CFG::R, CFG::R,
-             CFG::TM, CFG::TNP, CFG::WM, CFG::WN, CFG::WK, CFG::MB, CFG::CB, CFG::SLOTS, CFG::DB ? "_db" : CFG::NST > 1 ? "_r1" : "");
+             CFG::TM, CFG::TNP, CFG::WM, CFG::WN, CFG::WK, CFG::MB, CFG::CB, CFG::SLOTS, CFG::DB ? "_db" : "");
     v.name = buf;
     v.dtype = CFG::DT;
     v.split = 1;

@@ -509,3 +509,22 @@ def test_run_ops_validates_each_element_and_reports_the_failing_index():
         B.conv_run_ops([B.op_conv(d, 256 + 2, 512, None, 1024)])
     assert e.value.status == B.CONV_EINVAL
     assert ctypes.sizeof(B.conv_op) == 4 + 44 + 5 * 8 + 8 + 36 + 4   # the C layout: int32, conv_desc, 5 pointers, size_t, 9 int32, tail padding
+
+
+def test_variant_names_are_distinct():
+    """Names are the keys of saved caches: of two kernels with one name, a cache could only ever select one."""
+    S = wl.ConvShape
+    shapes = [S(n, c, h, h, k, r, r, s, p) for (r, s, p) in ((1, 1, 0), (3, 1, 1), (3, 2, 1), (3, 3, 0), (5, 1, 2), (5, 2, 2), (7, 2, 3), (11, 4, 0))
+              for (n, c, h, k) in ((1, 8, 13, 16), (2, 64, 14, 64), (20, 256, 13, 384), (64, 64, 56, 192), (1, 3, 227, 96), (8, 3, 224, 64), (20, 256, 6, 4096))
+              if h + 2 * p >= r]
+    shapes += [S(20, 256, 6, 6, 4096, 6, 6, 1, 0), S(64, 4096, 1, 1, 1000, 1, 1, 1, 0)]
+    seen = 0
+    for shape in shapes:
+        for dtype in (wl.F32, wl.F16, wl.BF16):
+            for flags in ({}, {"in_nhwc": True, "out_nhwc": True, "filt_krsc": True}, {"in_nhwc": True, "out_nhwc": True, "filt_packed": True},
+                          {"in_nhwc": True, "filt_packed": True}, {"out_nhwc": True}):
+                d = B.desc_of(shape, dtype, relu=True, **flags)
+                names = [B.conv_variant_name(d, i) for i in range(B.conv_variant_count(d))]
+                assert len(names) == len(set(names)), (shape, dtype, flags)
+                seen += len(names)
+    assert seen > 5000
