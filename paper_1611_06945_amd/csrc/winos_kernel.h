@@ -19,13 +19,19 @@
 //     asked for instruction by instruction: left alone, the compiler puts the vector work first and the loads last.
 //   * Input rows are fetched 16 bytes per lane, the last vector of a row ending with the row: with 4-byte loads the issue
 //     of the loads alone took 300 .. 1700 clocks of a wave's 4000 per step.  Neighbouring tile rows share their rows.
-// What bounds it: 64 channels x 32 tiles multiply for 1540 of the ~3000 clocks a step takes (LDS traffic ~1000, vector work
-// ~1400 of a SIMD, not all of it underneath); the start (5000 clocks) and the inverse transform (7000) of a workgroup are
-// exposed, with one workgroup per CU.  Tiles of 64 were tried (twice the registers, no room for the two-stage mix: 238 us
-// where 96 x 32 took 218), and two workgroups of 32 x 32 per CU (vector work per product doubles: 350).
-// Measured (us per call back to back, filter transform included, kernel before -> this one; boxes differ by up to 10 %): 20
-// images of 13x13x256 -> 384 46 -> 35.5, 64 of 56x56x64 -> 192 340 -> 198 .. 222.  With other inputs from call to call 32.8 and 217;
-// traced, in which a launch takes longer, 31.3 + 8.8 for the filter transform and 237 + 6.2.
+//   * With 64 or 96 channels (LOOP) the grid is one workgroup per CU, which takes tile after tile; the steps of successive tiles
+//     follow each other, so that only the first one pays for its start (of 64 images of 56x56x64 -> 192, 12.25 tiles per CU, the
+//     starts and the drained stores took 75 of 227 us).  The inverse transform has its own piece of LDS for that; channels
+//     come to it 32 at a time.  A layer of fewer tiles than CUs loses nothing by it.
+// What bounds it: bytes from L2 first.  A step of 96 channels x 32 tiles fetches 147 KB of filters and 20 to 36 of rows and takes
+// 5600 clocks, 32 bytes a clock and CU; its MFMAs are 2304.  On 64 images of 56x56x64 -> 192, of 183 us the epilogue is 52 (22 of
+// them its stores), filters that do not come from L1 27, rows 14, the transform 9, splits 3.  Filters requested earlier (each
+// part as soon as its last product is issued) gain nothing.  Tiles of 64 would halve the filters' bytes but need twice the
+// accumulators (238 us where 96 x 32 took 218, both without LOOP); two workgroups of 32 x 32 per CU double the vector work per
+// product (350).  Taking a split's parts out with v_dot2_f32_bf16 (7 instructions a pair instead of 11) was 0 to 5 % slower.
+// Measured (us per call back to back, filter transform included, start of this form -> now; boxes differ by up to 10 %): 64 images of
+// 56x56x64 -> 192 227 -> 179 (M96), 262 -> 188 (M64), 16 of 28x28x128 -> 256 44.3 -> 40.8, 8 of 40x40x96 -> 100 21.4 -> 21.0; 20 of
+// 13x13x256 -> 384, 186 tiles, 35.7 -> 35.6 (8.8 of them the filter transform).
 // Range: the parts of x reach 24 bits below x, which for |x| < 2^-102 is below bf16's normal numbers.  Both operands are
 // therefore scaled by 2^24 ahead of the splits: every part of every fp32 number, subnormal ones included, is then a normal
 // bf16 number or zero, whatever the other operand is.  Sums carry 2^48 and are scaled back behind the inverse transform.
@@ -46,12 +52,14 @@ struct WinosCfg {
     static_assert((2 * MB) % RING == 0 && RING >= 2, "the filter ring must divide the groups of a step");
     static constexpr int NT = 512;        // 8 waves of two planes
     static constexpr int WPS = MB == 1 && LBV <= 2 ? 4 : 2;  // waves per SIMD the registers are fitted to
+    static constexpr bool LOOP = MB > 1;  // a workgroup takes one tile after another, each started beneath the one before
     static constexpr int TM = 32 * MB;    // output channels per workgroup
     static constexpr int TT = 32;         // tiles (2x2 output blocks) per workgroup: one transform task (tile, channel) per thread
     static constexpr int V_FLOATS = 16 * 4 * TT * 4;
     static constexpr int MP = TT + 4;     // row pitch of the plane buffer of the epilogue
-    static constexpr int E_FLOATS = (MB < 2 ? MB : 2) * 16 * 32 * MP;  // two 32-channel blocks at a time
+    static constexpr int E_FLOATS = 16 * 32 * MP;  // a 32-channel block at a time
     static constexpr int SLOTS = NT * LBV;  // 16-byte vectors of input rows staged per step
+    static constexpr int SPARE = 64 * 4;    // a vector per lane behind the rows, for tasks without a row
     // the inputs are scaled where that takes fewer instructions: staged rows 4 * LBV, transform 8 per thread and step (at
     // equal counts the rows are better, beneath the stage with less vector work)
     static constexpr bool SCALE_ROWS = LBV <= 2;
@@ -64,10 +72,12 @@ struct WinosGeom {
     int W4;        // 16-byte vectors of a row; the last one ends with the row
     int PWL;       // floats per staged row
     int pitch;     // floats per channel of the staged rows, 16 mod 64: the lanes of a transform read distinct banks
+    int KT, TN;    // channel tiles, groups of tiles
+    FastDiv dTW, dIR, dTH, dW4, dRow, dGroup;  // by TW, IR, TH, W4, rows_max * W4 and 3 * TN
 };
 
 template <class CFG>
-__host__ __device__ inline WinosGeom winos_geom(int N, int W, int OH, int OW)
+inline WinosGeom winos_geom(int N, int K, int W, int OH, int OW)
 {
     WinosGeom g;
     g.TH = (OH + 1) / 2;
@@ -82,15 +92,17 @@ __host__ __device__ inline WinosGeom winos_geom(int N, int W, int OH, int OW)
     g.PWL = 2 * g.TW + 2;
     g.pitch = g.rows_max * g.PWL;
     g.pitch += ((16 - g.pitch % 64) + 64) % 64;
+    g.KT = (K + CFG::TM - 1) / CFG::TM;
+    g.TN = (g.tiles + CFG::TT - 1) / CFG::TT;
     return g;
 }
 
 template <class CFG>
-size_t winos_lds_bytes(int N, int W, int OH, int OW)
+size_t winos_lds_bytes(const WinosGeom& g)
 {
-    const size_t pipe = sizeof(float) * (CFG::V_FLOATS + 16 * (size_t)winos_geom<CFG>(N, W, OH, OW).pitch + 4 * CFG::NT);
+    const size_t pipe = sizeof(float) * (CFG::V_FLOATS + 16 * (size_t)g.pitch + CFG::SPARE);
     const size_t epi = sizeof(float) * CFG::E_FLOATS;
-    return pipe > epi ? pipe : epi;
+    return CFG::LOOP ? pipe + epi : pipe > epi ? pipe : epi;
 }
 
 inline size_t winos_filter_bytes(int K, int C) { return (size_t)((C + 15) / 16) * 16 * ((K + 31) / 32) * 3072; }
@@ -141,95 +153,137 @@ __global__ __launch_bounds__(512) void winos_filter_kernel(const float* __restri
     }
 }
 
-// a.dX, a.dY, a.dZ, a.dS, a.dRS divide by TW, IR, TH, W4, rows_max * W4; a.ws holds U
-template <class CFG>
-__global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
+struct WinosArgs {
+    ConvArgs a;  // a.ws holds U
+    WinosGeom d;
+};
+
+// The kernel's arguments, to be read again where they are asked for: what a tile needs once would otherwise be kept in scalar
+// registers through the loop, more of them than there are (150 moves a step between them and lanes of vector registers)
+__device__ __forceinline__ const WinosArgs& winos_args_again()
 {
+    auto p = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const WinosArgs*)p;
+}
+
+template <class CFG>
+__global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(WinosArgs w)
+{
+    const ConvArgs& a = w.a;
+    const WinosGeom& d = w.d;
     constexpr int MB = CFG::MB, LBV = CFG::LBV, NT = CFG::NT, TM = CFG::TM, TT = CFG::TT, MP = CFG::MP;
+    asm volatile("" ::"s"(a.in), "s"(a.ws), "s"(a.N), "s"(a.C), "s"(a.H), "s"(a.W), "s"(a.K), "s"(a.pad), "s"(a.HW), "s"(a.in_bytes), "s"(d.tiles), "s"(d.IR), "s"(d.rows_max), "s"(d.PWL), "s"(d.pitch));
+    asm volatile("" ::"s"(d.KT), "s"(d.TN), "s"(d.dTW.mul), "s"(d.dTW.shift), "s"(d.dTW.d), "s"(d.dIR.mul), "s"(d.dIR.shift), "s"(d.dIR.d), "s"(d.dTH.mul), "s"(d.dTH.shift), "s"(d.dTH.d), "s"(d.dW4.mul), "s"(d.dW4.shift), "s"(d.dW4.d), "s"(d.dRow.mul), "s"(d.dRow.shift), "s"(d.dRow.d), "s"(d.dGroup.mul), "s"(d.dGroup.shift), "s"(d.dGroup.d));
     constexpr uint32_t kFar = 0x80000000u;  // tensors stay below 2 GiB: this offset plus any scalar offset is out of range
     typedef Mma<CONV_BF16, 32> mma_t;
     extern __shared__ __attribute__((aligned(16))) float smem[];
 
-    const WinosGeom geo = winos_geom<CFG>(a.N, a.W, a.OH, a.OW);
-    const int PWL = geo.PWL, pitch = geo.pitch;
+    const int PWL = d.PWL, pitch = d.pitch;
     float* const Vs = smem;                  // [16][4][TT][4]
-    float* const Rs = smem + CFG::V_FLOATS;  // [16][pitch], then a spare vector per thread
+    float* const Rs = smem + CFG::V_FLOATS;  // [16][pitch], then the spare vectors
+    float* const Ms = CFG::LOOP ? Rs + 16 * pitch + CFG::SPARE : smem;  // [16][32][MP], of the epilogue
 
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int C16 = (a.C + 15) >> 4, MBK = (a.K + 31) >> 5;
-    // one XCD's workgroups are a contiguous run of "groups of 3 channel tiles; within a group all tile groups"
-    int t0, m0;
-    {
-        const int KT = (a.K + TM - 1) / TM, TN = (geo.tiles + TT - 1) / TT, total = KT * TN;
-        const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-        const int s = x * (total >> 3) + (x < (total & 7) ? x : (total & 7)) + j;
-        const int per_group = 3 * TN;
-        const int gr = s / per_group, rem = s - gr * per_group;
-        const int gs = (KT - 3 * gr) < 3 ? (KT - 3 * gr) : 3;
-        const int tg = rem / gs, kk = rem - tg * gs;
-        t0 = tg * TT;
-        m0 = (3 * gr + kk) * TM;
-    }
+    // An XCD's workgroups share a contiguous run of "groups of 3 channel tiles; within a group all tile groups", workgroup
+    // `mine` of `wgs` its tiles mine, mine + wgs, ...
+    const int total = d.KT * d.TN, xcd = blockIdx.x & 7, mine = blockIdx.x >> 3;
+    const int first = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : (total & 7)), count = (total >> 3) + (xcd < (total & 7) ? 1 : 0);
+    const int wgs = ((int)gridDim.x >> 3) + (xcd < ((int)gridDim.x & 7) ? 1 : 0);
+    struct Place {
+        int t0, m0;
+    };
+    auto place_of = [&](const WinosGeom& d, int q) {
+        uint32_t gr, rem;
+        d.dGroup.divmod((uint32_t)(first + q), gr, rem);
+        const int left = d.KT - 3 * (int)gr, gs = left < 3 ? left : 3;
+        const uint32_t tg = gs == 3 ? rem / 3u : rem >> (gs - 1);
+        return Place{(int)tg * TT, (3 * (int)gr + (int)(rem - tg * gs)) * TM};
+    };
 
     // ---- transformed filters: ring of groups (plane of this wave, 32-channel block), three parts each ----------------
     constexpr int GRP = 2 * MB, RING = CFG::RING;
     const __amdgpu_buffer_rsrc_t ru = make_rsrc(a.ws, (uint32_t)C16 * 16u * (uint32_t)MBK * 3072u);
     const uint32_t a_lane = (uint32_t)lane * 16u;
     const uint32_t u_plane = (uint32_t)MBK * 3072u, u_step = u_plane * 16u;
-    const uint32_t u_base = (uint32_t)(wave * 2) * u_plane + (uint32_t)(m0 >> 5) * 3072u;
+    auto filters_of = [&](const Place& p) { return (uint32_t)(wave * 2) * u_plane + (uint32_t)(p.m0 >> 5) * 3072u; };
     uint4 ar[RING][3];
-    auto load_a = [&](auto slot_c, auto grp_c, uint32_t step) {
+    auto load_a = [&](auto slot_c, auto grp_c, uint32_t base) {
         constexpr int slot = decltype(slot_c)::value, grp = decltype(grp_c)::value;
-        const uint32_t soff = u_base + step * u_step + (uint32_t)(grp / MB) * u_plane + (uint32_t)(grp % MB) * 3072u;
+        const uint32_t soff = base + (uint32_t)(grp / MB) * u_plane + (uint32_t)(grp % MB) * 3072u;
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(ru, (int)a_lane, (int)(soff + q * 1024u), 0);
+            // (the part's kilobyte in a scalar or a vector register, whichever kind is short in the loop)
+            const u32x4 v = CFG::LOOP ? __builtin_amdgcn_raw_buffer_load_b128(ru, (int)(a_lane + q * 1024u), (int)soff, 0)
+                                      : __builtin_amdgcn_raw_buffer_load_b128(ru, (int)a_lane, (int)(soff + q * 1024u), 0);
             ar[slot][q] = make_uint4(v.x, v.y, v.z, v.w);
         }
     };
 
     // ---- input rows ----------------------------------------------------------------------------------------------------
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
-    auto stacked_row = [&](uint32_t tile_row) {
+    auto stacked_row = [&](const WinosGeom& d, uint32_t tile_row) {
         uint32_t n, ty;
-        a.dZ.divmod(tile_row, n, ty);
-        return (int)n * geo.IR + 2 * (int)ty;
+        d.dTH.divmod(tile_row, n, ty);
+        return (int)n * d.IR + 2 * (int)ty;
     };
-    uint32_t g_first, t_in_row;
-    a.dX.divmod((uint32_t)t0, g_first, t_in_row);
-    const int t_last = (t0 + TT < geo.tiles ? t0 + TT : geo.tiles) - 1;
-    const int s0 = __builtin_amdgcn_readfirstlane(stacked_row(g_first));
-    const int nrows = __builtin_amdgcn_readfirstlane(stacked_row(a.dX.div((uint32_t)t_last))) + 4 - s0;
+    auto first_row = [&](const WinosGeom& d, int t0) { return __builtin_amdgcn_readfirstlane(stacked_row(d, d.dTW.div((uint32_t)t0))); };
     // task = (channel of the step, staged row, 16-byte vector of the row): the loads of a wave are contiguous runs of rows
     uint32_t r_goff[LBV];
-    int r_lds[LBV], r_c[LBV];
+    int r_lds[LBV], r_task[LBV];  // r_task: column, channel << 12, row << 16
 #pragma unroll
     for (int i = 0; i < LBV; ++i) {
-        uint32_t c, e, ri, xv, n, yy;
-        a.dRS.divmod((uint32_t)(i * NT + tid), c, e);
-        a.dS.divmod(e, ri, xv);
-        a.dY.divmod((uint32_t)s0 + ri, n, yy);
-        const int y = (int)yy - a.pad, x = (int)xv * 4 < a.W - 4 ? (int)xv * 4 : a.W - 4;
-        const bool ok = c < 16u && (int)ri < nrows && (unsigned)y < (unsigned)a.H && (int)n < a.N;
-        r_goff[i] = ok ? (uint32_t)((((int)n * a.C + (int)c) * a.H + y) * a.W + x) * 4u : kFar;
-        r_lds[i] = ok ? (int)ri * PWL + x + a.pad + (int)c * pitch : 16 * pitch + tid * 4;
-        r_c[i] = (int)c;
+        uint32_t c, e, ri, xv;
+        d.dRow.divmod((uint32_t)(i * NT + tid), c, e);
+        d.dW4.divmod(e, ri, xv);
+        const int x = (int)xv * 4 < a.W - 4 ? (int)xv * 4 : a.W - 4;
+        r_lds[i] = c < 16u ? (int)(ri * (uint32_t)PWL + c * (uint32_t)pitch) + x + a.pad : 16 * pitch + lane * 4;
+        r_task[i] = x | (int)(c & 15u) << 12 | (c < 16u ? (int)ri : 0x7fff) << 16;
     }
+    // Rows are fetched for tile `row_q`, step `row_step`, up to three steps ahead of the products
+    int row_q = mine, row_step = 0;
+    auto aim_rows = [&](const WinosArgs& w) {
+        if (row_q >= count) {
+#pragma unroll
+            for (int i = 0; i < LBV; ++i) r_goff[i] = kFar;
+            return;
+        }
+        const ConvArgs& a = w.a;
+        const WinosGeom& d = w.d;
+        const int t0 = place_of(d, row_q).t0, t_last = (t0 + TT < d.tiles ? t0 + TT : d.tiles) - 1;
+        const int s0 = first_row(d, t0), nrows = first_row(d, t_last) + 4 - s0;
+#pragma unroll
+        for (int i = 0; i < LBV; ++i) {
+            const int ri = r_task[i] >> 16, c = r_task[i] >> 12 & 15, x = r_task[i] & 0xfff;
+            uint32_t n, yy;
+            d.dIR.divmod((uint32_t)(s0 + ri), n, yy);
+            const int y = (int)yy - a.pad;
+            const bool ok = ri < nrows && (unsigned)y < (unsigned)a.H && (int)n < a.N;
+            r_goff[i] = ok ? (uint32_t)((((int)n * a.C + c) * a.H + y) * a.W + x) * 4u : kFar;
+        }
+    };
     const uint32_t step_bytes = (uint32_t)a.HW * 64u;
     struct Rows {
         f32x4 v[LBV];
     };
-    auto load_rows = [&](Rows& r, int step) {  // channels past the last one read as zero
+    auto load_rows = [&](Rows& r) {  // channels past the last one read as zero
 #pragma unroll
         for (int i = 0; i < LBV; ++i)
-            r.v[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rin, (int)(step * 16 + r_c[i] < a.C ? r_goff[i] : kFar),
-                                                                                     (int)((uint32_t)step * step_bytes), 0));
+            r.v[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rin, (int)(row_step * 16 + (r_task[i] >> 12 & 15) < a.C ? r_goff[i] : kFar),
+                                                                                     (int)((uint32_t)row_step * step_bytes), 0));
+        ++row_step;
+        if (CFG::LOOP && row_step == C16) {
+            row_step = 0;
+            row_q += wgs;
+            aim_rows(winos_args_again());
+        }
     };
-    auto store_rows = [&](const Rows& r) {
+    auto store_rows = [&](const Rows& r) {  // (rows outside the image are written too, as zeros)
 #pragma unroll
         for (int i = 0; i < LBV; ++i) {
-            float* dst = Rs + r_lds[i];  // (a task without a row writes to its own spare vector behind the rows)
+            float* dst = Rs + r_lds[i];
 #pragma unroll
             for (int j = 0; j < 4; ++j) dst[j] = CFG::SCALE_ROWS ? r.v[i][j] * kSplitScale : r.v[i][j];
         }
@@ -237,24 +291,29 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
 
     // ---- input transform: thread = (tile, channel) ---------------------------------------------------------------------
     const int v_quad = wave & 3, v_sub = lane & 3, v_tile = (wave >> 2) * 16 + (lane >> 2);
-    int v_src;
-    {
-        const int t = (t0 + v_tile < geo.tiles) ? t0 + v_tile : t0;  // tiles past the end repeat the first one; never stored
+    typedef __attribute__((address_space(3))) char* lds_bytes;
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(3))) f32x2* lds_pairs;
+    uint32_t v_src[4];  // LDS address of a row each: addresses made in the loop would push its LDS reads behind the products they belong above
+    auto aim_transform = [&](const WinosGeom& d, int t0) {
+        const int t = (t0 + v_tile < d.tiles) ? t0 + v_tile : t0;  // tiles past the end repeat the first one; never stored
         uint32_t gr, tx;
-        a.dX.divmod((uint32_t)t, gr, tx);
-        v_src = (v_quad * 4 + v_sub) * pitch + (stacked_row(gr) - s0) * PWL + 2 * (int)tx;
-    }
+        d.dTW.divmod((uint32_t)t, gr, tx);
+        v_src[0] = (uint32_t)(uintptr_t)(lds_bytes)smem + (uint32_t)(CFG::V_FLOATS + (v_quad * 4 + v_sub) * d.pitch + (stacked_row(d, gr) - first_row(d, t0)) * d.PWL + 2 * (int)tx) * 4u;
+#pragma unroll
+        for (int r = 1; r < 4; ++r) v_src[r] = v_src[r - 1] + (uint32_t)d.PWL * 4u;
+    };
     float* const v_dst = Vs + (v_quad * TT + v_tile) * 4 + v_sub;
     struct Tile {
         float2 lo[4], hi[4];
     };
     auto read_tile = [&]() {
-        const float* src = Rs + v_src;
         Tile d;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            d.lo[r] = *(const float2*)&src[r * PWL];
-            d.hi[r] = *(const float2*)&src[r * PWL + 2];
+            const lds_pairs src = (lds_pairs)(uintptr_t)v_src[r];
+            d.lo[r] = make_float2(src[0][0], src[0][1]);
+            d.hi[r] = make_float2(src[1][0], src[1][1]);
         }
         return d;
     };
@@ -283,12 +342,14 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
     };
 
     typename mma_t::acc_t acc[2][MB];
+    auto clear = [&]() {
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+        for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
+            for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[x][mb][v] = 0.0f;
+                for (int v = 0; v < 16; ++v) acc[x][mb][v] = 0.0f;
+    };
 
     // lane (li, g) feeds column li of a block with channels 8g .. 8g+7 of the step
     struct Plane {
@@ -303,12 +364,12 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
         return split3(x);
     };
     // the six partial products of plane x, smallest first; the filters of group grp + RING - 1 are fetched meanwhile
-    auto multiply = [&](auto xc, const Split3& b, uint32_t step) {
+    auto multiply = [&](auto xc, const Split3& b, uint32_t now, uint32_t next) {
         constexpr int x = decltype(xc)::value;
         static_for<MB>([&](auto mbc) {
             constexpr int mb = decltype(mbc)::value, grp = x * MB + mb, ahead = grp + RING - 1;
             constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
-            load_a(std::integral_constant<int, ahead % RING>{}, std::integral_constant<int, ahead % GRP>{}, step + ahead / GRP);
+            load_a(std::integral_constant<int, ahead % RING>{}, std::integral_constant<int, ahead % GRP>{}, ahead < GRP ? now : next);
 #pragma unroll
             for (int q = 0; q < 6; ++q) acc[x][mb] = mma_t::run(ar[grp % RING][pa[q]], b.p[pb[q]], acc[x][mb]);
         });
@@ -327,55 +388,15 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
     typedef std::integral_constant<int, 0> c0_t;
     typedef std::integral_constant<int, 1> c1_t;
 
-    // ---- pipeline: entering step i, Vs holds the tiles of step i, `p0` the parts of this wave's first plane and `v1` its
-    // second plane, Rs the rows of step i+1, and the rows of step i+2 are in flight.  Every wave holds all it needs of Vs.
-    Rows rows, rows1;
-    load_rows(rows, 0);
-    static_for<RING - 1>([&](auto gc) { load_a(gc, gc, 0); });
-    load_rows(rows1, 1);
-    for (int i = tid; i < 4 * pitch; i += NT) *(f32x4*)&Rs[4 * i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};  // the border stays zero
-    __syncthreads();
-    store_rows(rows);
-    load_rows(rows, 2);
-    __syncthreads();
-    write_tile(read_tile());
-    __syncthreads();
-    Split3 p0 = split_plane(read_plane(0)), p1;
-    Plane v1 = read_plane(1);
-    store_rows(rows1);
-    __syncthreads();
-    for (int i = 0; i < C16; ++i) {
-        __builtin_amdgcn_sched_barrier(0);
-        const Tile d = read_tile();  // step i+1 (past the last step: nobody reads what becomes of it)
-        p1 = split_plane(v1);
-        multiply(c0_t{}, p0, (uint32_t)i);
-        write_tile(d);
-        interleave(std::integral_constant<int, ((CFG::SCALE_ROWS ? 96 : 104) + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (8 + 6 * MB - 1) / (6 * MB)>{});
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        const Plane v0 = read_plane(0);
-        v1 = read_plane(1);
-        multiply(c1_t{}, p1, (uint32_t)i);
-        store_rows(rows);
-        p0 = split_plane(v0);
-        interleave(std::integral_constant<int, (48 + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (2 * LBV + 6 * MB - 1) / (6 * MB)>{});
-        __builtin_amdgcn_sched_barrier(0);
-        load_rows(rows, i + 3);
-        __syncthreads();
-    }
-
     // ---- epilogue, 32 channels at a time: planes to LDS, inverse transform, bias + activation, 2x2 stores ---------------
-    float* const Ms = smem;  // [2][16][32][MP]
-    const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);
-    const __amdgpu_buffer_rsrc_t rout = make_rsrc(a.out, a.out_bytes);
-    const bool even = (a.OW & 1) == 0;  // a tile's two outputs of a row are 8-byte aligned and both inside
     // Entries (filter k, image n, window origin iy, ix of a tile's first output) of the lanes in `mask`, summed in fp32 from the
     // definition: taps outside the image are left out.  The wave takes them together, 64 / entries lanes (rounded down to a
     // power of two) for each, which share its channels; a tile's four outputs share their loads; a lane whose sums are all
     // NaN is done.  Bound by the scattered loads.  Call of 20 images of 13x13x256 -> 384 (40 us on ordinary data) with one
     // infinite pixel 148 us, one NaN filter value 130, NaN everywhere 43, results beyond 2^79 everywhere 820; with one lane
     // per entry and output 7900, 1370, 5900 and 5900.
-    auto sum_again = [&](uint64_t mask, int k, int n, int iy, int ix, float* y) {
+    auto sum_again = [&](const ConvArgs& a, uint64_t mask, int k, int n, int iy, int ix, float* y) {
+        const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
         const int count = __builtin_popcountll(mask), lg = 31 - __builtin_clz(64 / count);
         const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
         const bool mine = (mask >> lane) & 1;
@@ -436,70 +457,174 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(ConvArgs a)
             y[q] = mine ? total : y[q];
         }
     };
-    static_for<(MB + 1) / 2>([&](auto hc) {
-        constexpr int mb0 = decltype(hc)::value * 2, MB2 = MB - mb0 < 2 ? MB - mb0 : 2;
-        if constexpr (mb0 > 0) __syncthreads();
+    auto finish = [&](const Place& at) {
+        const WinosArgs& w = winos_args_again();
+        const ConvArgs& a = w.a;
+        const WinosGeom& d = w.d;
+        const __amdgpu_buffer_rsrc_t rout = make_rsrc(a.out, a.out_bytes);
+        const bool even = (a.OW & 1) == 0;  // a tile's two outputs of a row are 8-byte aligned and both inside
+        // thread = (tile, channel of 16): two channels of each block
+        const int kr = tid >> 5, t = at.t0 + li;
+        const bool in = t < d.tiles;
+        uint32_t gr, tx, n, ty;
+        d.dTW.divmod(in ? (uint32_t)t : 0u, gr, tx);
+        d.dTH.divmod(gr, n, ty);
+        const int oy = 2 * (int)ty, ox = 2 * (int)tx;
+        const uint32_t base = (uint32_t)(((int)n * a.K + at.m0 + kr) * a.OHW + oy * a.OW + ox) * 4u;
+        const uint32_t plane = (uint32_t)a.OHW * 4u, row = (uint32_t)a.OW * 4u;
+        const bool in1 = in && oy + 1 < a.OH, right = ox + 1 < a.OW;
+        float bias[MB][2];
 #pragma unroll
-        for (int mb = 0; mb < MB2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    Ms[((mb * 16 + wave * 2 + x) * 32 + acc_row<32>(v, lane)) * MP + li] = acc[x][mb0 + mb][v];
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < MB2 * 32 * TT / NT; ++j) {
-            const int e = j * NT + tid, kk = e / TT, kl = kk % 32, tl = e % TT;
-            const int k = m0 + mb0 * 32 + kk, t = t0 + tl;
-            const bool ok = k < a.K && t < geo.tiles;
-            const float* src = Ms + ((kk / 32) * 16 * 32 + kl) * MP + tl;
-            float m[4][4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) m[i][jj] = src[(4 * i + jj) * 32 * MP];
-            float r0[4], r1[4];
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                r0[jj] = (m[0][jj] + m[1][jj]) + m[2][jj];
-                r1[jj] = (m[1][jj] - m[2][jj]) - m[3][jj];
+            for (int j = 0; j < 2; ++j) {  // (scalar loads: vector ones would wait for the rows on their way)
+                float b0 = 0.0f, b1 = 0.0f;
+                if (a.bias) {
+                    const int k = at.m0 + mb * 32 + j * 16 + wave * 2, top = a.K - 1;
+                    b0 = a.bias[k < top ? k : top], b1 = a.bias[k + 1 < top ? k + 1 : top];
+                }
+                bias[mb][j] = g ? b1 : b0;
             }
-            float y[4];
-            y[0] = (r0[0] + r0[1]) + r0[2];
-            y[1] = (r0[1] - r0[2]) - r0[3];
-            y[2] = (r1[0] + r1[1]) + r1[2];
-            y[3] = (r1[1] - r1[2]) - r1[3];
-            uint32_t gr, tx, n, ty;
-            a.dX.divmod(ok ? (uint32_t)t : 0u, gr, tx);
-            a.dZ.divmod(gr, n, ty);
-            const int oy = 2 * (int)ty, ox = 2 * (int)tx;
-            const float big = (__builtin_fabsf(y[0]) + __builtin_fabsf(y[1])) + (__builtin_fabsf(y[2]) + __builtin_fabsf(y[3]));
-#pragma unroll
-            for (int q = 0; q < 4; ++q) y[q] *= kSplitUnscale;
-            const uint64_t again = __ballot(ok && !(big < __builtin_inff()));  // a NaN or an infinity in any of the four
-            if (again) sum_again(again, k, (int)n, oy - a.pad, ox - a.pad, y);
-            const float b = buffer_load_elem<float>(rbias, ok ? (uint32_t)k * 4u : kOutOfRange);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                y[q] += b;
-                if (a.relu) y[q] = y[q] > 0.0f ? y[q] : 0.0f;
-            }
-            const uint32_t base = (uint32_t)(((int)n * a.K + k) * a.OHW + oy * a.OW + ox) * 4u;
+        auto store = [&](uint32_t o, bool ok, bool ok1, const float* y) {
 #pragma unroll
             for (int dy = 0; dy < 2; ++dy) {
-                const bool in_row = ok && oy + dy < a.OH;
-                const uint32_t o = in_row ? base + (uint32_t)(dy * a.OW) * 4u : kOutOfRange;
+                const bool in_row = dy ? ok1 : ok;
+                const uint32_t oo = in_row ? o + (dy ? row : 0u) : kOutOfRange;
                 if (even) {
                     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                     __builtin_amdgcn_raw_buffer_store_b64(u32x2{__builtin_bit_cast(uint32_t, y[2 * dy]), __builtin_bit_cast(uint32_t, y[2 * dy + 1])},
-                                                          rout, (int)o, 0, 0);
+                                                          rout, (int)oo, 0, 0);
                 } else {
-                    buffer_store_elem<float>(y[2 * dy], rout, o);
-                    buffer_store_elem<float>(y[2 * dy + 1], rout, in_row && ox + 1 < a.OW ? o + 4u : kOutOfRange);
+                    buffer_store_elem<float>(y[2 * dy], rout, oo);
+                    buffer_store_elem<float>(y[2 * dy + 1], rout, in_row && right ? oo + 4u : kOutOfRange);
                 }
             }
+        };
+        uint32_t bad = 0;  // bit 2 * block + half: sums that are not finite
+        static_for<MB>([&](auto mbc) {
+            constexpr int mb = decltype(mbc)::value;
+            if constexpr (mb > 0) __syncthreads();
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) Ms[((wave * 2 + x) * 32 + acc_row<32>(v, lane)) * MP + li] = acc[x][mb][v];
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int kl = j * 16 + kr;
+                const float* src = Ms + kl * MP + li;
+                float m[4][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) m[i][jj] = src[(4 * i + jj) * 32 * MP];
+                float r0[4], r1[4];
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    r0[jj] = (m[0][jj] + m[1][jj]) + m[2][jj];
+                    r1[jj] = (m[1][jj] - m[2][jj]) - m[3][jj];
+                }
+                float y[4];
+                y[0] = (r0[0] + r0[1]) + r0[2];
+                y[1] = (r0[1] - r0[2]) - r0[3];
+                y[2] = (r1[0] + r1[1]) + r1[2];
+                y[3] = (r1[1] - r1[2]) - r1[3];
+                const float big = (__builtin_fabsf(y[0]) + __builtin_fabsf(y[1])) + (__builtin_fabsf(y[2]) + __builtin_fabsf(y[3]));
+                const bool fine = big < __builtin_inff();  // no NaN, no infinity in any of the four
+                const bool have = at.m0 + mb * 32 + kl < a.K;
+                bad |= in && have && !fine ? 1u << (2 * mb + j) : 0u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    y[q] = __builtin_fmaf(y[q], kSplitUnscale, bias[mb][j]);
+                    if (a.relu) y[q] = __builtin_fmaxf(y[q], 0.0f);
+                }
+                store(base + (uint32_t)(mb * 32 + j * 16) * plane, in && have && fine, in1 && have && fine, y);
+            }
+        });
+        if (__any(bad != 0)) {
+#pragma unroll 1
+            for (int e = 0; e < 2 * MB; ++e) {
+                const uint64_t again = __ballot(bad >> e & 1);
+                if (!again) continue;
+                const int k = at.m0 + e * 16 + kr;
+                float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                sum_again(a, again, k, (int)n, oy - a.pad, ox - a.pad, y);
+                const bool mine_ = bad >> e & 1;
+                const float b = a.bias && mine_ ? a.bias[k] : 0.0f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    y[q] += b;
+                    if (a.relu) y[q] = y[q] > 0.0f ? y[q] : 0.0f;
+                }
+                store(base + (uint32_t)(e * 16) * plane, mine_, mine_ && in1, y);
+            }
         }
-    });
+    };
+
+    // ---- pipeline: entering step i, Vs holds the tiles of step i, `p0` the parts of this wave's first plane and `v1` its
+    // second plane, Rs the rows of step i+1, and the rows of step i+2 are in flight.  Every wave holds all it needs of Vs.
+    // The steps of a workgroup's tiles follow each other without a gap.
+    Rows rows, rows1;
+    Place here = place_of(d, mine);
+    uint32_t now = filters_of(here);
+    aim_rows(w);
+    load_rows(rows);
+    static_for<RING - 1>([&](auto gc) { load_a(gc, gc, now); });
+    load_rows(rows1);
+    aim_transform(d, here.t0);
+    for (int i = tid; i < 4 * pitch; i += NT) *(f32x4*)&Rs[4 * i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};  // the border stays zero
+    __syncthreads();
+    store_rows(rows);
+    load_rows(rows);
+    __syncthreads();
+    write_tile(read_tile());
+    __syncthreads();
+    Split3 p0 = split_plane(read_plane(0)), p1;
+    Plane v1 = read_plane(1);
+    store_rows(rows1);
+    clear();
+    __syncthreads();
+    auto step = [&](uint32_t next) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : "+v"(v1.lo), "+v"(v1.hi));  // (its split belongs beneath the products that follow, not to the step before)
+        const Tile t = read_tile();  // the step after (past the last one: nobody reads what becomes of it)
+        p1 = split_plane(v1);
+        multiply(c0_t{}, p0, now, next);
+        write_tile(t);
+        interleave(std::integral_constant<int, ((CFG::SCALE_ROWS ? 96 : 104) + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (8 + 6 * MB - 1) / (6 * MB)>{});
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        const Plane v0 = read_plane(0);
+        v1 = read_plane(1);
+        multiply(c1_t{}, p1, now, next);
+        store_rows(rows);
+        p0 = split_plane(v0);
+        interleave(std::integral_constant<int, (48 + 6 * MB - 1) / (6 * MB)>{}, std::integral_constant<int, (2 * LBV + 6 * MB - 1) / (6 * MB)>{});
+        // (nor the split of the first plane behind the branch in load_rows)
+        asm volatile("" ::"v"(__builtin_bit_cast(u32x4, p0.p[0])), "v"(__builtin_bit_cast(u32x4, p0.p[1])), "v"(__builtin_bit_cast(u32x4, p0.p[2])));
+        __builtin_amdgcn_sched_barrier(0);
+        load_rows(rows);
+        __syncthreads();
+        now = next;
+    };
+    if constexpr (!CFG::LOOP) {
+        for (int i = 0; i < C16; ++i) step(now + u_step);
+        finish(here);
+        return;
+    }
+    for (int q = mine;;) {
+        for (int i = 1; i < C16; ++i) step(now + u_step);
+        // the last step of a tile prepares the first one of the next
+        const int qn = q + wgs;
+        const WinosGeom& d = winos_args_again().d;
+        const Place there = qn < count ? place_of(d, qn) : here;
+        if (qn < count) aim_transform(d, there.t0);
+        step(filters_of(there));
+        finish(here);
+        if (qn >= count) break;
+        clear();
+        here = there, q = qn;
+    }
 }
 
 template <class CFG>
@@ -511,21 +636,23 @@ size_t winos_ws_bytes(const Variant&, const conv_desc& d, int, int)
 template <class CFG>
 hipError_t winos_launch(const Variant&, ConvArgs& a, hipStream_t s)
 {
-    const size_t lds = winos_lds_bytes<CFG>(a.N, a.W, a.OH, a.OW);
+    WinosArgs w = {a, winos_geom<CFG>(a.N, a.K, a.W, a.OH, a.OW)};
+    WinosGeom& g = w.d;
+    const size_t lds = winos_lds_bytes<CFG>(g);
     const hipError_t e = ensure_dynamic_lds((const void*)winos_kernel<CFG>, lds);
     if (e != hipSuccess) return e;
-    const WinosGeom g = winos_geom<CFG>(a.N, a.W, a.OH, a.OW);
-    a.dX = make_fastdiv((uint32_t)g.TW);
-    a.dY = make_fastdiv((uint32_t)g.IR);
-    a.dZ = make_fastdiv((uint32_t)g.TH);
-    a.dS = make_fastdiv((uint32_t)g.W4);
-    a.dRS = make_fastdiv((uint32_t)(g.rows_max * g.W4));
+    g.dTW = make_fastdiv((uint32_t)g.TW);
+    g.dIR = make_fastdiv((uint32_t)g.IR);
+    g.dTH = make_fastdiv((uint32_t)g.TH);
+    g.dW4 = make_fastdiv((uint32_t)g.W4);
+    g.dRow = make_fastdiv((uint32_t)(g.rows_max * g.W4));
+    g.dGroup = make_fastdiv((uint32_t)(3 * g.TN));
     hipLaunchKernelGGL(winos_filter_kernel, dim3((unsigned)((a.K + 31) / 32), (unsigned)((a.C + 15) / 16)), dim3(512), 0, s,
                        (const float*)a.filt, (uint4*)a.ws, a.K, a.C);
     const hipError_t e2 = hipGetLastError();
     if (e2 != hipSuccess) return e2;
-    dim3 grid((unsigned)(((g.tiles + CFG::TT - 1) / CFG::TT) * ((a.K + CFG::TM - 1) / CFG::TM)));
-    hipLaunchKernelGGL(winos_kernel<CFG>, grid, dim3(CFG::NT), lds, s, a);
+    const int total = g.TN * g.KT;  // (LOOP: one workgroup per CU, 256 of them)
+    hipLaunchKernelGGL(winos_kernel<CFG>, dim3((unsigned)(CFG::LOOP && total > 256 ? 256 : total)), dim3(CFG::NT), lds, s, w);
     return hipGetLastError();
 }
 
@@ -541,9 +668,9 @@ bool winos_valid(const Variant&, const conv_desc& d, int OH, int OW)
     if (((long long)d.N * d.C + 64) * d.H * d.W * 4 >= lim || (long long)d.N * d.K * OH * OW * 4 >= lim) return false;
     if ((long long)winos_filter_bytes(d.K, d.C) * 2 >= lim || (d.C + 15) / 16 > 65535) return false;
     if ((long long)d.N * ((OH + 1) / 2 + 2) * ((OW + 1) / 2 + 1) >= (1LL << 28)) return false;
-    const WinosGeom g = winos_geom<CFG>(d.N, d.W, OH, OW);
+    const WinosGeom g = winos_geom<CFG>(d.N, d.K, d.W, OH, OW);
     if ((long long)g.rows_max * g.W4 * 16 > CFG::SLOTS) return false;  // every staged vector needs a slot
-    if (winos_lds_bytes<CFG>(d.N, d.W, OH, OW) > 160 * 1024) return false;
+    if (winos_lds_bytes<CFG>(g) > 160 * 1024) return false;
     if ((long long)((d.K + CFG::TM - 1) / CFG::TM) * ((g.tiles + CFG::TT - 1) / CFG::TT) >= lim) return false;
     return true;
 }

@@ -153,6 +153,31 @@ def test_tiles_summed_again(si, kind):
             assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
 
 
+# more tiles than workgroups: 1, 2, 3 and 5 steps a tile, last rounds of some workgroups only, channel tiles and images that change
+# from a workgroup's tile to its next
+LOOPS = [
+    ConvShape(70, 8, 19, 21, 130, 3, 3, 1, 1),
+    ConvShape(33, 24, 28, 28, 100, 3, 3, 1, 0),
+    ConvShape(90, 40, 13, 13, 200, 3, 3, 1, 1),
+    ConvShape(60, 80, 12, 30, 97, 3, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("si", range(len(LOOPS)))
+def test_several_tiles_of_a_workgroup(si):
+    icase = int_case(LOOPS[si], wl.F32, 4370 + si, relu=bool(si % 2), use_bias=si != 1)
+    for vi, name in variants_of(icase):
+        assert_bit_exact(icase, icase.run(variant=vi), name)
+    case = again_case(LOOPS[si], "corners" if si % 2 else "filter")
+    with np.errstate(all="ignore"):
+        ref = case.ref()
+    finite = np.isfinite(ref)
+    for vi, name in variants_of(case):
+        got = to_host_f64(case.run(variant=vi), wl.F32)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
+
+
 # (scale of the inputs, of the filters): parts of one operand below bf16's normal numbers or below its range, the other large
 # enough for ordinary results; both small; subnormal inputs
 SCALES = [(2.0**-120, 2.0**80), (2.0**-124, 2.0**100), (2.0**60, 2.0**-118), (2.0**-140, 2.0**100), (2.0**-60, 2.0**-52), (2.0**-100, 1.0)]
