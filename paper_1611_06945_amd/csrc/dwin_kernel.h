@@ -396,9 +396,12 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void dwin_kernel(ConvArgs a, Dwi
     // One chunk; 2 or more, 1 or no others follow (MORE).  DB: piece by piece between the MFMAs, the next stage's filters and
     // the next chunk's input go to the other buffers and their registers are loaded again for the stage and the chunk after,
     // so that every load has a whole stage or chunk to arrive and the issue of loads (which waits where the memory pipeline is
-    // full) keeps no wave from its MFMAs
-    auto compute = [&](auto more_c, int chunk) {
+    // full) keeps no wave from its MFMAs.  The second chunk's input is requested beneath the FIRST chunk's products, for the same
+    // reason: ahead of them it held the workgroup for 2000 of 23000 clocks (8 images of 33x35x100 -> 130 11.55 -> 11.26 us; over 190 drawn
+    // layers the tiles of 64 and 128 channels take 0.97 to 0.98 of what they took)
+    auto compute = [&](auto more_c, auto first_c, int chunk) {
         constexpr int MORE = decltype(more_c)::value;
+        constexpr bool FIRST = decltype(first_c)::value;
         if constexpr (!CFG::DB) read_slot(std::integral_constant<int, 0>{}, chunk, 0);
         static_for<XSL>([&](auto slot_c) {
             constexpr int k = decltype(slot_c)::value, stage = k / FSL, fs = k % FSL, t = k % FT, cur = k & 1;
@@ -447,7 +450,12 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void dwin_kernel(ConvArgs a, Dwi
                 constexpr int d1 = stage + 1 < NST ? 0 : 1, d2 = stage + 2 < NST ? 0 : NST == 1 ? 2 : 1;  // chunks from here to the next stages
                 constexpr int fat = FSL - 2 - FT / 3, xat = XSL - 2, FN = FSL - 1, XN = XSL - 1;
                 constexpr int f0 = fs == FN ? 0 : NHWC ? fs * FPT / FN : 0, f1 = fs == FN ? 0 : NHWC ? (fs + 1) * FPT / FN : fs == fat ? FPT : 0;
-                constexpr int x0 = k == XN ? 0 : NHWC ? k * XP / XN : 0, x1 = k == XN ? 0 : NHWC ? (k + 1) * XP / XN : k == xat ? XP : 0;
+                // the first chunk's products stand above the requests for the second chunk's input too, in the slots ahead of XL
+                constexpr int XL = FIRST ? (XSL + 2) / 3 : 0, KX = k - XL;
+                constexpr int x0 = k == XN || KX < 0 ? 0 : NHWC ? KX * XP / (XN - XL) : 0;
+                constexpr int x1 = k == XN || KX < 0 ? 0 : NHWC ? (KX + 1) * XP / (XN - XL) : k == xat ? XP : 0;
+                if constexpr (KX < 0 && MORE >= 1)
+                    static_for<(k + 1) * XP / (XL ? XL : 1) - k * XP / (XL ? XL : 1)>([&](auto ic) { load_xi(k * XP / (XL ? XL : 1) + decltype(ic)::value, chunk + 1); });
                 const uint32_t A = A0 + (((uint32_t)(chunk * NST + stage) & 1u) ^ 1u) * AN, B = B0 + (((uint32_t)chunk & 1u) ^ 1u) * BN;
                 static_for<f1 - f0>([&](auto ic) {
                     if constexpr (d1 <= MORE) store_fi(f0 + decltype(ic)::value, chunk + d1, A);
@@ -481,19 +489,25 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void dwin_kernel(ConvArgs a, Dwi
     store_all(0);
     if (tid < TM) bias_s[tid] = bias_r;
     if constexpr (CFG::DB) {
-        if (chunks > 1) static_for<XP>([&](auto ic) { load_xi(decltype(ic)::value, 1); });
         if (chunks * NST > 1) static_for<FPT>([&](auto ic) { load_fi(decltype(ic)::value, NST > 1 ? 0 : 1, NST > 1 ? 1 : 0); });
         __syncthreads();
         read_slot(std::integral_constant<int, 0>{}, 0, 0);
+        constexpr std::true_type first{};
+        constexpr std::false_type later{};
         int chunk = 0;
-        for (; chunk + 2 < chunks; ++chunk) compute(std::integral_constant<int, 2>{}, chunk);
-        if (chunk + 1 < chunks) compute(std::integral_constant<int, 1>{}, chunk++);
-        compute(std::integral_constant<int, 0>{}, chunk);
+        if (chunks > 2) {
+            compute(std::integral_constant<int, 2>{}, first, chunk++);
+            for (; chunk + 2 < chunks; ++chunk) compute(std::integral_constant<int, 2>{}, later, chunk);
+            compute(std::integral_constant<int, 1>{}, later, chunk++);
+        } else if (chunks == 2) {
+            compute(std::integral_constant<int, 1>{}, first, chunk++);
+        }
+        compute(std::integral_constant<int, 0>{}, later, chunk);
     } else {
         if (chunks > 1) load_all(1, 0, 1);
         __syncthreads();
         for (int chunk = 0;;) {
-            compute(std::integral_constant<int, 0>{}, chunk);
+            compute(std::integral_constant<int, 0>{}, std::false_type{}, chunk);
             __syncthreads();
             if (++chunk == chunks) break;
             store_all(chunk);
