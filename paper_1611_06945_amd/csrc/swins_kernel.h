@@ -13,8 +13,8 @@
 //   * Filters are split by a small kernel ahead into the workspace, in MFMA operand order ([step][32-channel block][part][lane]
 //     [8], 1 KB each), and come from L2 straight into registers; the four waves of a workgroup share them in L1.
 // What bounds it: 20 images of 227x227 -> 96 are one round of 240 workgroups of 49000 clocks, 34800 of them the loop (936 MFMAs
-// at 37 clocks, 32 at best), 8000 staging and 5500 stores that nothing covers with one workgroup per CU; 4 us are the filters'
-// launch.  Measured, us per call, best of the other kernels -> this one: 20 of 227x227 -> 96, 11x11 40 -> 34; 20 of 223x223 -> 64, 7x7
+// at 37 clocks, 32 at best), 8000 staging and 5500 stores that nothing covers with one workgroup per CU; 2 us are the filters'
+// launch.  Measured, us per call, best of the other kernels -> this one: 20 of 227x227 -> 96, 11x11 40 -> 32; 20 of 223x223 -> 64, 7x7
 // stride 2, 61 -> 38, 49 of 228x228 146 -> 81.  Where it begins (96 filters of 11x11, images of 227x227; best of the others -> this one): 2 images,
 // 24 tiles of 256 pixels, 14.8 -> 17.8, 3 17.8 -> 17.8, 5 19.3 -> 18.3, 6 23.9 -> 18.6, 10 30.0 -> 26.3, 12 38.7 -> 27.2; 64 filters
 // of 7x7, images of 224x224: 1 image, 49 tiles, 9.6 -> 11.7, 2 12.4 -> 12.2, 4 19.0 -> 15.1.  The selection takes it from there.
@@ -59,21 +59,27 @@ inline SwinsGeom swins_geom(int TN, int R, int ST, int W, int pad, int OH, int O
     return g;
 }
 
-// filters [K][3][R][S] -> U[step][block][part][lane][8], scaled and split
+// filters [K][3][R][S] -> U[step][block][part][lane][8], scaled and split: a wave per block of filters (x) and step (y).
+// One chain of latencies: the eight loads of a lane are requested together (as conditional loads in twenty workgroups of 256 threads
+// they were waited for one by one; call of 20 images of 227x227 -> 96 33.8 -> 32.0 us).
 template <class CFG>
-__global__ __launch_bounds__(256) void swins_filter_kernel(const float* __restrict__ filt, uint4* __restrict__ U, int K, int blocks)
+__global__ __launch_bounds__(64) void swins_filter_kernel(const float* __restrict__ filt, uint4* __restrict__ U, int K)
 {
-    const int u = blockIdx.x * 256 + threadIdx.x, lane = u & 63, b = (u >> 6) % blocks, j = (u >> 6) / blocks;
-    if (j >= CFG::KSTEPS) return;
+    const int lane = threadIdx.x, b = blockIdx.x, j = blockIdx.y, blocks = gridDim.x;
     const int k = b * 32 + (lane & 31), h = lane >> 5;
+    constexpr uint32_t row = CFG::C * CFG::R * CFG::S * 4;
+    const __amdgpu_buffer_rsrc_t rf = make_rsrc(filt, (uint32_t)K * row);
     float x[8];
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
         const int i2 = 2 * j + g, t = i2 / CFG::SQ, sq = i2 - t * CFG::SQ, line = 2 * t + h, r = line / CFG::C, c = line - r * CFG::C;
-        const float* src = filt + ((size_t)(k * CFG::C + c) * CFG::R + r) * CFG::S + 4 * sq;
+        const uint32_t off = (uint32_t)k * row + (uint32_t)((c * CFG::R + r) * CFG::S + 4 * sq) * 4u;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[4 * g + e] = k < K && line < CFG::NROW && 4 * sq + e < CFG::S ? src[e] * kSplitScale : 0.0f;
+        for (int e = 0; e < 4; ++e)
+            x[4 * g + e] = buffer_load_elem<float>(rf, k < K && line < CFG::NROW && 4 * sq + e < CFG::S ? off + e * 4u : kOutOfRange);
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] *= kSplitScale;
     const Split3 s = split3(x);
     uint4* dst = U + ((size_t)(j * blocks + b) * 3) * 64 + lane;
 #pragma unroll
@@ -414,8 +420,7 @@ hipError_t swins_launch(const Variant&, ConvArgs& a, hipStream_t s)
     const hipError_t e = ensure_dynamic_lds((const void*)swins_kernel<CFG>, swins_lds(g));
     if (e != hipSuccess) return e;
     const int blocks = (a.K + 31) / 32;
-    hipLaunchKernelGGL(swins_filter_kernel<CFG>, dim3((unsigned)((CFG::KSTEPS * blocks * 64 + 255) / 256)), dim3(256), 0, s, (const float*)a.filt,
-                       (uint4*)a.ws, a.K, blocks);
+    hipLaunchKernelGGL(swins_filter_kernel<CFG>, dim3((unsigned)blocks, (unsigned)CFG::KSTEPS), dim3(64), 0, s, (const float*)a.filt, (uint4*)a.ws, a.K);
     g.dT = make_fastdiv((uint32_t)g.tpi);
     hipLaunchKernelGGL(swins_kernel<CFG>, dim3((unsigned)(a.N * g.tpi), (unsigned)((a.K + CFG::TM - 1) / CFG::TM)), dim3(CFG::NT), swins_lds(g), s, a, g);
     return hipGetLastError();
