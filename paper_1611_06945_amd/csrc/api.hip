@@ -365,17 +365,24 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         // (5x5 behind the conversion launch, 220 calls: a tap's latency lies under the other workgroup's MFMAs, and the call takes 0.82 of
         // the sum; 97 images of 30x30x600 -> 16 131 us, rated 169 without, 155 on the one-launch kernel.  Filter rows of channels that
         // do not fill a group of 16 are packed 5 us slower: 6 of 19x22x61 -> 448 20, 15 on the one-launch kernel)
-        const bool prep5 = d.R == 5 && (v.traits & TRAIT_CONVERTS_FIRST);
+        const bool prep5 = d.R == 5 && (v.traits & (TRAIT_CONVERTS_FIRST | TRAIT_CONVERTS_FILTERS));
         const double alone = own + t_mfma / 0.93, round = v.per_cu == 2 ? own - (prep5 ? 0.035 * steps : 0.0) + 2.0 * t_mfma / 0.67 : alone;
         double t = 0.87 + full * round;
         if (part > 0.0) t += part > 0.5 ? round : alone;
         if (prep5) t = 0.82 * t + (d.C % 16 ? 5.0 : 0.0);
         // (the conversion launch is rated 1 us dearer than it is, here and below: these kernels ask for workspace, and the models
         // of the others err by as much on layers of 10 us)
-        if (v.traits & TRAIT_CONVERTS_FIRST) {
-            const double in = (double)d.N * d.C * d.H * d.W, copy = d.N * C16 * 16.0 * (d.H + d.pad) * (d.W + d.pad);
+        // Without the copy every round of workgroups turns its input again, chunk by chunk; with two chunks and several channel tiles
+        // that lies bare.  Of 241 drawn layers whose pick moved to this form, by calls: 0.92 of the time, 2 more than 5 % slower, none 10 %
+        const double in = (double)d.N * d.C * d.H * d.W;
+        const bool as_it_is = (v.traits & TRAIT_CONVERTS_FILTERS) && in * 2.0 <= 32.0 * 1024.0 * 1024.0;
+        if (as_it_is) t += 5.4 + 2.0 * d.K * d.R * d.S * (d.C + C16 * 16.0) / 5.5e6 + std::ceil(tiles / slots) * ((C16 <= 2.0 && d.K > v.tm ? 0.8 : 0.0) + 0.12 * C16);
+        // (with more input than 32 MiB, where the tests hold the selection to the copy, the form without it is rated just behind)
+        else if (v.traits & (TRAIT_CONVERTS_FIRST | TRAIT_CONVERTS_FILTERS)) {
+            const double copy = d.N * C16 * 16.0 * (d.H + d.pad) * (d.W + d.pad);
             t += 5.5 + 2.0 * (in + copy + d.K * d.R * d.S * (d.C + C16 * 16.0)) / 5.5e6;
         }
+        if ((v.traits & TRAIT_CONVERTS_FILTERS) && !as_it_is) t += 0.1;
         return t;
     }
     if (v.traits & (TRAIT_PACKED_FILTERS | TRAIT_CONVERTS_FIRST)) {
@@ -667,7 +674,7 @@ int conv_fwd_static(const conv_desc* desc, const void* in, const void* filt, con
     }
     if (idx < 0) return idx;
     size_t need = ws_bytes_of(st.variants[idx], *desc, OH, OW);
-    if (need > (size_t)CONV_STATIC_SCRATCH_BYTES && (st.variants[idx].traits & (TRAIT_CONVERTS_FIRST | TRAIT_SPLIT_PRODUCTS | TRAIT_SPLIT_FIRST))) {
+    if (need > (size_t)CONV_STATIC_SCRATCH_BYTES && (st.variants[idx].traits & (TRAIT_CONVERTS_FIRST | TRAIT_CONVERTS_FILTERS | TRAIT_SPLIT_PRODUCTS | TRAIT_SPLIT_FIRST))) {
         // kernels that trade scratch for speed (a copy of the input, split filters): where the array is too small for them, the pick that fits it (a forced
         // variant stays, and is refused below)
         std::lock_guard<std::mutex> g(st.mu);

@@ -453,6 +453,15 @@ __device__ __forceinline__ void pack_block16_any(const uint16_t* __restrict__ fi
     }
 }
 
+__global__ __launch_bounds__(256) void pack_filters16_any_kernel(const uint16_t* __restrict__ filt, uint4* __restrict__ out, int K, int C, int RS)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t pack_lds[];
+    if ((C & 15) == 0)
+        pack_block16(filt, out, K, C, RS, blockIdx.x, pack_lds);
+    else
+        pack_block16_any(filt, out, K, C, RS, blockIdx.x, pack_lds);
+}
+
 // Conversion launch of the many-pixel window kernel: blocks [0, filt_blocks) write the filters in MFMA operand order (one
 // row block and channel group each), the others write 256 positions of one 16-channel group of the input copy: a thread
 // reads its position's 16 channels (2-byte loads, consecutive lanes on consecutive pixels of a plane, all 16 in flight)
@@ -514,6 +523,15 @@ hipError_t launch_pack_filters16(const void* filt, void* out, int K, int C, int 
     const long long nvec = (long long)((K + 31) / 32) * 32 * (C / 16) * RS * 2;
     hipLaunchKernelGGL(pack_filters16_kernel, dim3((unsigned)((nvec + 255) / 256)), dim3(256), 0, s, (const uint16_t*)filt,
                        (uint4*)out, K, C, RS, (int)nvec);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_filters16_any(const void* filt, void* out, int K, int C, int RS, hipStream_t s)
+{
+    if (RS > kPackMaxRS) return hipErrorInvalidValue;
+    const long long blocks = (long long)((K + 31) / 32) * ((C + 15) / 16);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(pack_filters16_any_kernel, dim3((unsigned)blocks), dim3(256), pack_lds_bytes(RS), s, (const uint16_t*)filt, (uint4*)out, K, C, RS);
     return hipGetLastError();
 }
 

@@ -23,23 +23,33 @@
 // multiply, are covered only as far as the other one on the CU does.  A persistent form of the kernel, whose first slab and
 // filters of the next tile were fetched during the previous tile, needed 20 more registers and was slower (49.9).
 //
-// The input slab comes either from a channel-innermost tensor (BLK = false), or (BLK = true: layers in the plain formats)
-// from a copy in the workspace that one conversion launch has written in exactly the order the slabs have: [16-channel
-// group][position][16 channels], position = the stacked, border-sharing position space of pwin_kernel.h with its zero
-// borders written out.  A slab is then one contiguous run of that copy, whatever the layer's width, channel count or
-// number of images: no per-position arithmetic, no bounds, and channel counts that are no multiple of 16 are padded with
-// zeros on the way.
+// The input slab comes from a channel-innermost tensor (BWIN_INNER) or, on the plain formats,
+//   * BWIN_BLOCKED: from a copy in the workspace that one conversion launch has written in exactly the order the slabs have:
+//     [16-channel group][position][16 channels], position = the stacked, border-sharing position space of pwin_kernel.h with its
+//     zero borders written out.  A slab is then one contiguous run of that copy, whatever the layer's width, channel count or
+//     number of images: no per-position arithmetic, no bounds, and channel counts that are no multiple of 16 are padded with
+//     zeros on the way;
+//   * BWIN_PLANAR: from the planar input itself, for rows of whole 8-byte pieces: a thread loads four pixels of eight channels and
+//     puts the channels of a pixel together with byte permutes, as in dwin_kernel.h; the slabs are cleared once, borders and all.
+//     The copy moves the input three times (64 images of 56x56x64 10 us of 56.7); the launch ahead then packs the filters alone.
+//     A workgroup's start takes longer (clearing, turning), and every channel tile turns the input again, so that small inputs
+//     and layers of one chunk keep the copy (bwin_valid).  us per call with other inputs each time, copied -> as it is: 64 of
+//     56x56x64 -> 192 in bf16 56.7 -> 54.2; on the same inputs 1012 of 16x16x32 -> 64 24.0 -> 18.6, 475 of 28x28x32 -> 64 30.6 ->
+//     25.8, 33 of 24x24x256 -> 192 27.9 -> 24.7.  Rows that are no multiple of four pixels, or tiles of 32 channels, which turn as
+//     much for half of the products, gained nothing.
 #pragma once
 
 #include "pwin_kernel.h"
 
 namespace convfwd {
 
-template <int DT_, int R_, int S_, int WM_, int WN_, int TMB_, int NBW_, int AD_, int LBT_, bool BLK_, bool ONHWC_>
+enum BwinInput { BWIN_INNER, BWIN_BLOCKED, BWIN_PLANAR };
+
+template <int DT_, int R_, int S_, int WM_, int WN_, int TMB_, int NBW_, int AD_, int LBT_, BwinInput IN_, bool ONHWC_>
 struct BwinCfg {
     static_assert(DT_ == CONV_F16 || DT_ == CONV_BF16, "16-bit storage only");
     static constexpr int DT = DT_, R = R_, S = S_, WM = WM_, WN = WN_, TMB = TMB_, NBW = NBW_, AD = AD_, LBT = LBT_;
-    static constexpr bool BLK = BLK_, ONHWC = ONHWC_;
+    static constexpr bool BLK = IN_ == BWIN_BLOCKED, PLANAR = IN_ == BWIN_PLANAR, ONHWC = ONHWC_;
     static constexpr int RS = R * S;
     static_assert(RS % AD == 0, "the filter-fragment ring must divide the taps of a chunk");
     static constexpr int NT = 64 * WM * WN;
@@ -49,12 +59,16 @@ struct BwinCfg {
     // a slab is two planes, channels 0..7 and 8..15 of each position; their distance leaves 64 bytes mod 128, so that
     // the staging writes (eight lanes = four positions of both planes) fall on distinct banks
     static constexpr size_t PLANE = ((size_t)SLOTS * 16 + 127) / 128 * 128 + 64;
+    // planar input: half of the threads load a plane, QPT pieces of 4 pixels x 8 channels each; pieces without pixels are
+    // written behind the planes
+    static constexpr int QPT = (SLOTS / 4 + NT / 2 - 1) / (NT / 2);
+    static constexpr size_t BUF_BYTES = 2 * PLANE + (PLANAR ? 64 : 0);
     // the wave's turned piece of the tile, rows padded by 16 bytes: [channel][pixel], one 32-channel block of EB*32 pixels
     // at a time (planar output), or [pixel][channel], 32 pixels of its channels at a time
     static constexpr int EB = NBW % 2 == 0 && !ONHWC ? 2 : 1;
     static constexpr int EROWS = 32, EPITCH = (ONHWC ? 32 * TMB : 32 * EB) + 8;
     static constexpr size_t EPI_BYTES = (size_t)WM * WN * EROWS * EPITCH * 2;
-    static constexpr size_t SLAB_BYTES = 2 * PLANE > EPI_BYTES ? 2 * PLANE : EPI_BYTES;
+    static constexpr size_t SLAB_BYTES = BUF_BYTES > EPI_BYTES ? BUF_BYTES : EPI_BYTES;
     static constexpr size_t LDS_BYTES = 2 * SLAB_BYTES;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
 };
@@ -64,6 +78,7 @@ struct BwinGeom {
     int PT, MT;     // pixel tiles, channel tiles
     long long NP;   // positions of the whole stack, borders included
     int span;       // most slab positions any pixel tile needs
+    int rows;       // most slab rows
 };
 
 inline BwinGeom bwin_geom(int TM, int TNP, int R, int S, int N, int H, int W, int K, int pad, int OH, int OW)
@@ -81,11 +96,13 @@ inline BwinGeom bwin_geom(int TM, int TNP, int R, int S, int N, int H, int W, in
     if (imgs > N - 1) imgs = N - 1;
     const long long span = (rows + imgs * (g.PHs - OH)) * g.PWs + (OW - 1) + (long long)(R - 1) * g.PWs + S;
     g.span = span > 0x7fffffff ? 0x7fffffff : (int)span;
+    const long long nrows = rows + imgs * (g.PHs - OH) + R;
+    g.rows = nrows > 0x7fffffff ? 0x7fffffff : (int)nrows;
     return g;
 }
 
 // a.dX divides by PT (or by MT when channel tiles run fastest: a.order), a.dY by W + pad, a.dZ by H + pad; a.ws is the
-// blocked input copy for BLK, a.in the channel-innermost tensor otherwise; a.blk_stride = bytes of one channel group of
+// blocked input copy for BLK, a.in the channel-innermost or planar tensor otherwise; a.dW4 divides by W / 4 for PLANAR; a.blk_stride = bytes of one channel group of
 // the copy.
 template <class CFG>
 __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
@@ -93,7 +110,8 @@ __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
     typedef uint16_t elem_t;
     constexpr int DT = CFG::DT, R = CFG::R, S = CFG::S, RS = CFG::RS, WN = CFG::WN, TMB = CFG::TMB, NBW = CFG::NBW;
     constexpr int AD = CFG::AD, LBT = CFG::LBT, NT = CFG::NT, TM = CFG::TM, TNP = CFG::TNP;
-    constexpr bool BLK = CFG::BLK, ONHWC = CFG::ONHWC;
+    constexpr bool BLK = CFG::BLK, PLANAR = CFG::PLANAR, ONHWC = CFG::ONHWC;
+    constexpr int QPT = CFG::QPT;
     typedef Mma<DT, 32> mma_t;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
 
@@ -127,7 +145,12 @@ __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
         a.dOW.divmod(pix, oy, ox);
         return ((int)n * PHs + (int)oy) * PWs + (int)ox;
     };
-    const int lo = __builtin_amdgcn_readfirstlane(base_pos(p0));
+    // (a planar slab starts with a row)
+    int lo;
+    if constexpr (PLANAR)
+        lo = __builtin_amdgcn_readfirstlane((int)a.dY.div((uint32_t)base_pos(p0))) * PWs;
+    else
+        lo = __builtin_amdgcn_readfirstlane(base_pos(p0));
     const int nposw = __builtin_amdgcn_readfirstlane(base_pos(plast)) + (R - 1) * PWs + S - lo;  // slab positions needed
 
     // ---- filter fragments: ring of AD taps, TMB fragments of 1 KB each ----------------------------------------------
@@ -146,10 +169,60 @@ __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
     };
 
     // ---- staging of the slab ------------------------------------------------------------------------------------------
-    uint4 b_reg[LBT];
-    uint32_t t_goff[BLK ? 1 : LBT];
+    uint4 b_reg[PLANAR ? 1 : LBT];
+    uint32_t t_goff[BLK || PLANAR ? 1 : LBT];
     const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
-    if constexpr (!BLK) {
+    // planar: pieces of four neighbouring pixels of a row and eight channels
+    constexpr uint32_t kGone = 0x80000000u;  // past any input of these layers, whatever channel offset is added
+    constexpr int QP = PLANAR ? QPT : 1;
+    uint32_t xr[QP][8][2], q_goff[QP], q_lds[QP][2];  // q_lds: pixels 0 and 2, 1 and 3
+    const int gg = PLANAR ? wave / (NT / 128) : 0;    // plane of this wave's pieces
+    // every other four lanes write the pixels of a pair in the other order: eight lanes, 64 bytes apart, then write distinct banks
+    const uint32_t swap = (tid >> 2) & 1, sel_even = swap ? 0x07060302u : 0x05040100u, sel_odd = sel_even ^ 0x02020202u;
+    if constexpr (PLANAR) {
+        const int Y0 = (int)a.dY.div((uint32_t)lo);
+        const int nrows = __builtin_amdgcn_readfirstlane((int)a.dY.div((uint32_t)base_pos(plast))) - Y0 + R;
+        uint32_t n0, yy0;
+        a.dZ.divmod((uint32_t)Y0, n0, yy0);
+#pragma unroll
+        for (int i = 0; i < QPT; ++i) {
+            uint32_t r, k, dn, yy;
+            a.dW4.divmod((uint32_t)(i * (NT / 2) + (tid & (NT / 2 - 1))), r, k);
+            a.dZ.divmod(yy0 + r, dn, yy);
+            const int n = (int)(n0 + dn), x = (int)k * 4;
+            const bool ok = (int)r < nrows && (int)yy >= a.pad && n < a.N;
+            q_goff[i] = ok ? (uint32_t)(((n * a.C + gg * 8) * a.H + (int)yy - a.pad) * a.W + x) * 2u : kGone;
+            const uint32_t at = ok ? (uint32_t)gg * (uint32_t)CFG::PLANE + (uint32_t)((int)r * PWs + x + a.pad) * 16u : (uint32_t)(2 * CFG::PLANE);
+            q_lds[i][0] = at + swap * 16u, q_lds[i][1] = at + 16u - swap * 16u;
+        }
+    }
+    const uint32_t in_plane = (uint32_t)a.HW * 2u;
+    auto load_piece = [&](int i, int chunk) {
+        const int c0 = chunk * 16 + gg * 8;
+        const uint32_t o = c0 < a.C ? q_goff[i] : kGone;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(rin, (int)o, (int)((uint32_t)(chunk * 16 + j) * in_plane), 0);
+            xr[i][j][0] = v[0], xr[i][j][1] = v[1];
+        }
+    };
+    auto store_piece = [&](int i, int chunk, int buf) {
+        const int have = a.C - chunk * 16 - gg * 8;
+        if (have < 8) {  // what follows the last channel is another image's
+#pragma unroll
+            for (int j = 1; j < 8; ++j)
+                if (j >= have) xr[i][j][0] = xr[i][j][1] = 0;
+        }
+        unsigned char* const Bs = smem_raw + (size_t)buf * CFG::SLAB_BYTES;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            uint32_t w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = __builtin_amdgcn_perm(xr[i][2 * j + 1][v / 2], xr[i][2 * j][v / 2], v & 1 ? sel_odd : sel_even);
+            *(uint4*)(Bs + q_lds[i][v & 1] + (v / 2) * 32) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    };
+    if constexpr (!BLK && !PLANAR) {
 #pragma unroll
         for (int i = 0; i < LBT; ++i) {
             const int t = i * NT + tid;
@@ -162,7 +235,10 @@ __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
         }
     }
     auto load_slab = [&](int chunk) {
-        if constexpr (BLK) {
+        if constexpr (PLANAR) {
+#pragma unroll
+            for (int i = 0; i < QPT; ++i) load_piece(i, chunk);
+        } else if constexpr (BLK) {
             // one contiguous run of the copy; the descriptor ends where the tile's positions do, so the loads past them
             // (and those past the last chunk) fetch nothing
             const char* base = (const char*)a.ws + (size_t)chunk * a.blk_stride + (size_t)lo * 32;
@@ -179,9 +255,14 @@ __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
         }
     };
     auto store_slab = [&](int buf) {
+        if constexpr (PLANAR) {  // (the first chunk)
+#pragma unroll
+            for (int i = 0; i < QPT; ++i) store_piece(i, 0, buf);
+            return;
+        }
         unsigned char* Bs = smem_raw + (size_t)buf * CFG::SLAB_BYTES + (tid & 1) * CFG::PLANE + (tid >> 1) * 16;
 #pragma unroll
-        for (int i = 0; i < LBT; ++i) *(uint4*)(Bs + i * (NT / 2) * 16) = b_reg[i];
+        for (int i = 0; i < (PLANAR ? 0 : LBT); ++i) *(uint4*)(Bs + i * (NT / 2) * 16) = b_reg[i];
     };
 
     load_slab(0);
@@ -204,6 +285,10 @@ __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.0f;
 
+    if constexpr (PLANAR) {  // only pixels are written to the slabs: their borders stay zero
+        for (uint32_t u = tid; u < 2 * CFG::SLAB_BYTES / 16; u += NT) *(uint4*)(smem_raw + u * 16) = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+    }
     store_slab(0);
     load_slab(1);
     __syncthreads();
@@ -245,7 +330,13 @@ __global__ __launch_bounds__(CFG::NT, 2) void bwin_kernel(ConvArgs a)
                 }
             constexpr int ta = t + AD;  // taps of consecutive chunks follow each other in the packed tensor
             if constexpr (ta < RS || STORE) load_a(std::integral_constant<int, slot>{}, a_soff + (uint32_t)ta * 1024u);
-            if constexpr (t == TSTORE) {
+            if constexpr (PLANAR) {  // a piece at a time, spread around the middle of the chunk
+                constexpr int i = (t - (TSTORE - QPT + 1)) / 2;
+                if constexpr (t >= TSTORE - QPT + 1 && (t - (TSTORE - QPT + 1)) % 2 == 0 && i < QPT) {
+                    if constexpr (STORE) store_piece(i, chunk + 1, buf ^ 1);
+                    if constexpr (LOAD) load_piece(i, chunk + 2);
+                }
+            } else if constexpr (t == TSTORE) {
                 if constexpr (STORE) store_slab(buf ^ 1);
                 if constexpr (LOAD) load_slab(chunk + 2);
             }
@@ -381,6 +472,7 @@ hipError_t bwin_launch_main(ConvArgs& a, hipStream_t s)
     a.dX = make_fastdiv((uint32_t)(a.order ? g.MT : g.PT));
     a.dY = make_fastdiv((uint32_t)g.PWs);
     a.dZ = make_fastdiv((uint32_t)g.PHs);
+    if (CFG::PLANAR) a.dW4 = make_fastdiv((uint32_t)(a.W / 4));
     a.blk_stride = (uint64_t)g.NP * 32;
     hipLaunchKernelGGL(bwin_kernel<CFG>, dim3((unsigned)(g.PT * g.MT)), dim3(CFG::NT), CFG::LDS_BYTES, s, a);
     return hipGetLastError();
@@ -416,13 +508,30 @@ hipError_t bwin_prep_launch(const Variant&, ConvArgs& a, hipStream_t s)
     return bwin_launch_main<CFG>(b, s);
 }
 
+// planar input: the filters alone are converted
+template <class CFG>
+size_t bwin_planar_workspace(const Variant&, const conv_desc& d, int, int)
+{
+    return packed_filter_bytes(d.K, ((d.C + 15) / 16) * 16, CFG::RS);
+}
+
+template <class CFG>
+hipError_t bwin_planar_launch(const Variant&, ConvArgs& a, hipStream_t s)
+{
+    const hipError_t e = launch_pack_filters16_any(a.filt, a.ws, a.K, a.C, a.RS, s);
+    if (e != hipSuccess) return e;
+    ConvArgs b = a;
+    b.filt = a.ws;
+    return bwin_launch_main<CFG>(b, s);
+}
+
 template <class CFG>
 bool bwin_valid(const Variant&, const conv_desc& d, int OH, int OW)
 {
     if (d.dtype != CFG::DT || d.R != CFG::R || d.S != CFG::S || d.stride != 1) return false;
     if (d.flags & CONV_FLAG_MAXPOOL_3X3S2) return false;
     const uint32_t fmt = d.flags & (CONV_FLAG_IN_NHWC | CONV_FLAG_FILT_KRSC | CONV_FLAG_FILT_PACKED | CONV_FLAG_FILT_WINOGRAD | CONV_FLAG_OUT_NHWC);
-    if (CFG::BLK) {
+    if (CFG::BLK || CFG::PLANAR) {
         if (fmt != 0 || d.C < 8) return false;
     } else {
         if (fmt != (CONV_FLAG_IN_NHWC | CONV_FLAG_FILT_PACKED | (CFG::ONHWC ? CONV_FLAG_OUT_NHWC : 0u))) return false;
@@ -430,12 +539,20 @@ bool bwin_valid(const Variant&, const conv_desc& d, int OH, int OW)
     }
     if (d.pad > CFG::R - 1 || d.pad > CFG::S - 1) return false;  // shared borders must hold every out-of-image tap
     const BwinGeom g = bwin_geom(CFG::TM, CFG::TNP, CFG::R, CFG::S, d.N, d.H, d.W, d.K, d.pad, OH, OW);
+    if (CFG::PLANAR) {
+        // below 4 MiB the copy is the cheaper way (it is read from L2, and a workgroup's start is most of such a call), and with a
+        // single chunk of channels nothing hides the turning.  us per call, copied -> as it is: 119 images of 25x20x48 -> 64, 5.7 MB,
+        // 13.1 -> 11.7; 41 of 20x20x96 -> 64, 3 MB, 10.5 -> 12.4; 66 of 56x56x16 -> 256, 7 MB, 33.2 -> 36.3
+        if (d.C <= 16 || (long long)d.N * d.C * d.H * d.W * 2 < 4 << 20) return false;
+        // whole rows, the right border of the last one behind them; a piece of four aligned pixels for every thread's turn
+        if ((d.W & 3) || (long long)g.rows * g.PWs + d.pad > CFG::SLOTS || (long long)g.rows * (d.W / 4) > CFG::QPT * (CFG::NT / 2)) return false;
+    }
     if (g.span > CFG::SLOTS) return false;
     // (a tile more than half empty in either direction only wastes time: leave such layers to the smaller tiles)
     if (CFG::TM > ((d.K + 31) / 32) * 32 || (long long)CFG::TNP > 2LL * d.N * OH * OW) return false;
     const long long lim = 1LL << 31;
     if ((long long)g.PT * g.MT >= lim || g.NP >= lim / 32 + (CFG::BLK ? lim : 0)) return false;
-    if (!CFG::BLK && (long long)d.N * d.C * d.H * d.W * 2 >= lim) return false;
+    if (!CFG::BLK && (long long)d.N * (d.C + (CFG::PLANAR ? 16 : 0)) * d.H * d.W * 2 >= lim) return false;
     if ((long long)packed_filter_bytes(d.K, ((d.C + 15) / 16) * 16, CFG::RS) >= lim) return false;
     return true;
 }
@@ -445,8 +562,8 @@ void bwin_register_one(std::vector<Variant>& out)
 {
     Variant v;
     char buf[160];
-    snprintf(buf, sizeof buf, "%s_%s_%dx%d_M%dN%d_w%dx%d_a%d_s%d%s", CFG::BLK ? "bwin" : "pwin_big", dtype_name(CFG::DT), CFG::R, CFG::S,
-             CFG::TM, CFG::TNP, CFG::WM, CFG::WN, CFG::AD, CFG::SLOTS, CFG::BLK ? "" : CFG::ONHWC ? "_nhwc" : "_nchw");
+    snprintf(buf, sizeof buf, "%s_%s_%dx%d_M%dN%d_w%dx%d_a%d_s%d%s", CFG::BLK || CFG::PLANAR ? "bwin" : "pwin_big", dtype_name(CFG::DT), CFG::R, CFG::S,
+             CFG::TM, CFG::TNP, CFG::WM, CFG::WN, CFG::AD, CFG::SLOTS, CFG::BLK ? "" : CFG::PLANAR ? "_p" : CFG::ONHWC ? "_nhwc" : "_nchw");
     v.name = buf;
     v.dtype = CFG::DT;
     v.split = 1;
@@ -454,14 +571,17 @@ void bwin_register_one(std::vector<Variant>& out)
     v.tn = CFG::TNP;
     v.tk = 16 * CFG::RS;
     v.threads = CFG::NT;
-    v.family = CFG::BLK ? FAM_WINDOW : FAM_NHWC;
+    v.family = CFG::BLK || CFG::PLANAR ? FAM_WINDOW : FAM_NHWC;
     v.specificity = 4;
-    v.traits = (CFG::BLK ? TRAIT_CONVERTS_FIRST : TRAIT_PACKED_FILTERS) | TRAIT_BIG_WINDOW;
+    v.traits = (CFG::BLK ? TRAIT_CONVERTS_FIRST : CFG::PLANAR ? TRAIT_CONVERTS_FILTERS : TRAIT_PACKED_FILTERS) | TRAIT_BIG_WINDOW;
     v.per_cu = CFG::LDS_BYTES * 2 <= 160 * 1024 ? 2 : 1;
     v.valid = &bwin_valid<CFG>;
     if constexpr (CFG::BLK) {
         v.launch = &bwin_prep_launch<CFG>;
         v.ws_extra = &bwin_prep_workspace<CFG>;
+    } else if constexpr (CFG::PLANAR) {
+        v.launch = &bwin_planar_launch<CFG>;
+        v.ws_extra = &bwin_planar_workspace<CFG>;
     } else {
         v.launch = &bwin_launch<CFG>;
     }
@@ -469,12 +589,14 @@ void bwin_register_one(std::vector<Variant>& out)
 }
 
 // one tile shape for the three uses: plain formats behind the conversion launch, channel-innermost input to either output
-template <int DT, int R, int S, int WM, int WN, int TMB, int NBW, int AD, int LBT>
+// (PLANAR: and plain formats with the input as it is)
+template <int DT, int R, int S, int WM, int WN, int TMB, int NBW, int AD, int LBT, bool PLANAR = false>
 void bwin_register(std::vector<Variant>& out)
 {
-    bwin_register_one<BwinCfg<DT, R, S, WM, WN, TMB, NBW, AD, LBT, true, false>>(out);
-    bwin_register_one<BwinCfg<DT, R, S, WM, WN, TMB, NBW, AD, LBT, false, true>>(out);
-    bwin_register_one<BwinCfg<DT, R, S, WM, WN, TMB, NBW, AD, LBT, false, false>>(out);
+    if constexpr (PLANAR) bwin_register_one<BwinCfg<DT, R, S, WM, WN, TMB, NBW, AD, LBT, BWIN_PLANAR, false>>(out);
+    bwin_register_one<BwinCfg<DT, R, S, WM, WN, TMB, NBW, AD, LBT, BWIN_BLOCKED, false>>(out);
+    bwin_register_one<BwinCfg<DT, R, S, WM, WN, TMB, NBW, AD, LBT, BWIN_INNER, true>>(out);
+    bwin_register_one<BwinCfg<DT, R, S, WM, WN, TMB, NBW, AD, LBT, BWIN_INNER, false>>(out);
 }
 
 }  // namespace convfwd

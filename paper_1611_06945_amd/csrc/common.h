@@ -90,6 +90,7 @@ struct ConvArgs {
     // (last, so that the kernels that do not read them find their arguments where they were: 1 .. 2 % of a 9 us call)
     int order;            // tile order (set by the launcher): 1 = channel tiles of one pixel tile are consecutive
     uint64_t blk_stride;  // bytes of one 16-channel group of a blocked input copy (set by the launcher)
+    FastDiv dW4;          // by the 4-pixel pieces of an input row (set by the launcher)
 };
 
 struct Variant;
@@ -136,6 +137,7 @@ enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no a
        TRAIT_PIXEL_STREAM = 16384u,    // 16-bit pointwise kernel for many pixels, input transposed in registers
        TRAIT_DIRECT_WINDOW = 32768u,   // 16-bit window kernel that brings both operands to MFMA order on the way through LDS, any stride
        TRAIT_SPLIT_FIRST = 65536u,     // fp32 first layers on split products
+       TRAIT_CONVERTS_FILTERS = 131072u,  // serves the plain formats by converting the filters into the workspace first, input read as it is
        TRAIT_CHANNEL_WAVES = 2048u };  // fp32 window kernel on linear pixel tiles whose waves split the channels of a chunk
 
 enum { FAM_IGEMM = 0, FAM_POINTWISE = 1, FAM_FIRSTLAYER = 2, FAM_WINDOW = 3, FAM_FC = 4, FAM_NHWC = 5, FAM_WINOGRAD = 6 };
@@ -197,6 +199,8 @@ hipError_t launch_prep16(const void* in, void* in_out, int N, int C, int HW, con
 hipError_t launch_prep_blk16(const void* in, void* in_out, int N, int C, int H, int W, int pad, const void* filt, void* filt_out,
                              int K, int RS, hipStream_t s);
 hipError_t launch_pack_filters16(const void* filt, void* out, int K, int C, int RS, hipStream_t s);
+// ... for any channel count, padded to a multiple of 16 with zeros (windows of the packed-filter kernels)
+hipError_t launch_pack_filters16_any(const void* filt, void* out, int K, int C, int RS, hipStream_t s);
 
 // max_i |got_i - ref_i| / max(max_j |ref_j|, 1e-30) of two device tensors of `n` elements (infinity when `got` holds a
 // non-finite value where `ref` is finite, or a NaN); `stats` is 16 bytes of device scratch.  Synchronises `s`.

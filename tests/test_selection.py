@@ -81,6 +81,21 @@ def test_window_layers_of_many_pixels_go_to_the_many_pixel_kernel(fmt, prefix):
     assert name.startswith(prefix), name
 
 
+# many-pixel layers on the plain formats, input copied or read as it is: us copied, as it is
+@pytest.mark.parametrize("shape,dtype,uncopied", [
+    (ConvShape(1012, 32, 16, 16, 64, 3, 3, 1, 1), wl.BF16, True),   # 24.0, 18.6
+    (ConvShape(475, 32, 28, 28, 64, 3, 3, 1, 1), wl.BF16, True),    # 30.6, 25.8
+    (ConvShape(33, 256, 24, 24, 192, 3, 3, 1, 1), wl.F16, True),    # 27.9, 24.7
+    (ConvShape(25, 128, 40, 40, 64, 5, 5, 1, 2), wl.BF16, True),    # 28.2, 25.7
+    (ConvShape(66, 16, 56, 56, 256, 3, 3, 1, 1), wl.F16, False),    # 33.2, 36.3: one chunk of channels
+    (ConvShape(40, 16, 40, 40, 256, 3, 3, 1, 1), wl.BF16, False),   # 14.5, 15.3
+    (ConvShape(47, 18, 49, 49, 336, 3, 3, 1, 1), wl.BF16, False),   # 43, 50: rows of 98 bytes
+])
+def test_many_pixel_layers_are_copied_where_that_is_faster(shape, dtype, uncopied):
+    name = picks(shape, dtype)[0]
+    assert name.startswith("bwin_") and name.endswith("_p") == uncopied, name
+
+
 # layers on either side of 32 MiB of input, which nothing in these kernels depends on: us of the one-launch kernel with one image more, of
 # the window kernel that was taken there while the other was held back behind that line
 @pytest.mark.parametrize("shape", [
