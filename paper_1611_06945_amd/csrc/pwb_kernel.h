@@ -9,10 +9,12 @@
 //     barrier every wave runs alone, GD groups of 16 channels of input in flight.
 //   * All channels of a tile belong to one wave, so every input value is loaded once per 32*TMB output channels.
 //   * A lane ends with NPX neighbouring pixels of each channel: stores of 4 or 8 bytes, runs of 128 or 256 bytes.
-// Measured: 64 images of 28x28x256 -> 128 in fp16 (38.5 MB) 12.1 us = 3.2 TB/s, of the 4.7 a large copy reaches, with 64 x 512
+//   * Biases come from LDS: loaded between the stores they were waited for until the stores ahead of them were done, eight times a
+//     wave; a thread's filter vectors are stepped, not divided for (both: 12.2 -> 11.5 us).
+// Measured: 64 images of 28x28x256 -> 128 in fp16 (38.5 MB) 11.5 us = 3.3 TB/s, of the 4.7 a large copy reaches, with 64 x 512
 // tiles (17.2 us for the best of the other kernels, 32.5 for the one the cost model took).  What is left is start-up: the
 // filters' latency, the first groups' latency and the tail of a launch that is little more than one round (two waves or one
-// per workgroup, for more workgroups: 13.1 and 13.2 us).
+// per workgroup, for more workgroups: 13.1 and 13.2 us, before the biases moved).
 #pragma once
 
 #include "pwin_kernel.h"
@@ -30,7 +32,8 @@ struct PwbCfg {
     static constexpr int AB = 16;              // staging loads of the filters in flight per thread
 };
 
-inline size_t pwb_lds_bytes(int TM, int C) { return (size_t)TM * (((C + 15) / 16) * 16 + 8) * 2; }
+// filters, then the biases of the tile
+inline size_t pwb_lds_bytes(int TM, int C) { return (size_t)TM * (((C + 15) / 16) * 16 + 8) * 2 + (size_t)TM * 4; }
 
 // a.dX divides by the number of channel tiles
 template <class CFG>
@@ -80,24 +83,33 @@ __global__ __launch_bounds__(CFG::NT, 2) void pwb_kernel(ConvArgs a)
     };
 
     // ---- filters to LDS; the first input groups are requested behind the first batch of filter loads -------------------
+    float* const bias_s = (float*)(Fs + TM * pitch);
+    const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);
+    const float bias_r = buffer_load_elem<float>(rbias, tid < TM ? (uint32_t)(m0 + tid) * 4u : kOutOfRange);
     const int vecs = TM * G * 2;  // 16-byte vectors of the tile, channels padded to whole groups with zeros
+    // (a thread's vectors are NT apart: rows and columns are stepped, a division each took as long as the loads)
+    uint32_t row, c8, row_step, c8_step;
+    a.dY.divmod((uint32_t)tid, row, c8);
+    a.dY.divmod((uint32_t)NT, row_step, c8_step);
     for (int v0 = 0; v0 < vecs; v0 += AB * NT) {
         uint4 f[AB];
+        uint32_t at[AB];
 #pragma unroll
         for (int i = 0; i < AB; ++i) {
-            const int v = v0 + i * NT + tid;
-            uint32_t row, c8;
-            a.dY.divmod((uint32_t)v, row, c8);
-            const bool ok = v < vecs && m0 + (int)row < a.K && (int)c8 < C8;
-            f[i] = buffer_load_vec(rfilt, ok ? (uint32_t)((m0 + (int)row) * a.C + (int)c8 * 8) * 2u : kOutOfRange);
+            const bool ok = row < (uint32_t)TM && m0 + (int)row < a.K && (int)c8 < C8;
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rfilt, (int)(ok ? __umul24(row, (uint32_t)a.C * 2u) + c8 * 16u : 0x80000000u), (int)((uint32_t)(m0 * a.C) * 2u), 0);
+            f[i] = make_uint4(v.x, v.y, v.z, v.w);
+            at[i] = row < (uint32_t)TM ? __umul24(row, (uint32_t)pitch) + c8 * 8u : kOutOfRange;
+            row += row_step, c8 += c8_step;
+            if (c8 >= 2u * (uint32_t)G) c8 -= 2u * (uint32_t)G, ++row;
         }
-        if (v0 == 0) static_for<GD>([&](auto sc) { load_group(sc, decltype(sc)::value); });
+        if (v0 == 0) {
+            static_for<GD>([&](auto sc) { load_group(sc, decltype(sc)::value); });
+            if (tid < TM) bias_s[tid] = bias_r;
+        }
 #pragma unroll
         for (int i = 0; i < AB; ++i) {
-            const int v = v0 + i * NT + tid;
-            uint32_t row, c8;
-            a.dY.divmod((uint32_t)v, row, c8);
-            if (v < vecs) *(uint4*)&Fs[row * pitch + c8 * 8] = f[i];
+            if (at[i] != kOutOfRange) *(uint4*)&Fs[at[i]] = f[i];
         }
     }
 
@@ -142,7 +154,7 @@ __global__ __launch_bounds__(CFG::NT, 2) void pwb_kernel(ConvArgs a)
     if (grp < G) pass(std::true_type{}, grp);
 
     // ---- bias + activation + rounding; lane (li, g) holds channels 8i + 4g .. +3 of a block at its NPX pixels -----------
-    const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);
+    // (biases from LDS: memory serves a wave in order, and a load between the stores was waited for until those ahead of it were done)
     const __amdgpu_buffer_rsrc_t rout = make_rsrc(a.out, a.out_bytes);
     const uint32_t out_off = (uint32_t)(((int)n * a.K + m0 + 4 * g) * a.HW + (int)pix) * 2u;
     auto store = [&](auto relu_c) {
@@ -151,7 +163,7 @@ __global__ __launch_bounds__(CFG::NT, 2) void pwb_kernel(ConvArgs a)
         for (int mb = 0; mb < TMB; ++mb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const f32x4 bs = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rbias, (m0 + mb * 32 + 8 * i + 4 * g) * 4, 0, 0));
+                const f32x4 bs = *(const f32x4*)(bias_s + mb * 32 + 8 * i + 4 * g);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int row = mb * 32 + 8 * i + r, v = 4 * i + r;
