@@ -373,16 +373,15 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         // (the conversion launch is rated 1 us dearer than it is, here and below: these kernels ask for workspace, and the models
         // of the others err by as much on layers of 10 us)
         // Without the copy every round of workgroups turns its input again, chunk by chunk; with two chunks and several channel tiles
-        // that lies bare.  Of 241 drawn layers whose pick moved to this form, by calls: 0.92 of the time, 2 more than 5 % slower, none 10 %
-        const double in = (double)d.N * d.C * d.H * d.W;
-        const bool as_it_is = (v.traits & TRAIT_CONVERTS_FILTERS) && in * 2.0 <= 32.0 * 1024.0 * 1024.0;
-        if (as_it_is) t += 5.4 + 2.0 * d.K * d.R * d.S * (d.C + C16 * 16.0) / 5.5e6 + std::ceil(tiles / slots) * ((C16 <= 2.0 && d.K > v.tm ? 0.8 : 0.0) + 0.12 * C16);
-        // (with more input than 32 MiB, where the tests hold the selection to the copy, the form without it is rated just behind)
-        else if (v.traits & (TRAIT_CONVERTS_FIRST | TRAIT_CONVERTS_FILTERS)) {
-            const double copy = d.N * C16 * 16.0 * (d.H + d.pad) * (d.W + d.pad);
+        // that lies bare.  Below 32 MiB of input 241 of 548 drawn layers moved to this form, at 0.92 of their time, two more than 5 % slower,
+        // none 10 %.  Above, 362 of 565 are of this form, at 0.82 of the time of the pick among the others (eight more than 5 % slower, five
+        // 10 to 23 %: 24 to 48 channels, two to four channel tiles), and the picks take 1.014 of the fastest kernel's time
+        if (v.traits & TRAIT_CONVERTS_FILTERS) {
+            t += 5.4 + 2.0 * d.K * d.R * d.S * (d.C + C16 * 16.0) / 5.5e6 + std::ceil(tiles / slots) * ((C16 <= 2.0 && d.K > v.tm ? 0.8 : 0.0) + 0.12 * C16);
+        } else if (v.traits & TRAIT_CONVERTS_FIRST) {
+            const double in = (double)d.N * d.C * d.H * d.W, copy = d.N * C16 * 16.0 * (d.H + d.pad) * (d.W + d.pad);
             t += 5.5 + 2.0 * (in + copy + d.K * d.R * d.S * (d.C + C16 * 16.0)) / 5.5e6;
         }
-        if ((v.traits & TRAIT_CONVERTS_FILTERS) && !as_it_is) t += 0.1;
         return t;
     }
     if (v.traits & (TRAIT_PACKED_FILTERS | TRAIT_CONVERTS_FIRST)) {

@@ -108,6 +108,27 @@ def test_picks_without_a_workspace_do_not_flip_with_one_image_more(shape):
     assert names[0] == names[1] and names[0].startswith("dwin_"), names
 
 
+# ... and with one: us of the form that reads the input as it is, of the best one behind a copy, with one image more (and with twice as many)
+@pytest.mark.parametrize("shape", [
+    ConvShape(83, 64, 56, 56, 192, 3, 3, 1, 1),   # 67, 70 (111, 130)
+    ConvShape(83, 256, 28, 28, 256, 3, 3, 1, 1),  # 79, 81 (127, 141)
+    ConvShape(167, 128, 28, 28, 128, 3, 3, 1, 1),  # 45, 51 (70, 87)
+    ConvShape(668, 32, 28, 28, 64, 3, 3, 1, 1),   # 33, 38 (56, 72)
+    ConvShape(113, 256, 24, 24, 192, 3, 3, 1, 1),  # 61, 66 (97, 112)
+    ConvShape(81, 128, 40, 40, 64, 5, 5, 1, 2),   # 64, 65 (91, 105)
+])
+def test_picks_with_a_workspace_do_not_flip_with_one_image_more(shape):
+    for N in (shape.N, shape.N + 1, 2 * shape.N):
+        name = picks(dataclasses.replace(shape, N=N), wl.BF16)[0]
+        assert name.startswith("bwin_") and name.endswith("_p"), (N, name)
+
+
+def test_large_layers_read_as_they_are_fit_the_static_scratch():
+    d = B.desc_of(ConvShape(96, 64, 56, 56, 192, 3, 3, 1, 1), wl.BF16, relu=True)
+    names = [B.conv_variant_name(d, i) for i in range(B.conv_variant_count(d))]
+    assert B.conv_variant_workspace(d, names.index(B.conv_variant_name(d, -1))) <= 1 << 20 < B.CONV_STATIC_SCRATCH_BYTES
+
+
 # us of the one-launch kernel, of the kernels behind a conversion launch
 @pytest.mark.parametrize("shape", [
     ConvShape(40, 128, 64, 56, 32, 3, 3, 1, 1),  # 25, 31
