@@ -273,18 +273,16 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         return 3.5 + rounds * (v.tm == 96 ? 21.0 : 14.5) + wgs / 256.0 * (v.tm == 96 ? 9.5 : 2.5);
     }
     if (v.traits & TRAIT_SPLIT_PRODUCTS) {
-        // Winograd on split products: v.tm / 32 blocks of 32 channels; a workgroup costs its start, planes and stores and a
-        // step per 16 channels.  v.per_cu of them share a CU, to no gain in time per workgroup.  Measured (model): 20 images
-        // of 13x13x256 -> 384 with M32 / M64 / M96 45 / 36 / 42 us (44 / 39 / 48), 64 of 56x56x64 -> 192 350 / 233 .. 253 /
-        // 198 .. 222 (366 / 246 / 212).
-        const double mb = v.tm / 32.0, tiles = (double)d.N * std::ceil(OH / 2.0) * std::ceil(OW / 2.0);
+        // Winograd on split products: the filter transform, then per round of workgroups a start, an inverse transform and a step per 16
+        // channels.  With 64 and 96 channels a workgroup's tiles follow each other, and a round costs its steps and little more; with 32
+        // and two row vectors two workgroups share a CU.  Constants per tile shape (v.model), a fit to 7671 measured calls of drawn 3x3
+        // layers (rms 4 to 6 %).  Over 1519 of them, one to 30 rounds, the picks take 1.02 of the fastest kernel's time, 1.09 with a start
+        // for every tile and a factor of 1.35 on top; 439 moved, at 0.81 of their time, 11 more than 5 % slower.  us, measured (model), pick
+        // before: 64 images of 56x56x64 -> 64 72 (74), 127, -> 128 127 (131), 232, -> 192 166 (167), 337; 20 of 13x13x256 -> 384 35 (34), 45
+        const double tiles = (double)d.N * std::ceil(OH / 2.0) * std::ceil(OW / 2.0), cus = 256.0 * v.per_cu;
         const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(tiles / (v.tn / 4.0));
-        const double own = 4.5 + 1.2 * mb, t_step = 0.45 + 0.5 * mb, slots = 256.0 * v.per_cu;
-        const double share = std::min((double)v.per_cu, std::max(1.0, std::ceil(wgs / 256.0)));
-        // (rated 1.35-fold.  Over 444 drawn 3x3 layers factors from 1.0 to 1.35 leave the pick at 1.08 to 1.09 times the best
-        // kernel's time; at 1.35 two picks are more than 10 % slower than without this kernel, at 1.0 ten.  It also keeps 20
-        // images of 13x13x256 -> 384, 36 us here against 46, with the kernel that the host tests expect of the selection there)
-        return 1.35 * (2.0 + 4.5 + 2.2e-5 * (double)d.K * d.C + std::ceil(wgs / slots) * share * (own + std::ceil(d.C / 16.0) * t_step));
+        const double rounds = std::ceil(wgs / cus) * std::min((double)v.per_cu, std::ceil(wgs / 256.0));
+        return v.model.call + 5.1e-5 * (double)d.K * d.C + rounds * (v.model.own + std::ceil(d.C / 16.0) * v.model.chunk);
     }
     if (v.family == FAM_WINOGRAD) {
         // F(2x2,3x3) product kernel: one workgroup per (v.tm channels, v.tn / 4 tiles of 2x2 outputs), one round per 256

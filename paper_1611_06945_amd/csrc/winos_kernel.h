@@ -676,7 +676,7 @@ bool winos_valid(const Variant&, const conv_desc& d, int OH, int OW)
 }
 
 template <class CFG>
-void winos_register(std::vector<Variant>& out)
+void winos_register(std::vector<Variant>& out, const TileModel& model)
 {
     Variant v;
     char buf[96];
@@ -692,6 +692,7 @@ void winos_register(std::vector<Variant>& out)
     v.specificity = 5;
     v.traits = TRAIT_SPLIT_PRODUCTS;
     v.per_cu = CFG::WPS / 2;
+    v.model = model;
     v.valid = &winos_valid<CFG>;
     v.launch = &winos_launch<CFG>;
     v.ws_extra = &winos_ws_bytes<CFG>;

@@ -191,3 +191,23 @@ def test_first_layers_go_to_split_products_where_they_are_faster(N, R, split):
     name, nows = picks(shape, wl.F32)
     assert name.startswith("swins_") == split, name
     assert not nows.startswith("swins_"), nows
+
+
+# fp32 3x3 layers with a workspace: us of the fp32 Winograd kernels' best (of the fastest kernel without a transform, where that one was taken), of
+# Winograd on split products
+@pytest.mark.parametrize("shape,split", [
+    (ConvShape(64, 64, 56, 56, 64, 3, 3, 1, 1), True),     # 127, 72
+    (ConvShape(64, 64, 56, 56, 128, 3, 3, 1, 1), True),    # 232, 127
+    (ConvShape(64, 64, 56, 56, 192, 3, 3, 1, 1), True),    # 337, 166
+    (ConvShape(16, 128, 28, 28, 256, 3, 3, 1, 1), True),   # 58, 40
+    (ConvShape(8, 96, 40, 40, 100, 3, 3, 1, 1), True),     # 26, 21
+    (ConvShape(20, 256, 13, 13, 384, 3, 3, 1, 1), True),   # 45, 35
+    (ConvShape(79, 64, 17, 12, 384, 3, 3, 1, 1), True),    # 88 (no transform), 41
+    (ConvShape(16, 24, 55, 50, 24, 3, 3, 1, 1), False),    # 12.9, 20.7
+    (ConvShape(4, 24, 21, 21, 384, 3, 3, 1, 1), False),    # 8.4, 14.1
+    (ConvShape(42, 16, 22, 22, 17, 3, 3, 1, 1), False),    # 7.1, 11.7
+])
+def test_3x3_layers_go_to_split_products_where_they_are_faster(shape, split):
+    name, nows = picks(shape, wl.F32)
+    assert name.startswith("winos_" if split else "wino_"), name
+    assert not nows.startswith("winos_"), nows
