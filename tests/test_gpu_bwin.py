@@ -10,7 +10,7 @@ from paper_1611_06945_amd import binding as B
 from paper_1611_06945_amd import workloads as wl
 from paper_1611_06945_amd.workloads import ConvShape
 
-from gpu_util import TOL, DeviceCase, to_host_f64
+from gpu_util import TOL, DeviceCase, empty_out, to_host_f64, torch_mod
 from test_gpu_packed import PackedCase
 
 pytestmark = pytest.mark.gpu
@@ -93,10 +93,80 @@ def test_input_read_as_it_is_keeps_images_apart():
     data = dict(data, **{"in": data["in"].copy()})
     data["in"][1::2] = 0x7F80  # +infinity
     case = DeviceCase(shape, wl.BF16, data)
-    for i, name in enumerate(case.variant_names()):
-        if name.startswith("bwin_") and name.endswith("_p"):
-            got, want = (to_host_f64(c.run(variant=i), wl.BF16) for c in (case, plain))
-            assert np.array_equal(got[::2], want[::2]), name
+    mine = [(i, n) for i, n in enumerate(case.variant_names()) if n.startswith("bwin_") and n.endswith("_p")]
+    assert mine, shape
+    for i, name in mine:
+        got, want = (to_host_f64(c.run(variant=i), wl.BF16) for c in (case, plain))
+        assert np.array_equal(got[::2], want[::2]), name
+
+
+@pytest.mark.parametrize("where", ["filters", "inputs"])
+def test_input_read_as_it_is_with_values_that_are_not_finite(where):
+    """The products and their order are those of the form that copies the input: the same bits, not finite in the same places."""
+    shape = UNCOPIED[0]
+    data = data_of(shape, wl.F16, 4410, False)
+    x, f = data["in"].copy(), data["filt"].copy()
+    if where == "filters":
+        f[5, 35, 0, 0], f[70, 0, 2, 1], f[99, 17, 1, 1] = np.inf, np.nan, -np.inf
+    else:
+        x[0, 35, 0, 0], x[75, 16, 19, 19], x[149, 0, 7, 0] = np.inf, np.nan, -np.inf
+    case = DeviceCase(shape, wl.F16, dict(data, **{"in": x, "filt": f}), relu=False)
+    index = {n: i for i, n in enumerate(case.variant_names())}
+    mine = [n for n in index if n.startswith("bwin_") and n.endswith("_p")]
+    assert mine, shape
+    for name in mine:
+        got, want = (to_host_f64(case.run(variant=index[n]), wl.F16) for n in (name, name[:-2]))
+        assert np.isfinite(want).any() and not np.isfinite(want).all(), name
+        assert np.array_equal(got, want, equal_nan=True), name
+
+
+# packed filters above 2 MiB: channel tiles in turn instead of side by side.  Inputs just below the kernel's limit of 2 GiB, look-ahead
+# included: many images with ragged channels, one image whose channels lie 3.9 MB apart
+FAR = [
+    ConvShape(9, 520, 24, 24, 250, 3, 3, 1, 1),
+    ConvShape(1100, 300, 55, 56, 40, 3, 3, 1, 1),
+    ConvShape(1, 520, 17850, 112, 64, 3, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("si", range(len(FAR)))
+def test_input_read_as_it_is_far_apart(si):
+    """Bit for bit on small integers, at windows spread over the outputs, the first and the last ones among them."""
+    torch = torch_mod()
+    shape, (N, C, H, W) = FAR[si], FAR[si].in_shape()
+    packed = (shape.K + 31) // 32 * ((C + 15) // 16) * 1024 * shape.R * shape.S
+    assert packed > 2 << 20 if si == 0 else 2 * N * (C + 16) * H * W > 0.99 * 2**31
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4420 + si)
+    x = torch.empty(shape.in_shape(), dtype=torch.float16, device="cuda")
+    for n in range(N):
+        x[n] = torch.randint(-2, 3, (C, H, W), generator=g, device="cuda")
+    f = torch.randint(-2, 3, shape.filt_shape(), generator=g, device="cuda").half()
+    at = torch.cat([torch.zeros(1, dtype=torch.int64), torch.randint(0, N * shape.OH * shape.OW, (400,), generator=torch.Generator().manual_seed(si)),
+                    torch.tensor([N * shape.OH * shape.OW - 1])]).cuda()
+    n, oy, ox = at // (shape.OH * shape.OW), at // shape.OW % shape.OH, at % shape.OW
+    want = torch.zeros(len(at), shape.K, dtype=torch.float64, device="cuda")
+    for r in range(3):
+        for s in range(3):
+            y, xx = oy + r - shape.pad, ox + s - shape.pad
+            ok = (y >= 0) & (y < H) & (xx >= 0) & (xx < W)
+            v = x[n, :, y.clamp(0, H - 1), xx.clamp(0, W - 1)].double() * ok[:, None]
+            want += v @ f[:, :, r, s].double().t().contiguous()
+    desc = B.desc_of(shape, wl.F16, relu=False)
+    mine = [(i, nm) for i, nm in enumerate(B.conv_variant_name(desc, i) for i in range(B.conv_variant_count(desc))) if nm.startswith("bwin_") and nm.endswith("_p")]
+    assert mine, shape
+    ws = torch.empty(max(B.conv_variant_workspace(desc, i) for i, _ in mine), dtype=torch.uint8, device="cuda")
+    for i, name in mine:
+        print(name, shape, flush=True)
+        out = empty_out(shape.out_shape(), wl.F16)
+        B.conv_force_variant(desc, i)
+        try:
+            B.conv_fwd_ws(desc, x, f, None, out, ws, ws.numel())
+            torch.cuda.synchronize()
+        finally:
+            B.conv_force_variant(desc, -1)
+        assert not bool(torch.isnan(out).any()), name
+        assert bool((out[n, :, oy, ox].double() == want.half().double()).all()), name
 
 
 @pytest.mark.parametrize("out_nhwc", [False, True])

@@ -165,10 +165,14 @@ LOOPS = [
 
 @pytest.mark.parametrize("si", range(len(LOOPS)))
 def test_several_tiles_of_a_workgroup(si):
-    icase = int_case(LOOPS[si], wl.F32, 4370 + si, relu=bool(si % 2), use_bias=si != 1)
+    shape = LOOPS[si]
+    icase = int_case(shape, wl.F32, 4370 + si, relu=bool(si % 2), use_bias=si != 1)
+    for M in (64, 96):  # the forms that take several
+        assert any(n.startswith("winos_f32_M%dT32_" % M) for _, n in variants_of(icase)), M
+        assert -(-shape.K // M) * -(-shape.N * -(-shape.OH // 2) * -(-shape.OW // 2) // 32) > 256, M
     for vi, name in variants_of(icase):
         assert_bit_exact(icase, icase.run(variant=vi), name)
-    case = again_case(LOOPS[si], "corners" if si % 2 else "filter")
+    case = again_case(shape, "corners" if si % 2 else "filter")
     with np.errstate(all="ignore"):
         ref = case.ref()
     finite = np.isfinite(ref)
