@@ -542,7 +542,11 @@ bool bwin_valid(const Variant&, const conv_desc& d, int OH, int OW)
     if (CFG::PLANAR) {
         // below 4 MiB the copy is the cheaper way (it is read from L2, and a workgroup's start is most of such a call), and with a
         // single chunk of channels nothing hides the turning.  us per call, copied -> as it is: 119 images of 25x20x48 -> 64, 5.7 MB,
-        // 13.1 -> 11.7; 41 of 20x20x96 -> 64, 3 MB, 10.5 -> 12.4; 66 of 56x56x16 -> 256, 7 MB, 33.2 -> 36.3
+        // 13.1 -> 11.7; 41 of 20x20x96 -> 64, 3 MB, 10.5 -> 12.4; 66 of 56x56x16 -> 256, 7 MB, 33.2 -> 36.3.  Every kernel called, with the
+        // line taken away: of 1122 drawn layers below 2 MiB this form was the fastest for none, from 2 to 4 MiB for 26 of 512, by 2 %, from 4 to
+        // 8 for 69 of 226, from 8 to 32 for 249 of 497; as a valid variant it would only be measured in vain by every tuned call down there.
+        // (The limits below rely on more than one chunk, too: the second is always asked for, with offsets that one image of C <= 16 would
+        // carry past 32 bits)
         if (d.C <= 16 || (long long)d.N * d.C * d.H * d.W * 2 < 4 << 20) return false;
         // whole rows, the right border of the last one behind them; a piece of four aligned pixels for every thread's turn
         if ((d.W & 3) || (long long)g.rows * g.PWs + d.pad > CFG::SLOTS || (long long)g.rows * (d.W / 4) > CFG::QPT * (CFG::NT / 2)) return false;

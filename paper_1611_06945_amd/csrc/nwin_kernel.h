@@ -210,7 +210,7 @@ __global__ __launch_bounds__(CFG::NT) void nwin_kernel(ConvArgs a)
 
     // ---- add the KW channel-waves' partial sums in wave order, then bias + activation + rounding + store --------
     // (biases from LDS: memory serves a wave in order, and a load between the stores was waited for until those ahead of it were done;
-    // 20 images of 13x13x192 -> 384 12.3 -> 11.8 us, 5 of 13x13x256 -> 384 12.7 -> 12.0)
+    // 20 images of 13x13x192 -> 384 12.0 -> 11.5 us, 5 of 13x13x256 -> 384 12.7 -> 12.0)
     float* const red = (float*)smem_raw;  // [KW][32 rows][RP]
     float* const bias_s = red + CFG::RED_FLOATS;
     if (tid < TM) bias_s[tid] = bias_r;

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(CFG::NT) void pwin_kernel(ConvArgs a)
     store_slab(0);
     load_slab(1);  // unconditional: with a single chunk the data is never used
     // (the biases are on their way from here, for behind the loop a memory latency would stand bare: 5 images of 13x13x256 -> 384
-    // 6.2 -> 6.0 us, 20 11.4 -> 11.3)
+    // 6.15 -> 5.95 us, 20 10.9 -> 10.7)
     static_assert(TM <= NT, "a thread for every bias");
     const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);
     const float bias_r = buffer_load_elem<float>(rbias, tid < TM && m0 + tid < a.K ? (uint32_t)(m0 + tid) * 4u : kOutOfRange);

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(CFG::NT) void pwk_kernel(ConvArgs a)
 
     static_for<GD>([&](auto sc) { load_group(sc, decltype(sc)::value); });
     // (with four waves the biases are on their way from here, for behind the loop a memory latency would stand bare: 5 images of
-    // 28x28x256 -> 128 in fp32 6.08 -> 6.00 us; with more waves, whose loops are shorter, they come no earlier: 6.39 -> 6.50)
+    // 28x28x256 -> 128 in fp32 6.07 -> 6.02 us, 2 of 14x14x256 -> 256 in fp16 5.41 -> 5.36; with more waves, whose loops are shorter, they come no earlier: 6.39 -> 6.50)
     constexpr bool EARLY = KW <= 4;
     const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);
     auto load_bias = [&]() { return buffer_load_elem<float>(rbias, tid < TM && m0 + tid < a.K ? (uint32_t)(m0 + tid) * 4u : kOutOfRange); };

@@ -13,8 +13,8 @@
 //   * Filters are split by a small kernel ahead into the workspace, in MFMA operand order ([step][32-channel block][part][lane]
 //     [8], 1 KB each), and come from L2 straight into registers; the four waves of a workgroup share them in L1.
 // What bounds it: 20 images of 227x227 -> 96 are one round of 240 workgroups of 49000 clocks, 34800 of them the loop (936 MFMAs
-// at 37 clocks, 32 at best), 8000 staging and 5500 stores that nothing covers with one workgroup per CU; 2 us are the filters'
-// launch.  Measured, us per call, best of the other kernels -> this one: 20 of 227x227 -> 96, 11x11 40 -> 32; 20 of 223x223 -> 64, 7x7
+// at 37 clocks, 32 at best), 8000 staging and 5500 stores that nothing covers with one workgroup per CU; 2.2 of 32.1 us are the filters'
+// launch (29.9 with the filters split beforehand).  Measured, us per call, best of the other kernels -> this one: 20 of 227x227 -> 96, 11x11 40 -> 32; 20 of 223x223 -> 64, 7x7
 // stride 2, 61 -> 38, 49 of 228x228 146 -> 81.  Where it begins (96 filters of 11x11, images of 227x227; best of the others -> this one): 2 images,
 // 24 tiles of 256 pixels, 14.8 -> 17.8, 3 17.8 -> 17.8, 5 19.3 -> 18.3, 6 23.9 -> 18.6, 10 30.0 -> 26.3, 12 38.7 -> 27.2; 64 filters
 // of 7x7, images of 224x224: 1 image, 49 tiles, 9.6 -> 11.7, 2 12.4 -> 12.2, 4 19.0 -> 15.1.  The selection takes it from there.
@@ -61,7 +61,8 @@ inline SwinsGeom swins_geom(int TN, int R, int ST, int W, int pad, int OH, int O
 
 // filters [K][3][R][S] -> U[step][block][part][lane][8], scaled and split: a wave per block of filters (x) and step (y).
 // One chain of latencies: the eight loads of a lane are requested together (as conditional loads in twenty workgroups of 256 threads
-// they were waited for one by one; call of 20 images of 227x227 -> 96 33.8 -> 32.0 us).
+// they were waited for one by one; call of 20 images of 227x227 -> 96 34.2 -> 32.1 us, 29.9 without this launch.  Traced launches hide it:
+// none takes less than 4.8 us under the profiler).
 template <class CFG>
 __global__ __launch_bounds__(64) void swins_filter_kernel(const float* __restrict__ filt, uint4* __restrict__ U, int K)
 {

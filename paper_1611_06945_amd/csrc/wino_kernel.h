@@ -490,7 +490,7 @@ __global__ __launch_bounds__(CFG::NT) void wino_kernel(ConvArgs a)
 
     // ---- epilogue: planes to LDS, inverse transform, bias + activation, 2x2 stores -----------------------------------
     // (biases are requested ahead of the exchange: between the stores each was waited for until the stores ahead of it were done;
-    // 20 images of 13x13x256 -> 384 46.2 -> 45.3 us, 8 of 56x56x64 -> 64 23.0 -> 22.8)
+    // 20 images of 13x13x256 -> 384 46.4 -> 45.4 us, 8 of 56x56x64 -> 64 23.1 -> 22.9)
     float* const Ms = smem;  // [16][TM][MP]
     constexpr int NE = (TM * TT + NT - 1) / NT;
     const __amdgpu_buffer_rsrc_t rbias = make_rsrc(a.bias, a.bias ? (uint32_t)a.K * 4u : 0u);

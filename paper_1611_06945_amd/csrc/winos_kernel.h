@@ -20,18 +20,21 @@
 //   * Input rows are fetched 16 bytes per lane, the last vector of a row ending with the row: with 4-byte loads the issue
 //     of the loads alone took 300 .. 1700 clocks of a wave's 4000 per step.  Neighbouring tile rows share their rows.
 //   * With 64 or 96 channels (LOOP) the grid is one workgroup per CU, which takes tile after tile; the steps of successive tiles
-//     follow each other, so that only the first one pays for its start (of 64 images of 56x56x64 -> 192, 12.25 tiles per CU, the
-//     starts and the drained stores took 75 of 227 us).  The inverse transform has its own piece of LDS for that; channels
-//     come to it 32 at a time.  A layer of fewer tiles than CUs loses nothing by it.
+//     follow each other, so that only the first one pays for its start (64 images of 56x56x64 -> 192 are 12.25 tiles per CU: with
+//     a workgroup for each, starts and drained stores took a third of the call).  The inverse transform has its own piece of LDS for
+//     that; channels come to it 32 at a time.  A layer of fewer tiles than CUs loses nothing by it.
 // What bounds it: bytes from L2 first.  A step of 96 channels x 32 tiles fetches 147 KB of filters and 20 to 36 of rows and takes
-// 5600 clocks, 32 bytes a clock and CU; its MFMAs are 2304.  On 64 images of 56x56x64 -> 192, of 183 us the epilogue is 52 (22 of
-// them its stores), filters that do not come from L1 27, rows 14, the transform 9, splits 3.  Filters requested earlier (each
-// part as soon as its last product is issued) gain nothing.  Tiles of 64 would halve the filters' bytes but need twice the
-// accumulators (238 us where 96 x 32 took 218, both without LOOP); two workgroups of 32 x 32 per CU double the vector work per
-// product (350).  Taking a split's parts out with v_dot2_f32_bf16 (7 instructions a pair instead of 11) was 0 to 5 % slower.
-// Measured (us per call back to back, filter transform included, start of this form -> now; boxes differ by up to 10 %): 64 images of
-// 56x56x64 -> 192 227 -> 179 (M96), 262 -> 188 (M64), 16 of 28x28x128 -> 256 44.3 -> 40.8, 8 of 40x40x96 -> 100 21.4 -> 21.0; 20 of
-// 13x13x256 -> 384, 186 tiles, 35.7 -> 35.6 (8.8 of them the filter transform).
+// 5600 clocks, 32 bytes a clock and CU; its MFMAs are 2304.  On 64 images of 56x56x64 -> 192 the counters show 2.18 GB from L2 in 185 us and
+// MFMAs busy for 54.  Left out one at a time: the inverse transform 42 us (19 of them its stores), loads of filters 25, of rows 44
+// (the products are then of zeros), splits 24, input transform 12, the code that sums tiles again 9, by its registers; the thirteenth
+// round of tiles is a quarter full.  With 96 channels and five row vectors 4 registers are spilled, reloaded once a tile, outside
+// the steps.  Filters requested earlier (each part as soon as its
+// last product is issued) gain nothing.  Tiles of 64 would halve the filters' bytes but need twice the accumulators (238 us where
+// 96 x 32 took 218, both without LOOP); two workgroups of 32 x 32 per CU double the vector work per product (350).  Taking a
+// split's parts out with v_dot2_f32_bf16 (7 instructions a pair instead of 11) was 0 to 5 % slower.
+// Measured (us per call, other inputs each time, filter transform included, a workgroup per tile -> LOOP, same box in turn): 64 images of
+// 56x56x64 -> 192 217 -> 185 (M96), 251 -> 193 (M64), 16 of 28x28x128 -> 256 43.2 -> 40.0, 8 of 40x40x96 -> 100 21.2 -> 21.1; 20 of
+// 13x13x256 -> 384, 186 tiles, 34.9 both ways (7 of them the filter transform).
 // Range: the parts of x reach 24 bits below x, which for |x| < 2^-102 is below bf16's normal numbers.  Both operands are
 // therefore scaled by 2^24 ahead of the splits: every part of every fp32 number, subnormal ones included, is then a normal
 // bf16 number or zero, whatever the other operand is.  Sums carry 2^48 and are scaled back behind the inverse transform.
@@ -392,8 +395,8 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(WinosArgs w)
     // Entries (filter k, image n, window origin iy, ix of a tile's first output) of the lanes in `mask`, summed in fp32 from the
     // definition: taps outside the image are left out.  The wave takes them together, 64 / entries lanes (rounded down to a
     // power of two) for each, which share its channels; a tile's four outputs share their loads; a lane whose sums are all
-    // NaN is done.  Bound by the scattered loads.  Call of 20 images of 13x13x256 -> 384 (40 us on ordinary data) with one
-    // infinite pixel 148 us, one NaN filter value 130, NaN everywhere 43, results beyond 2^79 everywhere 820; with one lane
+    // NaN is done.  Bound by the scattered loads.  Call of 20 images of 13x13x256 -> 384 (39 us on ordinary data) with one
+    // infinite pixel 141 us, one NaN filter value 120, NaN everywhere 41, results beyond 2^79 everywhere 787; with one lane
     // per entry and output 7900, 1370, 5900 and 5900.
     auto sum_again = [&](const ConvArgs& a, uint64_t mask, int k, int n, int iy, int ix, float* y) {
         const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
