@@ -281,7 +281,11 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         // before: 64 images of 56x56x64 -> 64 72 (74), 127, -> 128 127 (131), 232, -> 192 166 (167), 337; 20 of 13x13x256 -> 384 35 (34), 45
         const double tiles = (double)d.N * std::ceil(OH / 2.0) * std::ceil(OW / 2.0), cus = 256.0 * v.per_cu;
         const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(tiles / (v.tn / 4.0));
-        const double rounds = std::ceil(wgs / cus) * std::min((double)v.per_cu, std::ceil(wgs / 256.0));
+        double rounds = std::ceil(wgs / cus) * std::min((double)v.per_cu, std::ceil(wgs / 256.0));
+        // (64 tiles a workgroup: a last round that is at most half full is of halved tiles.  91 of 700 drawn layers moved to that form, at 0.84 of
+        // their time, none more than 5 % slower)
+        const double rest = wgs - 256.0 * std::floor(wgs / 256.0);
+        if (v.model.grow > 0.0f && rest > 0.0 && rest <= 128.0) rounds = std::floor(wgs / 256.0) + v.model.grow;
         return v.model.call + 5.1e-5 * (double)d.K * d.C + rounds * (v.model.own + std::ceil(d.C / 16.0) * v.model.chunk);
     }
     if (v.family == FAM_WINOGRAD) {

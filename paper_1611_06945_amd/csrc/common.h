@@ -118,7 +118,7 @@ struct Variant {
     WorkspaceFn ws_extra = nullptr;  // workspace the variant needs beyond split partial sums (null: none)
     unsigned traits = 0;             // TRAIT_* bits read by the cost model used when no measurement exists
     int per_cu = 1;                  // workgroups that share a CU, for the families whose cost model asks
-    TileModel model = {0, 0, 0, 0};  // TRAIT_DIRECT_WINDOW, TRAIT_SPLIT_PRODUCTS (`grow` unused)
+    TileModel model = {0, 0, 0, 0};  // TRAIT_DIRECT_WINDOW, TRAIT_SPLIT_PRODUCTS (`grow`: a last round of halved tiles, 0 without)
 };
 
 enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no alignment demands, slower steps)

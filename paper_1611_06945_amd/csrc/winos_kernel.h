@@ -40,7 +40,7 @@
 // bf16 number or zero, whatever the other operand is.  Sums carry 2^48 and are scaled back behind the inverse transform.
 // What this can lose is at the upper end, and shows: an operand above 2^103, a sum above 2^79 or an infinity gives an
 // infinity or a NaN in every output that it reaches.  An output tile that is not finite is summed again in fp32 from the
-// definition (sum_again).
+// definition (winos_sum_again).
 #pragma once
 
 #include "pwin_kernel.h"
@@ -168,6 +168,77 @@ __device__ __forceinline__ const WinosArgs& winos_args_again()
     auto p = __builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));
     return *(const WinosArgs*)p;
+}
+
+// Entries (filter k, image n, window origin iy, ix of a tile's first output) of the lanes in `mask`, summed in fp32 from the
+// definition: taps outside the image are left out.  The wave takes them together, 64 / entries lanes (rounded down to a
+// power of two) for each, which share its channels; a tile's four outputs share their loads; a lane whose sums are all
+// NaN is done.  Bound by the scattered loads.  Call of 20 images of 13x13x256 -> 384 (39 us on ordinary data) with one
+// infinite pixel 141 us, one NaN filter value 120, NaN everywhere 41, results beyond 2^79 everywhere 787; with one lane
+// per entry and output 7900, 1370, 5900 and 5900.
+__device__ __forceinline__ void winos_sum_again(const ConvArgs& a, int lane, uint64_t mask, int k, int n, int iy, int ix, float* y)
+{
+    constexpr uint32_t kFar = 0x80000000u;
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
+    const int count = __builtin_popcountll(mask), lg = 31 - __builtin_clz(64 / count);
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    const bool mine = (mask >> lane) & 1;
+    const int entry = lane >> lg, step = 1 << lg;
+    // (lanes outside the mask push to the last lane, which no entry reads when there are any)
+    const int owners = __builtin_amdgcn_ds_permute((mine ? rank : 63) * 4, lane);
+    const int owner = __shfl(owners, entry < count ? entry : 0);
+    k = __shfl(k, owner);
+    n = __shfl(n, owner);
+    iy = __shfl(iy, owner);
+    ix = __shfl(ix, owner);
+    const int x0 = ix < 0 ? 0 : ix > a.W - 4 ? a.W - 4 : ix, d = ix - x0;  // d in -1 .. 2
+    bool in_x[4];
+    uint32_t row[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        in_x[r] = (unsigned)(ix + r) < (unsigned)a.W;
+        const bool in_y = (unsigned)(iy + r) < (unsigned)a.H && entry < count;
+        row[r] = in_y ? (uint32_t)((n * a.C * a.H + iy + r) * a.W + x0) * 4u : kFar;
+    }
+    const __amdgpu_buffer_rsrc_t rf = make_rsrc(a.filt, a.filt_bytes);
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int c = lane & (step - 1); entry < count && c < a.C; c += step) {
+        const uint32_t fo = (uint32_t)(k * a.C + c) * 36u;
+        const f32x4 f0 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, (int)fo, 0, 0));
+        const f32x4 f1 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, (int)fo, 16, 0));
+        const float f8 = buffer_load_elem<float>(rf, fo + 32u);
+        const float f[9] = {f0[0], f0[1], f0[2], f0[3], f1[0], f1[1], f1[2], f1[3], f8};
+        f32x4 v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            v[r] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rin, (int)(row[r] == kFar ? kFar : row[r] + (uint32_t)(c * a.HW) * 4u), 0, 0));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float x[4] = {d < 0 ? 0.0f : d == 0 ? v[r][0] : d == 1 ? v[r][1] : v[r][2],
+                                d < 0 ? v[r][0] : d == 0 ? v[r][1] : d == 1 ? v[r][2] : v[r][3],
+                                d < 0 ? v[r][1] : d == 0 ? v[r][2] : d == 1 ? v[r][3] : 0.0f,
+                                d < 0 ? v[r][2] : d == 0 ? v[r][3] : 0.0f};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int w = r - (q >> 1);  // row of the window
+                if (w < 0 || w > 2) continue;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    const int cx = (q & 1) + t;
+                    s[q] = row[r] != kFar && in_x[cx] ? __builtin_fmaf(x[cx], f[w * 3 + t], s[q]) : s[q];
+                }
+            }
+        }
+        if (s[0] != s[0] && s[1] != s[1] && s[2] != s[2] && s[3] != s[3]) break;
+    }
+    for (int o = step >> 1; o > 0; o >>= 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], o);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float total = __shfl(s[q], rank << lg & 63);
+        y[q] = mine ? total : y[q];
+    }
 }
 
 template <class CFG>
@@ -392,74 +463,6 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(WinosArgs w)
     typedef std::integral_constant<int, 1> c1_t;
 
     // ---- epilogue, 32 channels at a time: planes to LDS, inverse transform, bias + activation, 2x2 stores ---------------
-    // Entries (filter k, image n, window origin iy, ix of a tile's first output) of the lanes in `mask`, summed in fp32 from the
-    // definition: taps outside the image are left out.  The wave takes them together, 64 / entries lanes (rounded down to a
-    // power of two) for each, which share its channels; a tile's four outputs share their loads; a lane whose sums are all
-    // NaN is done.  Bound by the scattered loads.  Call of 20 images of 13x13x256 -> 384 (39 us on ordinary data) with one
-    // infinite pixel 141 us, one NaN filter value 120, NaN everywhere 41, results beyond 2^79 everywhere 787; with one lane
-    // per entry and output 7900, 1370, 5900 and 5900.
-    auto sum_again = [&](const ConvArgs& a, uint64_t mask, int k, int n, int iy, int ix, float* y) {
-        const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes);
-        const int count = __builtin_popcountll(mask), lg = 31 - __builtin_clz(64 / count);
-        const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        const bool mine = (mask >> lane) & 1;
-        const int entry = lane >> lg, step = 1 << lg;
-        // (lanes outside the mask push to the last lane, which no entry reads when there are any)
-        const int owners = __builtin_amdgcn_ds_permute((mine ? rank : 63) * 4, lane);
-        const int owner = __shfl(owners, entry < count ? entry : 0);
-        k = __shfl(k, owner);
-        n = __shfl(n, owner);
-        iy = __shfl(iy, owner);
-        ix = __shfl(ix, owner);
-        const int x0 = ix < 0 ? 0 : ix > a.W - 4 ? a.W - 4 : ix, d = ix - x0;  // d in -1 .. 2
-        bool in_x[4];
-        uint32_t row[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            in_x[r] = (unsigned)(ix + r) < (unsigned)a.W;
-            const bool in_y = (unsigned)(iy + r) < (unsigned)a.H && entry < count;
-            row[r] = in_y ? (uint32_t)((n * a.C * a.H + iy + r) * a.W + x0) * 4u : kFar;
-        }
-        const __amdgpu_buffer_rsrc_t rf = make_rsrc(a.filt, a.filt_bytes);
-        float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int c = lane & (step - 1); entry < count && c < a.C; c += step) {
-            const uint32_t fo = (uint32_t)(k * a.C + c) * 36u;
-            const f32x4 f0 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, (int)fo, 0, 0));
-            const f32x4 f1 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, (int)fo, 16, 0));
-            const float f8 = buffer_load_elem<float>(rf, fo + 32u);
-            const float f[9] = {f0[0], f0[1], f0[2], f0[3], f1[0], f1[1], f1[2], f1[3], f8};
-            f32x4 v[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                v[r] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rin, (int)(row[r] == kFar ? kFar : row[r] + (uint32_t)(c * a.HW) * 4u), 0, 0));
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float x[4] = {d < 0 ? 0.0f : d == 0 ? v[r][0] : d == 1 ? v[r][1] : v[r][2],
-                                    d < 0 ? v[r][0] : d == 0 ? v[r][1] : d == 1 ? v[r][2] : v[r][3],
-                                    d < 0 ? v[r][1] : d == 0 ? v[r][2] : d == 1 ? v[r][3] : 0.0f,
-                                    d < 0 ? v[r][2] : d == 0 ? v[r][3] : 0.0f};
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int w = r - (q >> 1);  // row of the window
-                    if (w < 0 || w > 2) continue;
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) {
-                        const int cx = (q & 1) + t;
-                        s[q] = row[r] != kFar && in_x[cx] ? __builtin_fmaf(x[cx], f[w * 3 + t], s[q]) : s[q];
-                    }
-                }
-            }
-            if (s[0] != s[0] && s[1] != s[1] && s[2] != s[2] && s[3] != s[3]) break;
-        }
-        for (int o = step >> 1; o > 0; o >>= 1)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], o);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float total = __shfl(s[q], rank << lg & 63);
-            y[q] = mine ? total : y[q];
-        }
-    };
     auto finish = [&](const Place& at) {
         const WinosArgs& w = winos_args_again();
         const ConvArgs& a = w.a;
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(CFG::NT, CFG::WPS) void winos_kernel(WinosArgs w)
                 if (!again) continue;
                 const int k = at.m0 + e * 16 + kr;
                 float y[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                sum_again(a, again, k, (int)n, oy - a.pad, ox - a.pad, y);
+                winos_sum_again(a, lane, again, k, (int)n, oy - a.pad, ox - a.pad, y);
                 const bool mine_ = bad >> e & 1;
                 const float b = a.bias && mine_ ? a.bias[k] : 0.0f;
 #pragma unroll

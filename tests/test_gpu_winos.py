@@ -227,3 +227,38 @@ def test_static_scratch_serves_layers_whose_fastest_kernel_wants_more(shape, dty
     B.conv_fwd_static(desc, x, f, None, got)
     torch.cuda.synchronize()
     assert B.conv_compare_outputs(dtype, got, want, got.numel()) <= (TOL[dtype] if dtype != wl.BF16 else 1e-2)
+
+
+# A row of planes per wave (64 tiles a workgroup): input rows go to LDS by whole 16-byte vectors, the last one of a row reaching into
+# the next row or behind the tensor, and columns outside the image are read elsewhere; rows as wide as either staging takes
+ROWS = [
+    ConvShape(2, 9, 6, 5, 33, 3, 3, 1, 1),
+    ConvShape(3, 16, 9, 6, 64, 3, 3, 1, 1),
+    ConvShape(2, 24, 40, 7, 40, 3, 3, 1, 0),
+    ConvShape(2, 8, 21, 36, 40, 3, 3, 1, 1),
+    ConvShape(2, 8, 12, 76, 40, 3, 3, 1, 1),
+    ConvShape(1, 17, 9, 92, 65, 3, 3, 1, 1),
+    ConvShape(130, 16, 8, 8, 64, 3, 3, 1, 1),   # halves of tiles only, the last one of them empty
+    ConvShape(137, 20, 16, 16, 70, 3, 3, 1, 1),  # whole tiles, then halves
+]
+
+
+@pytest.mark.parametrize("si", range(len(ROWS)))
+def test_planes_row_by_row(si):
+    shape = ROWS[si]
+    icase = int_case(shape, wl.F32, 4500 + si, relu=bool(si % 2), use_bias=si != 1)
+    mine = [(i, n) for i, n in variants_of(icase) if "M64T64" in n]
+    assert mine, shape
+    rcase = random_case(shape, wl.F32, 4550 + si, relu=not si % 2)
+    special = again_case(shape, "corners" if si % 2 else "filter")
+    with np.errstate(all="ignore"):
+        ref = special.ref()
+    for vi, name in mine:
+        print(name, shape, flush=True)
+        assert_bit_exact(icase, icase.run(variant=vi), name)
+        err = rcase.error(rcase.run(variant=vi))
+        assert err <= 1e-6, "%s: %.3g" % (name, err)
+        got = to_host_f64(special.run(variant=vi), wl.F32)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        finite = np.isfinite(ref)
+        assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
