@@ -69,6 +69,7 @@ State& state()
         register_wino_f32(s->variants);
         register_winos_f32(s->variants);
         register_swins_f32(s->variants);
+        register_sdir_f32(s->variants);
         register_swin_f16(s->variants);
         register_swin_bf16(s->variants);
         register_swinp_f16(s->variants);
@@ -271,6 +272,19 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double wgs = (double)d.N * std::ceil((double)OH * OW / v.tn) * std::ceil(d.K / (double)v.tm), rounds = std::ceil(wgs / 256.0);
         if (d.R == 7) return 8.2 + rounds * (v.tm == 64 ? 7.4 : 4.4);
         return 3.5 + rounds * (v.tm == 96 ? 21.0 : 14.5) + wgs / 256.0 * (v.tm == 96 ? 9.5 : 2.5);
+    }
+    if (v.traits & TRAIT_SPLIT_DIRECT) {
+        // The filters' launch, then per round of workgroups (the last one as long as its fullest CU makes it) a start and chunks of
+        // channels, of which a share goes with the positions that are staged.  Constants per tile shape: a fit to 8500 measured calls of
+        // 1840 drawn layers (rms 4 to 8 %, 6 to 11 % at 3x3).  The implicit GEMMs beside it are rated less closely, which 3x3 pays for with a factor: over
+        // 343 other layers the picks take, at 5x5, 0.71 of what they took (72 of 103 moved, at 0.61, none more than 5 % slower; 1.03 of the
+        // fastest kernel's time, 1.46 before), at 3x3 stride 2 and 1 0.97 each (rated as they are 12 and 4 of 120 were more than 5 % slower, with 1.15
+        // and 1.08 3 each).  us: 50 images of 14x14x424 -> 96 5x5 239, 119
+        const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn), chunks = std::ceil(Q / v.tk);
+        const double slots = 256.0 * v.per_cu, full = std::floor(wgs / slots), rest = std::ceil((wgs - full * slots) / 256.0);
+        const double rounds = full * std::pow((double)v.per_cu, (double)v.model.grow) + (rest > 0.0 ? std::pow(rest, (double)v.model.grow) : 0.0);
+        const double pieces = std::ceil((double)sdir_positions(v.tn, d.N, d.R, d.stride, OH, OW) / v.slab_threads) * v.slab_threads / v.slab, share = d.R == 3 ? 0.4 : 0.2;
+        return (d.R == 5 ? 1.0 : d.stride > 1 ? 1.2 : 1.1) * (v.model.call + 1.2e-6 * d.K * Q + rounds * (v.model.own + chunks * v.model.chunk * (1.0 - share + share * pieces)));
     }
     if (v.traits & TRAIT_SPLIT_PRODUCTS) {
         // Winograd on split products: the filter transform, then per round of workgroups a start, an inverse transform and a step per 16
@@ -675,7 +689,7 @@ int conv_fwd_static(const conv_desc* desc, const void* in, const void* filt, con
     }
     if (idx < 0) return idx;
     size_t need = ws_bytes_of(st.variants[idx], *desc, OH, OW);
-    if (need > (size_t)CONV_STATIC_SCRATCH_BYTES && (st.variants[idx].traits & (TRAIT_CONVERTS_FIRST | TRAIT_CONVERTS_FILTERS | TRAIT_SPLIT_PRODUCTS | TRAIT_SPLIT_FIRST))) {
+    if (need > (size_t)CONV_STATIC_SCRATCH_BYTES && (st.variants[idx].traits & (TRAIT_CONVERTS_FIRST | TRAIT_CONVERTS_FILTERS | TRAIT_SPLIT_PRODUCTS | TRAIT_SPLIT_FIRST | TRAIT_SPLIT_DIRECT))) {
         // kernels that trade scratch for speed (a copy of the input, split filters): where the array is too small for them, the pick that fits it (a forced
         // variant stays, and is refused below)
         std::lock_guard<std::mutex> g(st.mu);

@@ -118,7 +118,9 @@ struct Variant {
     WorkspaceFn ws_extra = nullptr;  // workspace the variant needs beyond split partial sums (null: none)
     unsigned traits = 0;             // TRAIT_* bits read by the cost model used when no measurement exists
     int per_cu = 1;                  // workgroups that share a CU, for the families whose cost model asks
-    TileModel model = {0, 0, 0, 0};  // TRAIT_DIRECT_WINDOW, TRAIT_SPLIT_PRODUCTS (`grow`: a last round of halved tiles, 0 without)
+    TileModel model = {0, 0, 0, 0};  // TRAIT_DIRECT_WINDOW, TRAIT_SPLIT_DIRECT, TRAIT_SPLIT_PRODUCTS (`grow`: a last round of halved tiles, 0 without)
+    int slab = 0;                    // TRAIT_SPLIT_DIRECT: positions its slab has room for
+    int slab_threads = 0;            // ... and threads that fill it
 };
 
 enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no alignment demands, slower steps)
@@ -138,6 +140,7 @@ enum { TRAIT_SCALAR_LOADS = 1u,  // filter tile fetched element by element (no a
        TRAIT_DIRECT_WINDOW = 32768u,   // 16-bit window kernel that brings both operands to MFMA order on the way through LDS, any stride
        TRAIT_SPLIT_FIRST = 65536u,     // fp32 first layers on split products
        TRAIT_CONVERTS_FILTERS = 131072u,  // serves the plain formats by converting the filters into the workspace first, input read as it is
+       TRAIT_SPLIT_DIRECT = 262144u,   // fp32 window kernel on split products, any stride
        TRAIT_CHANNEL_WAVES = 2048u };  // fp32 window kernel on linear pixel tiles whose waves split the channels of a chunk
 
 enum { FAM_IGEMM = 0, FAM_POINTWISE = 1, FAM_FIRSTLAYER = 2, FAM_WINDOW = 3, FAM_FC = 4, FAM_NHWC = 5, FAM_WINOGRAD = 6 };
@@ -166,6 +169,7 @@ void register_pwb_f16(std::vector<Variant>& out);
 void register_pwb_bf16(std::vector<Variant>& out);
 void register_winos_f32(std::vector<Variant>& out);
 void register_swins_f32(std::vector<Variant>& out);
+void register_sdir_f32(std::vector<Variant>& out);
 void register_pwk_f32(std::vector<Variant>& out);
 void register_pwk_f16(std::vector<Variant>& out);
 void register_pwk_bf16(std::vector<Variant>& out);
@@ -205,6 +209,18 @@ hipError_t launch_pack_filters16_any(const void* filt, void* out, int K, int C, 
 // max_i |got_i - ref_i| / max(max_j |ref_j|, 1e-30) of two device tensors of `n` elements (infinity when `got` holds a
 // non-finite value where `ref` is finite, or a NaN); `stats` is 16 bytes of device scratch.  Synchronises `s`.
 hipError_t compare_outputs(int dtype, const void* got, const void* ref, size_t n, uint32_t* stats, hipStream_t s, double* err);
+
+// fp32 window kernel on split products: most positions that a tile of `TN` consecutive output pixels stages
+inline long long sdir_positions(int TN, int N, int R, int stride, int OH, int OW)
+{
+    const long long up = ((long long)TN + OW - 2) / OW;  // output rows between a tile's first and last pixel
+    long long cross = (up + OH - 1) / OH;
+    if (cross > N - 1) cross = N - 1;
+    long long rows = up * stride + R + cross * (R > stride ? R - stride : 0);
+    const long long all = N * ((OH - 1LL) * stride + R);
+    if (rows > all) rows = all;
+    return rows * ((OW - 1LL) * stride + R);
+}
 
 // Device ceilings measured in place (probe_kernels.hip).
 hipError_t probe_mfma(int dtype, int block, float* sink, hipStream_t s, double* tflops);

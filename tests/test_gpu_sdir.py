@@ -1,0 +1,74 @@
+"""GPU parity of the direct window kernel on split products (fp32) where its tiles, slabs and channel steps have their edges: bit
+for bit on small integers (the splits and every sum are exact), within a bound that shows a lost partial product on random data, and
+on operands that the parts cannot carry, where the sums are taken again from the definition."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1611_06945_amd import workloads as wl
+from paper_1611_06945_amd.workloads import ConvShape
+
+from gpu_util import TOL, DeviceCase, to_host_f64
+from test_gpu_parity import assert_bit_exact, int_case, random_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    ConvShape(1, 8, 5, 5, 17, 5, 5, 1, 2),      # half a channel step, one tile, rows shorter than a half wave
+    ConvShape(3, 17, 13, 13, 33, 5, 5, 1, 2),   # one channel over a step, one filter over a block, tiles across images
+    ConvShape(9, 40, 4, 3, 70, 3, 3, 1, 1),     # several images a tile, three steps
+    ConvShape(2, 130, 19, 23, 64, 3, 3, 2, 1),  # nine steps: waves with one more than others
+    ConvShape(2, 16, 30, 20, 40, 3, 3, 3, 0),   # windows side by side
+    ConvShape(2, 24, 33, 21, 100, 5, 5, 2, 1),  # a border smaller than the window needs to keep its size
+    ConvShape(1, 64, 57, 55, 48, 3, 3, 1, 1),   # wide rows
+    ConvShape(1, 20, 9, 8, 32, 5, 5, 4, 4),     # the largest stride and border, fewer rows than a tile spans
+]
+
+
+def variants_of(case):
+    return [(i, n) for i, n in enumerate(case.variant_names()) if n.startswith("sdir_")]
+
+
+@pytest.mark.parametrize("si", range(len(SHAPES)))
+def test_shapes(si):
+    shape = SHAPES[si]
+    icase = int_case(shape, wl.F32, 4600 + si, relu=bool(si % 2), use_bias=si != 1)
+    rcase = random_case(shape, wl.F32, 4650 + si, relu=not si % 2)
+    mine = variants_of(icase)
+    assert mine, shape
+    for vi, name in mine:
+        print(name, shape, flush=True)
+        assert_bit_exact(icase, icase.run(variant=vi), name)
+        err = rcase.error(rcase.run(variant=vi))
+        assert err <= 1e-6, "%s: %.3g" % (name, err)  # (any partial product left out: 3e-6 and more)
+
+
+@pytest.mark.parametrize("kind", ["corners", "filter", "huge", "tiny", "infinities"])
+@pytest.mark.parametrize("si", [1, 2, 3, 5])
+def test_sums_again_and_small_operands(si, kind):
+    shape = SHAPES[si]
+    x = wl.draw(("halfnormal", 1.0), shape.in_shape(), 4694).astype(np.float32)
+    f = wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), 4695).astype(np.float32)
+    if kind == "corners":
+        x[0, 0, 0, 0], x[-1, -1, -1, -1], x[-1, 3, 0, -1], x[0, 5, -1, 0] = np.nan, np.inf, -np.inf, np.nan
+    elif kind == "filter":
+        f[shape.K // 2, 1, 2, 0], f[-1, -1, 0, 1] = np.nan, -np.inf
+    elif kind == "huge":  # finite, every sum beyond what the scaled products can hold
+        x *= np.float32(1e26)
+    elif kind == "tiny":  # the third parts would be below bf16's normal numbers without the scale
+        x, f = (x.astype(np.float64) * 2.0**-120).astype(np.float32), (f.astype(np.float64) * 2.0**80).astype(np.float32)
+    else:
+        x[:] = np.inf
+    bias = np.full(shape.K, 0.0 if kind == "tiny" else 0.25, dtype=np.float32)
+    case = DeviceCase(shape, wl.F32, {"in": x, "filt": f, "bias": bias}, relu=False)
+    with np.errstate(all="ignore"):
+        ref = case.ref()
+    finite = np.isfinite(ref)
+    for vi, name in variants_of(case):
+        print(name, shape, kind, flush=True)
+        got = to_host_f64(case.run(variant=vi), wl.F32)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        if kind == "tiny":
+            assert np.abs(got - ref).max() <= 1e-6 * np.abs(ref).max(), name
+        elif finite.any():
+            assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
