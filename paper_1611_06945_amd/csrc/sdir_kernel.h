@@ -16,8 +16,8 @@
 // staging of a chunk, 1700 clocks of loads and 1800 of splits and stores beside 3500 of products, under which two workgroups of a CU lie
 // for each other; for layers of few chunks the start, 5800 clocks, and the filters' launch, 3 us.  Rows of a 5x5 window are a loop:
 // laid out, a layer of one chunk waited for its instructions (16x16x88 -> 49 11.1 -> 9.3 us, 35x33x112 -> 352 at stride 2 40 -> 30).
-// Measured, us per call, best of the other kernels -> this one: 36 images of 41x39x32 -> 49 5x5 63 -> 36, 4 of 7x10x496 -> 104 70 -> 44, 50 of
-// 14x14x424 -> 96 239 -> 119, 13 of 35x33x112 -> 352 3x3 stride 2 42 -> 35.
+// Measured, us per call in one run, the fastest of the other kernels -> the fastest of this one: 36 images of 41x39x32 -> 49 5x5 63 -> 35, 4 of
+// 7x10x496 -> 104 55 -> 41, 50 of 14x14x424 -> 96 234 -> 115, 13 of 35x33x112 -> 352 3x3 stride 2 41 -> 37.
 #pragma once
 
 #include "pwin_kernel.h"
