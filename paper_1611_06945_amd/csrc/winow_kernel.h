@@ -20,7 +20,7 @@
 // clock falls to 1.94 GHz (2.23 with filters of zeros): the power limit is near.
 // Measured (us per call, other inputs each time, filter transform included, winos_kernel's best -> here, same box in turn): 64 images of 56x56x64 ->
 // 192 182 -> 160, 16 of 28x28x128 -> 256 40.6 -> 34.4, 33 of 28x28x128 -> 192 48.9 -> 47.4; 20 of 13x13x256 -> 384, 96 tiles, 35.6 -> 37.0
-// (not taken).  Over 700 drawn layers it is the fastest for a third of those with 100 and more tiles, at 0.85 of the best time before.
+// (not taken).  Of 900 drawn layers 165 have 100 and more tiles; it is the fastest for 109 of them, there at 0.87 of the best time before.
 // Tried: eight waves, a block of tiles each (225 us: the filters' loads twice over, 64 bytes a clock and CU); planes to LDS as
 // they stand, without the columns' sums (11300 clocks an epilogue against 9600: LDS takes 64 bytes a clock); eight groups of filters ahead
 // instead of four, and v_dot2_f32_bf16 for what a part leaves (no faster, a fifth slower).
