@@ -304,7 +304,7 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
         const int q = wk * QW + j;
         bias[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rbias, (m0 + q / 4 / NBW * 32 + q % 4 * 8 + 4 * g) * 4, 0, 0));
     }
-    const float floor = a.relu ? 0.0f : -__builtin_inff();
+    const float floor = a.relu ? 0.0f : __builtin_nanf("");  // the maximum with a NaN is the other operand, a NaN (a bias that is one) stays
     uint64_t bad = 0;  // bit 4 * quad + channel: a sum that is not finite
 #pragma unroll
     for (int j = 0; j < QW; ++j) {

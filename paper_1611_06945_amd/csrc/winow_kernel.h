@@ -325,7 +325,7 @@ __global__ __launch_bounds__(CFG::NT, 1) void winow_kernel(WinowArgs w)
         uint32_t out_bytes = w.a.out_bytes, plane = (uint32_t)w.a.OHW * 4u, row = (uint32_t)w.a.OW * 4u;
         asm volatile("" : "+s"(out), "+s"(out_bytes), "+s"(plane));
         const __amdgpu_buffer_rsrc_t rout = make_rsrc((const void*)out, out_bytes);
-        float floor = w.a.relu ? 0.0f : -__builtin_inff();  // (of results that are finite)
+        float floor = w.a.relu ? 0.0f : __builtin_nanf("");  // (the maximum with a NaN is the other operand; a NaN, of the bias, stays)
         int room = w.a.K - at.m0 - kr;  // channels from the first of the four to the last one
         asm volatile("" : "+v"(floor), "+v"(room));
         uint32_t base[2][4];  // of a tile's four outputs in the first of the channels

@@ -72,3 +72,20 @@ def test_sums_again_and_small_operands(si, kind):
             assert np.abs(got - ref).max() <= 1e-6 * np.abs(ref).max(), name
         elif finite.any():
             assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
+
+
+@pytest.mark.parametrize("relu", [False, True])
+def test_biases_that_are_not_finite(relu):
+    """A NaN bias is the result of its channel where no activation drops it, and so is an infinite one."""
+    shape = SHAPES[3]
+    data = {"in": wl.draw(("halfnormal", 1.0), shape.in_shape(), 4696).astype(np.float32),
+            "filt": wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), 4697).astype(np.float32), "bias": np.full(shape.K, 0.25, dtype=np.float32)}
+    data["bias"][[0, 5, 31, 40]] = np.nan, np.inf, -np.inf, np.nan
+    case = DeviceCase(shape, wl.F32, data, relu=relu)
+    ref = case.ref()
+    assert np.isnan(ref).any() != relu
+    for vi, name in variants_of(case):
+        got = to_host_f64(case.run(variant=vi), wl.F32)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        finite = np.isfinite(ref)
+        assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
