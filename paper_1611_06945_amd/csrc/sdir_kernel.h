@@ -6,7 +6,9 @@
 //   * Leading products and the five small ones have accumulators of their own: a sum is then rounded once for sixteen channels and tap.
 //     Error against 64 bits (2-norm, relative, half-normal inputs; six products in one accumulator -> here, the pick before): 20x20x352 ->
 //     64 5x5 14.5e-7 -> 5.8e-7, 8.0e-7; 16x16x88 -> 49 7.2e-7 -> 2.7e-7, 4.3e-7; 19x23x130 -> 64 3x3 stride 2 5.1e-7 -> 1.9e-7, 2.1e-7.
-//     Waves that split the channels come closer still (1.2e-7 to 4.5e-7).  Over 302 drawn layers whose untuned pick moved here the error is
+//     Where a wave takes all channels of a 5x5 layer, a chunk's leading sums are added to those before it: 3 images of 16x16x220 -> 160 4.5e-7 ->
+//     1.3e-7, 2 of 40x40x176 -> 16 3.7e-7 -> 1.2e-7 (the implicit GEMM split eight ways 4.7e-7, 3.6e-7), for 1 % of the time
+//     (17 of 33x33x416 -> 64 186.5 -> 188.2 us, 5 of 28x31x224 -> 256 107.1 -> 108.4).  Waves that split the channels: 1.2e-7 to 4.5e-7.  Over 302 drawn layers whose untuned pick moved here the error is
 //     0.45 of the former pick's (geometric mean; 0.96 at most).
 //   * A small kernel ahead splits the filters into MFMA operand order; fragments come from L2 straight into registers.
 //   * Input is read four bytes a lane (any row length, border and stride), split and stored as [part][eight channels][position], rows
@@ -190,14 +192,17 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
         o_px[nb] = p < a.P ? (uint32_t)(n * a.K * a.OHW + pix) * 4u : kFar;
     }
 
-    // The leading products and the five small ones have sums of their own: a sum is rounded once for sixteen channels and tap, not six times
-    typename mma_t::acc_t acc[MBW][NBW], low[MBW][NBW];
+    // The leading products and the five small ones have sums of their own: a sum is rounded once for sixteen channels and tap, not six times.
+    // At 5x5, a wave that takes all channels adds a chunk's leading sums to those of the chunks before: the chain of roundings is 25
+    // long, then one for each chunk
+    constexpr bool FOLD = R == 5 && WK == 1;
+    typename mma_t::acc_t acc[MBW][NBW], low[MBW][NBW], done[MBW][NBW];
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = low[mb][nb][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = low[mb][nb][v] = done[mb][nb][v] = 0.0f;
 
     const int rounds = (C16 + WK - 1) / WK;
     load_x(wk);
@@ -254,6 +259,14 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
         }
         __builtin_amdgcn_sched_barrier(0);
         if (round + 1 < rounds) {
+            if constexpr (FOLD) {
+#pragma unroll
+                for (int mb = 0; mb < MBW; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < NBW; ++nb)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) done[mb][nb][v] += acc[mb][nb][v], acc[mb][nb][v] = 0.0f;
+            }
             if constexpr (WN > 1) __syncthreads();
             store_x();
             if constexpr (WN > 1) __syncthreads();
@@ -264,7 +277,7 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
 #pragma unroll
         for (int nb = 0; nb < NBW; ++nb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mb][nb][v] += low[mb][nb][v];
+            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = (FOLD ? done[mb][nb][v] + acc[mb][nb][v] : acc[mb][nb][v]) + low[mb][nb][v];
 
     // ---- sums of the waves that split the channels, in wave order; quad q = (block of channels, block of pixels, four channels) ----
     f32x4 y[QW];

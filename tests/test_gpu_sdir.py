@@ -89,3 +89,21 @@ def test_biases_that_are_not_finite(relu):
         assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
         finite = np.isfinite(ref)
         assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
+
+
+@pytest.mark.parametrize("shape", [ConvShape(3, 220, 16, 16, 160, 5, 5, 1, 2), ConvShape(2, 176, 40, 40, 16, 5, 5, 1, 2), ConvShape(2, 416, 33, 33, 64, 5, 5, 1, 2), ConvShape(2, 256, 13, 13, 64, 3, 3, 2, 1)])
+def test_no_less_precise_than_the_split_gemm_it_replaces(shape):
+    """Error against 64 bits (2-norm) of every tile beside that of the implicit GEMM that splits the reduction over eight workgroups, the most
+    precise of the kernels these layers ran on.  One chain of roundings over all channels and taps: 1.03 of it in the second layer."""
+    data = {"in": wl.draw(("halfnormal", 1.0), shape.in_shape(), 4698).astype(np.float32),
+            "filt": wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), 4699).astype(np.float32), "bias": np.zeros(shape.K, np.float32)}
+    case = DeviceCase(shape, wl.F32, data, relu=False)
+
+    def error(vi):
+        return np.linalg.norm(to_host_f64(case.run(variant=vi), wl.F32) - case.ref()) / np.linalg.norm(case.ref())
+
+    split = min(error(i) for i, n in enumerate(case.variant_names()) if n.startswith("ug_") and n.endswith("_sk8"))
+    for vi, name in variants_of(case):
+        err = error(vi)
+        print(name, "%.3g %.3g" % (err, split), flush=True)
+        assert err <= split, name
