@@ -27,6 +27,7 @@
 #pragma once
 
 #include "winos_kernel.h"
+#include "winow_deal.h"
 
 namespace convfwd {
 
@@ -116,11 +117,10 @@ __global__ __launch_bounds__(CFG::NT, 1) void winow_kernel(WinowArgs w)
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int C16 = (a.C + 15) >> 4, MBK = (a.K + 31) >> 5;
-    const int total = d.KT * d.TN, xcd = blockIdx.x & 7, mine = blockIdx.x >> 3;
-    const int first = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : (total & 7)), count = (total >> 3) + (xcd < (total & 7) ? 1 : 0);
-    const int wgs = ((int)gridDim.x >> 3) + (xcd < ((int)gridDim.x & 7) ? 1 : 0);
-    // Where the last round of an XCD's workgroups has tiles for no more than half of them, its tiles are halved
-    const int full = count - count % wgs, halved = 2 * (count - full) <= wgs, units = halved ? 2 * count - full : count;
+    const int mine = blockIdx.x >> 3;
+    const WinowShare share = winow_share(d.KT * d.TN, (int)gridDim.x, blockIdx.x & 7);
+    const int first = share.first, count = share.count, wgs = share.wgs, full = share.full, units = share.units;
+    const bool halved = share.halved;
     if (mine >= units) return;
     struct Place {
         int t0, m0, t1;  // first tile, first channel, behind the last tile
@@ -542,8 +542,7 @@ hipError_t winow_launch(const Variant&, ConvArgs& a, hipStream_t s)
                        (const float*)a.filt, (uint4*)a.ws, a.K, a.C);
     const hipError_t e2 = hipGetLastError();
     if (e2 != hipSuccess) return e2;
-    const int total = 2 * g.TN * g.KT;  // (halves of tiles: one workgroup per CU, 256 of them)
-    const dim3 grid((unsigned)(total > 256 ? 256 : total));
+    const dim3 grid((unsigned)winow_grid(g.TN * g.KT));
     if (even) hipLaunchKernelGGL((winow_kernel<CFG, true>), grid, dim3(CFG::NT), lds, s, w);
     else hipLaunchKernelGGL((winow_kernel<CFG, false>), grid, dim3(CFG::NT), lds, s, w);
     return hipGetLastError();
