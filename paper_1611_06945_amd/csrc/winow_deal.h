@@ -3,9 +3,9 @@
 
 namespace convfwd {
 
-// Workgroups of a launch: one per CU, and no more than two for each tile of the XCD with the most tiles, so that every XCD can halve its tiles
-// where they are few.  (Two for each tile of the launch were not enough: an XCD has the eighth of the tiles rounded up, and the eighth of
-// the workgroups rounded down; of the totals below 128 only multiples of eight were halved throughout.)
+// Workgroups of a launch: 256, one per CU, or two for each tile of the fullest XCD, so that every XCD can halve its tiles where they are few.
+// Two for each tile of the launch are not enough: an XCD's tiles may be an eighth rounded up and its workgroups an eighth rounded down
+// (of the numbers below 128 only multiples of eight are halved throughout).
 constexpr int winow_grid(int tiles) { return tiles > 120 ? 256 : 16 * ((tiles + 7) / 8); }
 
 struct WinowShare {

@@ -14,7 +14,9 @@
 //   * Between two MFMAs stand six vector instructions (a part of the next plane's operands, a row transform) or a load, in the
 //     order of the source: a lone wave has to find its own cover.
 //   * In the end a wave sums its row's columns, and the rows' sums meet in LDS in the wave that stores their channels.
-//   * Workgroups take tile after tile, one per CU; a last round with tiles for no more than half of the workgroups halves them.
+//   * Workgroups take tile after tile, one per CU; a last round with tiles for no more than half of the workgroups halves them (winow_deal.h).  us a
+//     call of fewer than 128 tiles, halved on XCDs that happened to have two workgroups for each -> on all: 17 of 13x13x256 -> 384 (84 tiles) 50.5 ->
+//     37.0, 27 of 28x28x128 -> 64 (83) 28.4 -> 20.7, 8 of 56x56x64 -> 64 (98) 20.7 -> 16.0, 19 of 28x28x128 -> 128 (118) 30.7 -> 23.3.
 // What bounds it: instruction issue.  A step is 96 MFMAs (3100 clocks) among 900 instructions, 4400 clocks; vector loads cost 25 to 30
 // clocks of issue each.  Per tile the epilogue takes 7700, addresses 2500, a workgroup's start 9000 once.  On the layer below the
 // clock falls to 1.94 GHz (2.23 with filters of zeros): the power limit is near.
