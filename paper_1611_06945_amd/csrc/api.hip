@@ -284,7 +284,7 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double slots = 256.0 * v.per_cu, full = std::floor(wgs / slots), rest = std::ceil((wgs - full * slots) / 256.0);
         const double rounds = full * std::pow((double)v.per_cu, (double)v.model.grow) + (rest > 0.0 ? std::pow(rest, (double)v.model.grow) : 0.0);
         const double pieces = std::ceil((double)sdir_positions(v.tn, d.N, d.R, d.stride, OH, OW) / v.slab_threads) * v.slab_threads / v.slab, share = d.R == 3 ? 0.4 : 0.2;
-        return (d.R == 5 ? 1.0 : 1.2) * (v.model.call + 1.2e-6 * d.K * Q + rounds * (v.model.own + chunks * v.model.chunk * (1.0 - share + share * pieces)));
+        return (d.R == 5 ? 1.0 : d.stride > 1 ? 1.2 : 1.1) * (v.model.call + 1.2e-6 * d.K * Q + rounds * (v.model.own + chunks * v.model.chunk * (1.0 - share + share * pieces)));
     }
     if (v.traits & TRAIT_SPLIT_PRODUCTS) {
         // Winograd on split products: the filter transform, then per round of workgroups a start, an inverse transform and a step per 16

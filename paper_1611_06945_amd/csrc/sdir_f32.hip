@@ -15,10 +15,10 @@ void register_sdir_f32(std::vector<Variant>& out)
     sdir_register<SdirCfg<3, 1, 1, 1, 8, 192>>(out, {4.45f, 1.50f, 4.492f, 0.4f});
     sdir_register<SdirCfg<5, 2, 1, 4, 1, 768>>(out, {5.24f, 1.79f, 7.363f, 0.8f});
     sdir_register<SdirCfg<5, 1, 1, 4, 1, 768>>(out, {5.38f, 0.88f, 4.269f, 0.8f});
-    sdir_register<SdirCfg<5, 2, 1, 2, 2, 384>>(out, {6.83f, 0.0f, 7.346f, 0.9f});
+    sdir_register<SdirCfg<5, 2, 1, 2, 2, 384>>(out, {7.08f, -0.12f, 7.356f, 0.9f});
     sdir_register<SdirCfg<5, 1, 1, 2, 2, 384>>(out, {6.28f, 0.08f, 4.338f, 0.9f});
     sdir_register<SdirCfg<5, 1, 1, 1, 4, 384>>(out, {5.02f, 1.08f, 5.309f, 0.4f});
-    sdir_register<SdirCfg<5, 1, 1, 1, 4, 192>>(out, {5.67f, 0.0f, 4.667f, 0.9f});
+    sdir_register<SdirCfg<5, 1, 1, 1, 4, 192>>(out, {6.22f, -0.23f, 4.696f, 0.9f});
     sdir_register<SdirCfg<5, 1, 1, 1, 8, 192>>(out, {4.23f, 0.90f, 8.355f, 0.4f});
 }
 

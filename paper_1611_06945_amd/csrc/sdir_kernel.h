@@ -6,11 +6,9 @@
 //   * Leading products and the five small ones have accumulators of their own: a sum is then rounded once for sixteen channels and tap.
 //     Error against 64 bits (2-norm, relative, half-normal inputs; six products in one accumulator -> here, the pick before): 20x20x352 ->
 //     64 5x5 14.5e-7 -> 5.8e-7, 8.0e-7; 16x16x88 -> 49 7.2e-7 -> 2.7e-7, 4.3e-7; 19x23x130 -> 64 3x3 stride 2 5.1e-7 -> 1.9e-7, 2.1e-7.
-//     Where a wave takes all channels, a chunk's leading sums are added to those before it: 3 images of 16x16x220 -> 160 5x5 4.5e-7 ->
-//     1.3e-7, 2 of 40x40x176 -> 16 3.7e-7 -> 1.2e-7 (the implicit GEMM split eight ways 4.7e-7, 3.6e-7), 29 of 44x44x304 -> 112 3x3 stride 2 3.3e-7 -> 1.1e-7
-//     (that one 3.5e-7), 20 of 13x13x256 -> 96 3x3 2.8e-7 -> 1.0e-7 (the fp32 window kernel split four ways 2.2e-7), for up to 1 % of the time where
-//     it is the fastest (17 of 33x33x416 -> 64 5x5 186.5 -> 188.2 us, 5 of 28x31x224 -> 256 107.1 -> 108.4, 48 of 63x66x128 -> 27 3x3 103.8 -> 104.7).  Waves that
-//     split the channels: 1.0e-7 to 5.2e-7.  Over 302 drawn layers whose untuned pick moved here the error is
+//     Where a wave takes all channels of a 5x5 layer, a chunk's leading sums are added to those before it: 3 images of 16x16x220 -> 160 4.5e-7 ->
+//     1.3e-7, 2 of 40x40x176 -> 16 3.7e-7 -> 1.2e-7 (the implicit GEMM split eight ways 4.7e-7, 3.6e-7), for 1 % of the time
+//     (17 of 33x33x416 -> 64 186.5 -> 188.2 us, 5 of 28x31x224 -> 256 107.1 -> 108.4).  Waves that split the channels: 1.2e-7 to 4.5e-7.  Over 302 drawn layers whose untuned pick moved here the error is
 //     0.45 of the former pick's (geometric mean; 0.96 at most).
 //   * A small kernel ahead splits the filters into MFMA operand order; fragments come from L2 straight into registers.
 //   * Input is read four bytes a lane (any row length, border and stride), split and stored as [part][eight channels][position], rows
@@ -86,66 +84,6 @@ __global__ __launch_bounds__(512) void sdir_filter_kernel(const float* __restric
         uint4* dst = U + (((size_t)c16 * RS + t) * gridDim.x + mb) * 192 + lane;
 #pragma unroll
         for (int q = 0; q < 3; ++q) dst[q * 64] = s.p[q];
-    }
-}
-
-// Four channels, k .. k + 3, of output pixel p for each lane in `mask`, summed in fp32 from the definition: taps outside the image are
-// left out.  The wave takes the lanes' pixels together, 64 / their number lanes (rounded down to a power of two) for each, which share its
-// channels; four sums share their input, a lane whose four sums are all NaN is done.  Bound by the loads of the few waves that have such
-// pixels.  us a call, a wave for each output -> here: 50 images of 14x14x424 -> 96 5x5 (122 on ordinary data) with one infinite pixel 5290 -> 713, one
-// NaN filter value 1100 -> 404, NaN everywhere 50500 -> 111, results beyond 2^79 everywhere 49500 -> 2280; 13 of 35x33x112 -> 352 3x3 stride 2
-// (40) 244 -> 69, 133 -> 74, 6190 -> 52, 6190 -> 511.
-template <int R>
-__device__ __forceinline__ void sdir_sum_again(const ConvArgs& a, int lane, uint64_t mask, int k, int p, float* y)
-{
-    constexpr int RS = R * R;
-    constexpr uint32_t kFar = 0x80000000u;
-    const int count = __builtin_popcountll(mask), lg = 31 - __builtin_clz(64 / count), step = 1 << lg, entry = lane >> lg;
-    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-    const bool mine = (mask >> lane) & 1;
-    // (lanes outside the mask push to the last lane, which no entry reads when there are any)
-    const int owners = __builtin_amdgcn_ds_permute((mine ? rank : 63) * 4, lane);
-    const int owner = __shfl(owners, entry < count ? entry : 0);
-    k = __shfl(k, owner);
-    p = __shfl(p, owner);
-    uint32_t n, pix, oy, ox;
-    a.dOHW.divmod((uint32_t)p, n, pix);
-    a.dOW.divmod(pix, oy, ox);
-    const int iy = (int)oy * a.stride - a.pad, ix = (int)ox * a.stride - a.pad;
-    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes), rf = make_rsrc(a.filt, a.filt_bytes);
-    const int origin = (int)n * a.C * a.HW + iy * a.W + ix;
-    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int c = lane & (step - 1); entry < count && c < a.C; c += step) {
-        const int at = origin + c * a.HW;
-        bool in[RS];
-        float x[RS];
-#pragma unroll
-        for (int t = 0; t < RS; ++t) {
-            in[t] = (unsigned)(iy + t / R) < (unsigned)a.H && (unsigned)(ix + t % R) < (unsigned)a.W;
-            x[t] = buffer_load_elem<float>(rin, in[t] ? (uint32_t)(at + t / R * a.W + t % R) * 4u : kFar);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {  // (a filter past the last one is not stored, and not read beyond the tensor)
-            const uint32_t fo = (uint32_t)((k + q) * a.C + c) * (RS * 4u);
-            float f[RS];
-#pragma unroll
-            for (int t = 0; t < RS - 1; t += 4) {
-                const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, (int)(fo + t * 4u), 0, 0));
-                f[t] = v[0], f[t + 1] = v[1], f[t + 2] = v[2], f[t + 3] = v[3];
-            }
-            f[RS - 1] = buffer_load_elem<float>(rf, fo + (RS - 1) * 4u);
-#pragma unroll
-            for (int t = 0; t < RS; ++t) s[q] = in[t] ? __builtin_fmaf(x[t], f[t], s[q]) : s[q];
-        }
-        if (s[0] != s[0] && s[1] != s[1] && s[2] != s[2] && s[3] != s[3]) break;
-    }
-    for (int o = step >> 1; o > 0; o >>= 1)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], o);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const float total = __shfl(s[q], rank << lg & 63);
-        y[q] = mine ? total : y[q];
     }
 }
 
@@ -255,9 +193,9 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
     }
 
     // The leading products and the five small ones have sums of their own: a sum is rounded once for sixteen channels and tap, not six times.
-    // A wave that takes all channels adds a chunk's leading sums to those of the chunks before: the chain of roundings is 9 or 25
+    // At 5x5, a wave that takes all channels adds a chunk's leading sums to those of the chunks before: the chain of roundings is 25
     // long, then one for each chunk
-    constexpr bool FOLD = WK == 1;
+    constexpr bool FOLD = R == 5 && WK == 1;
     typename mma_t::acc_t acc[MBW][NBW], low[MBW][NBW], done[MBW][NBW];
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb)
@@ -395,23 +333,31 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
         }
     }
     if (__any(bad != 0)) {
+        // each again from the definition, a lane's share of the channels each
 #pragma unroll 1
-        for (int j = 0; j < QW; ++j) {
-            const int q = wk * QW + j, k = m0 + q / 4 / NBW * 32 + q % 4 * 8 + 4 * g, p = p0 + (wn * NBW + q / 4 % NBW) * 32 + li;
-            const uint32_t mine = (uint32_t)(bad >> 4 * j) & 15u;
-            const uint64_t again = __ballot(mine && k < a.K && p < a.P);
-            if (!again) continue;
-            float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            sdir_sum_again<R>(a, lane, again, k, p, s);
-            uint32_t n, pix;
-            a.dOHW.divmod(p < a.P ? (uint32_t)p : 0u, n, pix);
-            const uint32_t o = (uint32_t)((int)n * a.K * a.OHW + (int)pix) * 4u;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const bool store = (mine >> r & 1) && k + r < a.K && p < a.P;
-                s[r] += a.bias && store ? a.bias[k + r] : 0.0f;
-                if (a.relu) s[r] = s[r] > 0.0f ? s[r] : 0.0f;
-                buffer_store_elem<float>(s[r], rout, store ? o + (uint32_t)(k + r) * plane : kFar);
+        for (int e = 0; e < 4 * QW; ++e) {
+            const int q = wk * QW + (e >> 2), k_ = m0 + q / 4 / NBW * 32 + q % 4 * 8 + 4 * g + (e & 3), p_ = p0 + (wn * NBW + q / 4 % NBW) * 32 + li;
+            uint64_t left = __ballot((bad >> e & 1) && k_ < a.K && p_ < a.P);
+            while (left) {
+                const int src = __builtin_ctzll(left);
+                left &= left - 1;
+                const int k = __shfl(k_, src), p = __shfl(p_, src);
+                uint32_t n, pix, oy, ox;
+                a.dOHW.divmod((uint32_t)p, n, pix);
+                a.dOW.divmod(pix, oy, ox);
+                float s = 0.0f;
+                for (int c = lane; c < a.C; c += 64)
+                    for (int t = 0; t < RS; ++t) {
+                        const int iy = (int)oy * a.stride - a.pad + t / R, ix = (int)ox * a.stride - a.pad + t % R;
+                        if ((unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W)
+                            s = __builtin_fmaf(((const float*)a.in)[((size_t)((int)n * a.C + c) * a.H + iy) * a.W + ix], ((const float*)a.filt)[((size_t)k * a.C + c) * RS + t], s);
+                    }
+                for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+                if (lane == src) {
+                    s += a.bias ? a.bias[k] : 0.0f;
+                    if (a.relu) s = s > 0.0f ? s : 0.0f;
+                    ((float*)a.out)[(size_t)((int)n * a.K + k) * a.OHW + pix] = s;
+                }
             }
         }
     }
@@ -456,8 +402,7 @@ bool sdir_valid(const Variant&, const conv_desc& d, int OH, int OW)
     if ((long long)sdir_filter_bytes(d.K, d.C, CFG::RS) + (long long)CFG::WK * CFG::RS * 3072 * ((d.K + 31) / 32) >= lim || (d.C + 15) / 16 > 65535) return false;
     if ((long long)d.N * ((OH - 1LL) * d.stride + CFG::R) >= (1LL << 30) || (long long)d.N * OH * OW + CFG::TN >= (1LL << 30)) return false;
     if (sdir_positions(CFG::TN, d.N, CFG::R, d.stride, OH, OW) > CFG::POS) return false;
-    // (a launch holds fewer than 2^32 threads)
-    return (long long)((d.K + CFG::TM - 1) / CFG::TM) * (((long long)d.N * OH * OW + CFG::TN - 1) / CFG::TN) * CFG::NT < (1LL << 32);
+    return (long long)((d.K + CFG::TM - 1) / CFG::TM) * (((long long)d.N * OH * OW + CFG::TN - 1) / CFG::TN) < (1LL << 30);
 }
 
 template <class CFG>
