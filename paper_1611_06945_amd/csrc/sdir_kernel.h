@@ -87,6 +87,66 @@ __global__ __launch_bounds__(512) void sdir_filter_kernel(const float* __restric
     }
 }
 
+// Four channels, k .. k + 3, of output pixel p for each lane in `mask`, summed in fp32 from the definition: taps outside the image are
+// left out.  The wave takes the lanes' pixels together, 64 / their number lanes (rounded down to a power of two) for each, which share its
+// channels; four sums share their input, a lane whose four sums are all NaN is done.  Bound by the loads of the few waves that have such
+// pixels.  us a call, a wave for each output -> here: 50 images of 14x14x424 -> 96 5x5 (122 on ordinary data) with one infinite pixel 5290 -> 713, one
+// NaN filter value 1100 -> 404, NaN everywhere 50500 -> 111, results beyond 2^79 everywhere 49500 -> 2280; 13 of 35x33x112 -> 352 3x3 stride 2
+// (40) 244 -> 69, 133 -> 74, 6190 -> 52, 6190 -> 511.
+template <int R>
+__device__ __forceinline__ void sdir_sum_again(const ConvArgs& a, int lane, uint64_t mask, int k, int p, float* y)
+{
+    constexpr int RS = R * R;
+    constexpr uint32_t kFar = 0x80000000u;
+    const int count = __builtin_popcountll(mask), lg = 31 - __builtin_clz(64 / count), step = 1 << lg, entry = lane >> lg;
+    const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    const bool mine = (mask >> lane) & 1;
+    // (lanes outside the mask push to the last lane, which no entry reads when there are any)
+    const int owners = __builtin_amdgcn_ds_permute((mine ? rank : 63) * 4, lane);
+    const int owner = __shfl(owners, entry < count ? entry : 0);
+    k = __shfl(k, owner);
+    p = __shfl(p, owner);
+    uint32_t n, pix, oy, ox;
+    a.dOHW.divmod((uint32_t)p, n, pix);
+    a.dOW.divmod(pix, oy, ox);
+    const int iy = (int)oy * a.stride - a.pad, ix = (int)ox * a.stride - a.pad;
+    const __amdgpu_buffer_rsrc_t rin = make_rsrc(a.in, a.in_bytes), rf = make_rsrc(a.filt, a.filt_bytes);
+    const int origin = (int)n * a.C * a.HW + iy * a.W + ix;
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int c = lane & (step - 1); entry < count && c < a.C; c += step) {
+        const int at = origin + c * a.HW;
+        bool in[RS];
+        float x[RS];
+#pragma unroll
+        for (int t = 0; t < RS; ++t) {
+            in[t] = (unsigned)(iy + t / R) < (unsigned)a.H && (unsigned)(ix + t % R) < (unsigned)a.W;
+            x[t] = buffer_load_elem<float>(rin, in[t] ? (uint32_t)(at + t / R * a.W + t % R) * 4u : kFar);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {  // (a filter past the last one is not stored, and not read beyond the tensor)
+            const uint32_t fo = (uint32_t)((k + q) * a.C + c) * (RS * 4u);
+            float f[RS];
+#pragma unroll
+            for (int t = 0; t < RS - 1; t += 4) {
+                const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rf, (int)(fo + t * 4u), 0, 0));
+                f[t] = v[0], f[t + 1] = v[1], f[t + 2] = v[2], f[t + 3] = v[3];
+            }
+            f[RS - 1] = buffer_load_elem<float>(rf, fo + (RS - 1) * 4u);
+#pragma unroll
+            for (int t = 0; t < RS; ++t) s[q] = in[t] ? __builtin_fmaf(x[t], f[t], s[q]) : s[q];
+        }
+        if (s[0] != s[0] && s[1] != s[1] && s[2] != s[2] && s[3] != s[3]) break;
+    }
+    for (int o = step >> 1; o > 0; o >>= 1)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] += __shfl_xor(s[q], o);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float total = __shfl(s[q], rank << lg & 63);
+        y[q] = mine ? total : y[q];
+    }
+}
+
 template <class CFG>
 __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d)
 {
@@ -333,31 +393,23 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
         }
     }
     if (__any(bad != 0)) {
-        // each again from the definition, a lane's share of the channels each
 #pragma unroll 1
-        for (int e = 0; e < 4 * QW; ++e) {
-            const int q = wk * QW + (e >> 2), k_ = m0 + q / 4 / NBW * 32 + q % 4 * 8 + 4 * g + (e & 3), p_ = p0 + (wn * NBW + q / 4 % NBW) * 32 + li;
-            uint64_t left = __ballot((bad >> e & 1) && k_ < a.K && p_ < a.P);
-            while (left) {
-                const int src = __builtin_ctzll(left);
-                left &= left - 1;
-                const int k = __shfl(k_, src), p = __shfl(p_, src);
-                uint32_t n, pix, oy, ox;
-                a.dOHW.divmod((uint32_t)p, n, pix);
-                a.dOW.divmod(pix, oy, ox);
-                float s = 0.0f;
-                for (int c = lane; c < a.C; c += 64)
-                    for (int t = 0; t < RS; ++t) {
-                        const int iy = (int)oy * a.stride - a.pad + t / R, ix = (int)ox * a.stride - a.pad + t % R;
-                        if ((unsigned)iy < (unsigned)a.H && (unsigned)ix < (unsigned)a.W)
-                            s = __builtin_fmaf(((const float*)a.in)[((size_t)((int)n * a.C + c) * a.H + iy) * a.W + ix], ((const float*)a.filt)[((size_t)k * a.C + c) * RS + t], s);
-                    }
-                for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-                if (lane == src) {
-                    s += a.bias ? a.bias[k] : 0.0f;
-                    if (a.relu) s = s > 0.0f ? s : 0.0f;
-                    ((float*)a.out)[(size_t)((int)n * a.K + k) * a.OHW + pix] = s;
-                }
+        for (int j = 0; j < QW; ++j) {
+            const int q = wk * QW + j, k = m0 + q / 4 / NBW * 32 + q % 4 * 8 + 4 * g, p = p0 + (wn * NBW + q / 4 % NBW) * 32 + li;
+            const uint32_t mine = (uint32_t)(bad >> 4 * j) & 15u;
+            const uint64_t again = __ballot(mine && k < a.K && p < a.P);
+            if (!again) continue;
+            float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            sdir_sum_again<R>(a, lane, again, k, p, s);
+            uint32_t n, pix;
+            a.dOHW.divmod(p < a.P ? (uint32_t)p : 0u, n, pix);
+            const uint32_t o = (uint32_t)((int)n * a.K * a.OHW + (int)pix) * 4u;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool store = (mine >> r & 1) && k + r < a.K && p < a.P;
+                s[r] += a.bias && store ? a.bias[k + r] : 0.0f;
+                if (a.relu) s[r] = s[r] > 0.0f ? s[r] : 0.0f;
+                buffer_store_elem<float>(s[r], rout, store ? o + (uint32_t)(k + r) * plane : kFar);
             }
         }
     }

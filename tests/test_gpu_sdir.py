@@ -5,10 +5,11 @@ import numpy as np
 import pytest
 
 import oracle
+from paper_1611_06945_amd import binding as B
 from paper_1611_06945_amd import workloads as wl
 from paper_1611_06945_amd.workloads import ConvShape
 
-from gpu_util import TOL, DeviceCase, to_host_f64
+from gpu_util import TOL, DeviceCase, empty_out, to_host_f64, torch_mod
 from test_gpu_parity import assert_bit_exact, int_case, random_case
 
 pytestmark = pytest.mark.gpu
@@ -107,3 +108,31 @@ def test_no_less_precise_than_the_split_gemm_it_replaces(shape):
         err = error(vi)
         print(name, "%.3g %.3g" % (err, split), flush=True)
         assert err <= split, name
+
+
+# The largest time allowed, in calls on ordinary data; measured with a wave for each output and with pixels that share a wave
+@pytest.mark.parametrize("kind,limit", [("one infinity", 20), ("NaN everywhere", 5), ("beyond the range", 60)])  # 43, 6; 410, 0.9; 400, 18
+def test_data_that_is_not_finite_takes_a_few_calls_time(kind, limit):
+    torch = torch_mod()
+    shape = ConvShape(50, 424, 14, 14, 96, 5, 5, 1, 2)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4690)
+    x = torch.randn(shape.in_shape(), generator=g, device="cuda").abs_()
+    f = torch.randn(shape.filt_shape(), generator=g, device="cuda").mul_(wl.he_sigma(shape))
+    desc = B.desc_of(shape, wl.F32, relu=True)
+    assert B.conv_variant_name(desc, -1).startswith("sdir_")
+    out, ws = empty_out(shape.out_shape(), wl.F32), torch.empty(B.conv_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+
+    def us():
+        return min(B.conv_time_us(desc, x, f, None, out, ws, ws.numel(), launches=3) for _ in range(3))
+
+    plain = us()
+    if kind == "one infinity":
+        x[7, 100, 6, 6] = float("inf")
+    elif kind == "NaN everywhere":
+        x.fill_(float("nan"))
+    else:
+        x.mul_(1e26)  # finite, every sum beyond what the scaled products can hold
+    special = us()
+    print("%s: %.0f us, %.0f on ordinary data" % (kind, special, plain), flush=True)
+    assert special <= limit * plain
