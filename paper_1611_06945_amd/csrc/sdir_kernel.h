@@ -454,7 +454,8 @@ bool sdir_valid(const Variant&, const conv_desc& d, int OH, int OW)
     if ((long long)sdir_filter_bytes(d.K, d.C, CFG::RS) + (long long)CFG::WK * CFG::RS * 3072 * ((d.K + 31) / 32) >= lim || (d.C + 15) / 16 > 65535) return false;
     if ((long long)d.N * ((OH - 1LL) * d.stride + CFG::R) >= (1LL << 30) || (long long)d.N * OH * OW + CFG::TN >= (1LL << 30)) return false;
     if (sdir_positions(CFG::TN, d.N, CFG::R, d.stride, OH, OW) > CFG::POS) return false;
-    return (long long)((d.K + CFG::TM - 1) / CFG::TM) * (((long long)d.N * OH * OW + CFG::TN - 1) / CFG::TN) < (1LL << 30);
+    // (a launch holds fewer than 2^32 threads)
+    return (long long)((d.K + CFG::TM - 1) / CFG::TM) * (((long long)d.N * OH * OW + CFG::TN - 1) / CFG::TN) * CFG::NT < (1LL << 32);
 }
 
 template <class CFG>
