@@ -14,7 +14,9 @@
 //   * Between two MFMAs stand six vector instructions (a part of the next plane's operands, a row transform) or a load, in the
 //     order of the source: a lone wave has to find its own cover.
 //   * In the end a wave sums its row's columns, and the rows' sums meet in LDS in the wave that stores their channels.
-//   * Workgroups take tile after tile, one per CU; a last round with tiles for no more than half of the workgroups halves them.
+//   * Workgroups take tile after tile, one per CU; a last round with tiles for no more than half of the workgroups halves them (winow_deal.h).  us a
+//     call of fewer than 128 tiles, halved on XCDs that happened to have two workgroups for each -> on all: 17 of 13x13x256 -> 384 (84 tiles) 50.5 ->
+//     37.0, 27 of 28x28x128 -> 64 (83) 28.4 -> 20.7, 8 of 56x56x64 -> 64 (98) 20.7 -> 16.0, 19 of 28x28x128 -> 128 (118) 30.7 -> 23.3.
 // What bounds it: instruction issue.  A step is 96 MFMAs (3100 clocks) among 900 instructions, 4400 clocks; vector loads cost 25 to 30
 // clocks of issue each.  Per tile the epilogue takes 7700, addresses 2500, a workgroup's start 9000 once.  On the layer below the
 // clock falls to 1.94 GHz (2.23 with filters of zeros): the power limit is near.
@@ -27,6 +29,7 @@
 #pragma once
 
 #include "winos_kernel.h"
+#include "winow_deal.h"
 
 namespace convfwd {
 
@@ -116,11 +119,10 @@ __global__ __launch_bounds__(CFG::NT, 1) void winow_kernel(WinowArgs w)
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, g = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int C16 = (a.C + 15) >> 4, MBK = (a.K + 31) >> 5;
-    const int total = d.KT * d.TN, xcd = blockIdx.x & 7, mine = blockIdx.x >> 3;
-    const int first = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : (total & 7)), count = (total >> 3) + (xcd < (total & 7) ? 1 : 0);
-    const int wgs = ((int)gridDim.x >> 3) + (xcd < ((int)gridDim.x & 7) ? 1 : 0);
-    // Where the last round of an XCD's workgroups has tiles for no more than half of them, its tiles are halved
-    const int full = count - count % wgs, halved = 2 * (count - full) <= wgs, units = halved ? 2 * count - full : count;
+    const int mine = blockIdx.x >> 3;
+    const WinowShare share = winow_share(d.KT * d.TN, (int)gridDim.x, blockIdx.x & 7);
+    const int first = share.first, count = share.count, wgs = share.wgs, full = share.full, units = share.units;
+    const bool halved = share.halved;
     if (mine >= units) return;
     struct Place {
         int t0, m0, t1;  // first tile, first channel, behind the last tile
@@ -542,8 +544,7 @@ hipError_t winow_launch(const Variant&, ConvArgs& a, hipStream_t s)
                        (const float*)a.filt, (uint4*)a.ws, a.K, a.C);
     const hipError_t e2 = hipGetLastError();
     if (e2 != hipSuccess) return e2;
-    const int total = 2 * g.TN * g.KT;  // (halves of tiles: one workgroup per CU, 256 of them)
-    const dim3 grid((unsigned)(total > 256 ? 256 : total));
+    const dim3 grid((unsigned)winow_grid(g.TN * g.KT));
     if (even) hipLaunchKernelGGL((winow_kernel<CFG, true>), grid, dim3(CFG::NT), lds, s, w);
     else hipLaunchKernelGGL((winow_kernel<CFG, false>), grid, dim3(CFG::NT), lds, s, w);
     return hipGetLastError();

@@ -1,9 +1,56 @@
-"""Host side of the fp32 window kernels on split products (CPU only): which layers they accept at the upper end of the library's range."""
+"""Host side of the fp32 window kernels on split products (CPU only): how the row-of-planes Winograd kernel deals its tiles, and which
+layers either kernel accepts at the upper end of the library's range."""
+import subprocess
+
 import pytest
 
 from paper_1611_06945_amd import binding as B
+from paper_1611_06945_amd import build
 from paper_1611_06945_amd import workloads as wl
 from paper_1611_06945_amd.workloads import ConvShape
+
+DEAL = r"""
+#include <cstdio>
+#include <vector>
+#include "winow_deal.h"
+using namespace convfwd;
+
+// longest chain of a workgroup in halves of a tile, every tile done once (a whole, or its two halves); -1 where that does not hold
+static int chain(int tiles)
+{
+    const int grid = winow_grid(tiles);
+    std::vector<int> done(2 * tiles, 0);
+    int longest = 0;
+    if (grid < 1 || grid > 256) return -1;
+    for (int b = 0; b < grid; ++b) {
+        const WinowShare s = winow_share(tiles, grid, b & 7);
+        int q = b >> 3, mine = 0;
+        const int whole = s.halved ? s.full : s.count;
+        for (; q < whole; q += s.wgs, mine += 2) ++done[2 * (s.first + q)], ++done[2 * (s.first + q) + 1];
+        if (q < s.units) ++done[2 * s.first + s.full + q], ++mine;
+        if (mine > longest) longest = mine;
+    }
+    for (int n : done) if (n != 1) return -1;
+    return longest;
+}
+
+int main()
+{
+    for (int t = 1; t <= 4100; ++t) printf("%d\n", chain(t));
+}
+"""
+
+
+def test_few_tiles_are_halved_on_every_xcd(tmp_path):
+    """A last round of at most 128 tiles is of halves, whatever their number, as the ratings have it; ahead of it 256 a round."""
+    src, exe = tmp_path / "deal.cpp", tmp_path / "deal"
+    src.write_text(DEAL)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-I", build.CSRC, "-o", str(exe), str(src)])
+    chains = [int(x) for x in subprocess.check_output([str(exe)], text=True).split()]
+    for tiles, halves in enumerate(chains, 1):
+        rest = tiles % 256
+        assert halves == 2 * (tiles // 256) + (0 if rest == 0 else 1 if rest <= 128 else 2), (tiles, halves)
+
 
 def names_of(shape):
     d = B.desc_of(shape, wl.F32, relu=True)
