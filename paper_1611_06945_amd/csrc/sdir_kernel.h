@@ -6,9 +6,11 @@
 //   * Leading products and the five small ones have accumulators of their own: a sum is then rounded once for sixteen channels and tap.
 //     Error against 64 bits (2-norm, relative, half-normal inputs; six products in one accumulator -> here, the pick before): 20x20x352 ->
 //     64 5x5 14.5e-7 -> 5.8e-7, 8.0e-7; 16x16x88 -> 49 7.2e-7 -> 2.7e-7, 4.3e-7; 19x23x130 -> 64 3x3 stride 2 5.1e-7 -> 1.9e-7, 2.1e-7.
-//     Where a wave takes all channels of a 5x5 layer, a chunk's leading sums are added to those before it: 3 images of 16x16x220 -> 160 4.5e-7 ->
-//     1.3e-7, 2 of 40x40x176 -> 16 3.7e-7 -> 1.2e-7 (the implicit GEMM split eight ways 4.7e-7, 3.6e-7), for 1 % of the time
-//     (17 of 33x33x416 -> 64 186.5 -> 188.2 us, 5 of 28x31x224 -> 256 107.1 -> 108.4).  Waves that split the channels: 1.2e-7 to 4.5e-7.  Over 302 drawn layers whose untuned pick moved here the error is
+//     Where a wave takes all channels, a chunk's leading sums are added to those before it: 3 images of 16x16x220 -> 160 5x5 4.5e-7 ->
+//     1.3e-7, 2 of 40x40x176 -> 16 3.7e-7 -> 1.2e-7 (the implicit GEMM split eight ways 4.7e-7, 3.6e-7), 29 of 44x44x304 -> 112 3x3 stride 2 3.3e-7 -> 1.1e-7
+//     (that one 3.5e-7), 20 of 13x13x256 -> 96 3x3 2.8e-7 -> 1.0e-7 (the fp32 window kernel split four ways 2.2e-7), for up to 1 % of the time where
+//     it is the fastest (17 of 33x33x416 -> 64 5x5 186.5 -> 188.2 us, 5 of 28x31x224 -> 256 107.1 -> 108.4, 48 of 63x66x128 -> 27 3x3 103.8 -> 104.7).  Waves that
+//     split the channels: 1.0e-7 to 5.2e-7.  Over 302 drawn layers whose untuned pick moved here the error is
 //     0.45 of the former pick's (geometric mean; 0.96 at most).
 //   * A small kernel ahead splits the filters into MFMA operand order; fragments come from L2 straight into registers.
 //   * Input is read four bytes a lane (any row length, border and stride), split and stored as [part][eight channels][position], rows
@@ -253,9 +255,9 @@ __global__ __launch_bounds__(CFG::NT, 2) void sdir_kernel(ConvArgs a, SdirGeom d
     }
 
     // The leading products and the five small ones have sums of their own: a sum is rounded once for sixteen channels and tap, not six times.
-    // At 5x5, a wave that takes all channels adds a chunk's leading sums to those of the chunks before: the chain of roundings is 25
+    // A wave that takes all channels adds a chunk's leading sums to those of the chunks before: the chain of roundings is 9 or 25
     // long, then one for each chunk
-    constexpr bool FOLD = R == 5 && WK == 1;
+    constexpr bool FOLD = WK == 1;
     typename mma_t::acc_t acc[MBW][NBW], low[MBW][NBW], done[MBW][NBW];
 #pragma unroll
     for (int mb = 0; mb < MBW; ++mb)

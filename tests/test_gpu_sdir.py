@@ -110,6 +110,24 @@ def test_no_less_precise_than_the_split_gemm_it_replaces(shape):
         assert err <= split, name
 
 
+@pytest.mark.parametrize("shape", [ConvShape(20, 256, 13, 13, 96, 3, 3, 1, 1), ConvShape(6, 256, 15, 15, 48, 3, 3, 1, 1)])
+def test_no_less_precise_than_the_split_window_kernel_it_replaces(shape):
+    """... and at 3x3 beside the fp32 window kernel that splits the reduction over four workgroups: 2.2e-7 in the first layer, one chain over all
+    channels and taps 2.8e-7."""
+    data = {"in": wl.draw(("halfnormal", 1.0), shape.in_shape(), 4688).astype(np.float32),
+            "filt": wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), 4689).astype(np.float32), "bias": np.zeros(shape.K, np.float32)}
+    case = DeviceCase(shape, wl.F32, data, relu=False)
+
+    def error(vi):
+        return np.linalg.norm(to_host_f64(case.run(variant=vi), wl.F32) - case.ref()) / np.linalg.norm(case.ref())
+
+    split = min(error(i) for i, n in enumerate(case.variant_names()) if n.startswith("wconv_") and n.endswith("_sk4"))
+    for vi, name in variants_of(case):
+        err = error(vi)
+        print(name, "%.3g %.3g" % (err, split), flush=True)
+        assert err <= split, name
+
+
 # The largest time allowed, in calls on ordinary data; measured with a wave for each output and with pixels that share a wave
 @pytest.mark.parametrize("kind,limit", [("one infinity", 20), ("NaN everywhere", 5), ("beyond the range", 60)])  # 43, 6; 410, 0.9; 400, 18
 def test_data_that_is_not_finite_takes_a_few_calls_time(kind, limit):
