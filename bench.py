@@ -53,22 +53,32 @@ TOL = {"f32": 1e-5, "f16": 5e-3, "bf16": 5e-3}   # max normalised error allowed 
 
 
 def executed_mfma_flops(variant, shape):
-    """FLOPs the matrix units execute per call: the direct count, except for the Winograd variants, which multiply
-    2.25x less (on tiles padded to the workgroup shape), winos_* as six bf16 partial products each."""
+    """FLOPs the matrix units execute per call: the direct count, except for the Winograd variants, which multiply 2.25x less, and
+    for the kernels on split products (winos_*, sdir_*, swins_*), whose fp32 products are six bf16 partial products each; both on tiles
+    padded to the workgroup shape, the latter on whole MFMA steps of 16 reduction elements too."""
     import re
 
+    def up(n, step):
+        return -(-n // step) * step
+
     m = re.match(r"winos?_f32_M(\d+)T(\d+)_", variant)
-    if not m:
-        return float(shape.flops)
-    tm, tt = int(m.group(1)), int(m.group(2))
-    tiles = shape.N * ((shape.OH + 1) // 2) * ((shape.OW + 1) // 2)
-    once = 2.0 * 16 * (-(-shape.K // tm) * tm) * (-(-tiles // tt) * tt) * shape.C
-    return 6.0 * once if variant.startswith("winos_") else once
+    if m:
+        split, tiles = variant.startswith("winos_"), shape.N * ((shape.OH + 1) // 2) * ((shape.OW + 1) // 2)
+        once = 2.0 * 16 * up(shape.K, int(m.group(1))) * up(tiles, int(m.group(2))) * (up(shape.C, 16) if split else shape.C)
+        return 6.0 * once if split else once
+    m = re.match(r"sdir_f32_\d+x\d+_M(\d+)N(\d+)_", variant)
+    if m:
+        return 12.0 * up(shape.K, int(m.group(1))) * up(shape.N * shape.OH * shape.OW, int(m.group(2))) * up(shape.C, 16) * shape.R * shape.S
+    m = re.match(r"swins_f32_\d+x\d+s\d+_c3_M(\d+)N(\d+)", variant)
+    if m:  # lines of four taps, four of them a step (two lanes' halves each)
+        steps = ((3 * shape.R + 1) // 2 * ((shape.S + 3) // 4) + 1) // 2
+        return 12.0 * up(shape.K, int(m.group(1))) * shape.N * up(shape.OH * shape.OW, int(m.group(2))) * 16 * steps
+    return float(shape.flops)
 
 
 def mfma_dtype(variant, dt):
     """The type whose matrix rate bounds a variant: that of the storage, except for fp32 products made of bf16 parts."""
-    return "bf16" if variant.startswith("winos_") else dt
+    return "bf16" if variant.startswith(("winos_", "sdir_", "swins_")) else dt
 
 
 class Resident:
@@ -460,7 +470,7 @@ def sweep_appendix_a(batch, dtype, table_out=None, launches=100, batches=5):
                     "n_variants": n})
         executed = executed_mfma_flops(chosen, w.shape)
         if ops[-1]["bound"] == "mfma" and executed != w.shape.flops:
-            # a Winograd variant: the fraction of the MFMA peak counts the FLOPs the matrix units execute (never above 1);
+            # a Winograd variant, or one on split products: the fraction of the MFMA peak counts the FLOPs the matrix units execute (never above 1);
             # the rate by the direct definition's FLOP count stays in `gflops` and `effective_frac_direct_flops`
             ops[-1]["effective_frac_direct_flops"] = ops[-1]["frac_roofline"]
             ops[-1]["frac_roofline"] = round(executed / (PEAK_TFLOPS[mfma_dtype(chosen, dt)] * 1e12) / (med * 1e-3), 5)
@@ -502,8 +512,9 @@ def sweep_appendix_a(batch, dtype, table_out=None, launches=100, batches=5):
             fh.write("ms: per launch, device events around batches of launches issued by the library (conv_time_us; median); "
                      "tuner us: the same variant as timed by the autotuner; one-variant us: the single variant valid on "
                      "every operation with the smallest total, timed the same way; gain = one-variant / tuner.  GFLOP and "
-                     "GFLOP/s count the FLOPs of the direct definition; for a Winograd variant (wino_*) the fraction of the roofline "
-                     "counts the FLOPs its matrix instructions execute (2.25x fewer).\n\n")
+                     "GFLOP/s count the FLOPs of the direct definition; for a Winograd variant (wino_*, winos_*) and for one on split "
+                     "products (winos_*, sdir_*, swins_*) the fraction of the roofline counts the FLOPs its matrix instructions execute "
+                     "(2.25x fewer; six bf16 products for one, against the bf16 peak).\n\n")
             fh.write("| # | operation (KSZ,S,OC, in -> out) | GFLOP | variant | ms | tuner us | GFLOP/s | bound | frac of roofline | one-variant us | gain |\n")
             fh.write("|---|---|---|---|---|---|---|---|---|---|---|\n")
             for i, o in enumerate(ops):
@@ -707,7 +718,7 @@ def main():
         if direct:
             t_us, nm = min(direct)
             roof["best_direct"] = {"variant": nm, "tuner_us": round(t_us, 2),
-                                   "frac": round(sh.flops / (t_us * 1e-6) / 1e12 / PEAK_TFLOPS[dt], 5)}
+                                   "frac": round(executed_mfma_flops(nm, sh) / (t_us * 1e-6) / 1e12 / PEAK_TFLOPS[mfma_dtype(nm, dt)], 5)}
 
     out = {
         "metric": "conv_fwd_gflops", "value": round(gflops, 1), "unit": "GFLOP/s", "n_gpus": 1,

@@ -1,5 +1,5 @@
-"""Host side of the fp32 window kernels on split products (CPU only): how the row-of-planes Winograd kernel deals its tiles, and which
-layers either kernel accepts at the upper end of the library's range."""
+"""Host side of the fp32 window kernels on split products (CPU only): how the row-of-planes Winograd kernel deals its tiles, which layers
+either kernel accepts at the upper end of the library's range, and what the benchmark rates kernels on split products by."""
 import subprocess
 
 import pytest
@@ -86,3 +86,17 @@ def test_outputs_stay_below_2_gib_with_the_spare_channels_of_a_tile(prefix, spar
     most = (((1 << 31) - 1) // (4 * H * H) - spare) // K
     assert forms(ConvShape(most, 8, H, H, K, R, R, 1, R // 2), prefix)
     assert not forms(ConvShape(most + 1, 8, H, H, K, R, R, 1, R // 2), prefix) and names_of(ConvShape(most + 1, 8, H, H, K, R, R, 1, R // 2))
+
+
+@pytest.mark.parametrize("variant,shape,executed", [
+    ("sdir_f32_5x5_M32N64_w2k2_s384", ConvShape(50, 424, 14, 14, 96, 5, 5, 1, 2), 12.0 * 96 * 9856 * 432 * 25),
+    ("sdir_f32_3x3_M64N128_w4k1_s768", ConvShape(13, 112, 35, 33, 352, 3, 3, 2, 1), 12.0 * 384 * 4096 * 112 * 9),
+    ("swins_f32_11x11s4_c3_M96N256", ConvShape(20, 3, 227, 227, 96, 11, 11, 4, 0), 12.0 * 96 * 20 * 3072 * 416),
+    ("swins_f32_7x7s2_c3_M64N256", ConvShape(20, 3, 224, 224, 64, 7, 7, 2, 3), 12.0 * 64 * 20 * 12544 * 176),
+    ("winos_f32_M64T64_p768", ConvShape(64, 64, 56, 56, 192, 3, 3, 1, 1), 12.0 * 16 * 192 * 50176 * 64),
+])
+def test_bench_rates_split_products_as_six_bf16_products(variant, shape, executed):
+    import bench
+
+    assert variant in names_of(shape)
+    assert bench.executed_mfma_flops(variant, shape) == executed and bench.mfma_dtype(variant, "f32") == "bf16"
