@@ -42,6 +42,9 @@ LARGE = [
     (ConvShape(8, 64, 1020, 1020, 32, 3, 3, 1, 1), wl.BF16),
     # many small images, 1.53 GB in all: the Winograd kernels' domain (input below 2 GiB including their look-ahead)
     (ConvShape(1900, 64, 56, 56, 32, 3, 3, 1, 1), wl.F32),
+    # input and output just below 2 GiB less what the fp32 window kernels on split products reach beyond a tensor with their spare channels
+    (ConvShape(2673, 64, 56, 56, 40, 3, 3, 1, 1), wl.F32),
+    (ConvShape(7169, 8, 24, 24, 130, 3, 3, 1, 1), wl.F32),
 ]
 
 

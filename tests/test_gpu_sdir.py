@@ -23,6 +23,10 @@ SHAPES = [
     ConvShape(2, 24, 33, 21, 100, 5, 5, 2, 1),  # a border smaller than the window needs to keep its size
     ConvShape(1, 64, 57, 55, 48, 3, 3, 1, 1),   # wide rows
     ConvShape(1, 20, 9, 8, 32, 5, 5, 4, 4),     # the largest stride and border, fewer rows than a tile spans
+    ConvShape(2, 137, 9, 7, 70, 5, 5, 1, 2),    # every form: two rounds of channels or more, in the last one some of the waves without any
+    ConvShape(2, 137, 9, 7, 70, 3, 3, 1, 1),
+    ConvShape(3, 273, 7, 7, 33, 5, 5, 1, 2),    # three rounds of eight waves
+    ConvShape(3, 273, 9, 11, 65, 3, 3, 2, 1),
 ]
 
 
@@ -126,6 +130,29 @@ def test_no_less_precise_than_the_split_window_kernel_it_replaces(shape):
         err = error(vi)
         print(name, "%.3g %.3g" % (err, split), flush=True)
         assert err <= split, name
+
+
+@pytest.mark.parametrize("kind", ["corners", "filter", "infinities"])
+@pytest.mark.parametrize("si", [1, 2, 3, 5, 9])
+def test_sums_again_under_the_activation(si, kind):
+    """A sum that is a NaN or -infinity is dropped by the activation, +infinity is not; channels and pixels past the last ones are not stored."""
+    shape = SHAPES[si]
+    x = wl.draw(("normal", 1.0), shape.in_shape(), 4692).astype(np.float32)
+    f = wl.draw(("normal", wl.he_sigma(shape)), shape.filt_shape(), 4693).astype(np.float32)
+    if kind == "corners":
+        x[0, 0, 0, 0], x[-1, -1, -1, -1], x[-1, 3, 0, -1], x[0, 5, -1, 0] = np.nan, np.inf, -np.inf, np.nan
+    elif kind == "filter":
+        f[shape.K // 2, 1, 2, 0], f[-1, -1, 0, 1] = np.nan, -np.inf
+    else:
+        x[0] = np.inf
+    case = DeviceCase(shape, wl.F32, {"in": x, "filt": f, "bias": wl.draw(("normal", 0.1), (shape.K,), 4691).astype(np.float32)}, relu=True)
+    with np.errstate(all="ignore"):
+        ref = case.ref()
+    finite = np.isfinite(ref)
+    for vi, name in variants_of(case):
+        got = to_host_f64(case.run(variant=vi), wl.F32)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)]), name
+        assert oracle.max_normalised_error(got[finite], ref[finite]) <= TOL[wl.F32], name
 
 
 # The largest time allowed, in calls on ordinary data; measured with a wave for each output and with pixels that share a wave

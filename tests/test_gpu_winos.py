@@ -203,6 +203,7 @@ def test_operands_at_the_lower_end_of_the_range(xs, fs):
 
 @pytest.mark.parametrize("shape,dtype", [
     (ConvShape(24, 640, 14, 14, 1024, 3, 3, 1, 1), wl.F32),   # split filters of 63 MB
+    (ConvShape(1, 512, 20, 20, 640, 5, 5, 1, 2), wl.F32),     # ... of 49 MB, of the direct window kernel
     # (40 images of 64x56x128 -> 32 and 39 of 28x26x944 -> 10 stood here while the selection was held to kernels with an input copy;
     # the kernel that is faster there, 25 against 31 and 44 against 57 us, needs no scratch)
     # (96 images of 56x56x64 -> 192 stood here while the selection was held to the copy above 32 MiB of input.  The form that reads the input

@@ -1,5 +1,7 @@
 """Host side of the fp32 window kernels on split products (CPU only): how the row-of-planes Winograd kernel deals its tiles, which layers
-either kernel accepts at the upper end of the library's range, and what the benchmark rates kernels on split products by."""
+either kernel accepts at the upper end of the library's range, which of the direct kernel's forms the GPU tests reach, and what the benchmark
+rates kernels on split products by."""
+import re
 import subprocess
 
 import pytest
@@ -86,6 +88,21 @@ def test_outputs_stay_below_2_gib_with_the_spare_channels_of_a_tile(prefix, spar
     most = (((1 << 31) - 1) // (4 * H * H) - spare) // K
     assert forms(ConvShape(most, 8, H, H, K, R, R, 1, R // 2), prefix)
     assert not forms(ConvShape(most + 1, 8, H, H, K, R, R, 1, R // 2), prefix) and names_of(ConvShape(most + 1, 8, H, H, K, R, R, 1, R // 2))
+
+
+def test_parity_shapes_reach_every_form_of_the_direct_kernel():
+    """Each form runs a layer of two rounds of channels and more, and one whose last round leaves some of its waves without channels."""
+    from test_gpu_sdir import SHAPES
+
+    rounds, ragged = {}, set()
+    for s in SHAPES:
+        for n in forms(s, "sdir_"):
+            split, chunks = int(re.search(r"k(\d+)_s", n).group(1)), -(-s.C // 16)
+            rounds[n] = max(rounds.get(n, 0), -(-chunks // split))
+            if chunks > split and chunks % split:
+                ragged.add(n)
+    assert len(rounds) == 14 and min(rounds.values()) >= 2, rounds
+    assert ragged == {n for n in rounds if "k1_" not in n}, set(rounds) - ragged
 
 
 @pytest.mark.parametrize("variant,shape,executed", [
