@@ -211,3 +211,38 @@ def test_3x3_layers_go_to_split_products_where_they_are_faster(shape, split):
     name, nows = picks(shape, wl.F32)
     assert name.startswith("winos_" if split else "wino_"), name
     assert not nows.startswith("winos_"), nows
+
+
+# fp32 5x5 and strided 3x3 layers with a workspace: us of the fastest other kernel (or of the one that was taken), of the direct kernel on split products
+@pytest.mark.parametrize("shape,direct", [
+    (ConvShape(43, 160, 6, 9, 32, 5, 5, 1, 2), True),      # 31.1, 18.8: taken with a start above zero for this form
+    (ConvShape(17, 160, 9, 7, 32, 5, 5, 1, 2), True),      # 31.3, 18.7: ... and this
+    (ConvShape(1, 160, 17, 20, 49, 5, 5, 1, 2), True),     # 31.2, 21.1: ... and this
+    (ConvShape(50, 424, 14, 14, 96, 5, 5, 1, 2), True),    # 234, 115
+    (ConvShape(36, 32, 41, 39, 49, 5, 5, 1, 2), True),     # 63, 35
+    (ConvShape(4, 496, 7, 10, 104, 5, 5, 1, 2), True),     # 55, 41
+    (ConvShape(13, 112, 35, 33, 352, 3, 3, 2, 1), True),   # 41, 37
+    (ConvShape(16, 19, 10, 13, 32, 3, 3, 2, 1), False),    # 7.0, 8.7
+    (ConvShape(5, 440, 18, 18, 112, 3, 3, 2, 1), False),   # 21.7, 32.7
+    (ConvShape(2, 432, 41, 41, 48, 3, 3, 2, 1), False),    # 21.3, 41.2
+    (ConvShape(1, 432, 64, 62, 48, 5, 5, 1, 2), False),    # 69, 125
+    (ConvShape(1, 16, 23, 23, 352, 5, 5, 1, 2), False),    # 6.1, 10.6
+])
+def test_5x5_and_strided_layers_go_to_the_direct_kernel_where_it_is_faster(shape, direct):
+    name, nows = picks(shape, wl.F32)
+    assert name.startswith("sdir_") == direct, name
+    assert not nows.startswith(("sdir_", "winos_")), nows
+
+
+# split Winograd by 64 channels x 64 tiles, a row of planes per wave, or by fewer: us of the best of either
+@pytest.mark.parametrize("shape,wide", [
+    (ConvShape(64, 64, 56, 56, 192, 3, 3, 1, 1), True),    # 160, 182
+    (ConvShape(16, 128, 28, 28, 256, 3, 3, 1, 1), True),   # 34.4, 40.6
+    (ConvShape(23, 128, 28, 28, 128, 3, 3, 1, 1), True),   # 30.0, 38.8
+    (ConvShape(20, 256, 13, 13, 384, 3, 3, 1, 1), False),  # 36.6, 35.1
+    (ConvShape(13, 128, 14, 14, 384, 3, 3, 1, 1), False),  # 25.0, 19.7
+])
+def test_many_tiles_of_split_winograd_go_to_the_row_of_planes_kernel(shape, wide):
+    name, nows = picks(shape, wl.F32)
+    assert name.startswith("winos_") and name.startswith("winos_f32_M64T64_") == wide, name
+    assert not nows.startswith(("sdir_", "winos_")), nows
