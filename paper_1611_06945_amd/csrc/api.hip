@@ -276,10 +276,12 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
     if (v.traits & TRAIT_SPLIT_DIRECT) {
         // The filters' launch, then per round of workgroups (the last one as long as its fullest CU makes it) a start and chunks of
         // channels, of which a share goes with the positions that are staged.  Constants per tile shape: a fit to 8500 measured calls of
-        // 1840 drawn layers (rms 4 to 8 %, 6 to 11 % at 3x3).  The implicit GEMMs beside it are rated less closely, which 3x3 pays for with a factor: over
-        // 343 other layers the picks take, at 5x5, 0.71 of what they took (72 of 103 moved, at 0.61, none more than 5 % slower; 1.03 of the
-        // fastest kernel's time, 1.46 before), at 3x3 stride 2 and 1 0.97 each (rated as they are 12 and 4 of 120 were more than 5 % slower, with 1.15
-        // and 1.08 3 each).  us: 50 images of 14x14x424 -> 96 5x5 239, 119
+        // 1840 drawn layers (rms 4 to 8 %, 6 to 11 % at 3x3).  Over 2476 other layers, every kernel timed, against the pick without this kernel and
+        // the row-of-planes Winograd: 5x5, 375 of 482 picks moved, at 0.61 of their time, 12 of them more than 5 % slower (1.24 at most), all
+        // picks at 0.68 of their time and 1.03 of the fastest kernel's (1.52 before); 3x3 stride 2, 86 of 461 at 0.85, 8 slower (1.31), all 0.97 and 1.03
+        // (1.06); stride 1, 278 of 1533 here, 23 slower (1.25), with the 126 of Winograd 0.96 and 1.07 (1.12).  The implicit GEMMs beside it are rated less
+        // closely, which 3x3 pays for with a factor.  Where more than 5 % is lost, and all picks: stride 2, 1.1 26, 0.975, 1.2 8, 0.971, 1.3 4, 0.973;
+        // stride 1, 1.0 106, 0.961, 1.1 23, 0.960, 1.2 5, 0.966.  us: 50 images of 14x14x424 -> 96 5x5 239, 119
         const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(P / (double)v.tn), chunks = std::ceil(Q / v.tk);
         const double slots = 256.0 * v.per_cu, full = std::floor(wgs / slots), rest = std::ceil((wgs - full * slots) / 256.0);
         const double rounds = full * std::pow((double)v.per_cu, (double)v.model.grow) + (rest > 0.0 ? std::pow(rest, (double)v.model.grow) : 0.0);
@@ -296,8 +298,8 @@ double heuristic_cost(const Variant& v, const conv_desc& d, int OH, int OW)
         const double tiles = (double)d.N * std::ceil(OH / 2.0) * std::ceil(OW / 2.0), cus = 256.0 * v.per_cu;
         const double wgs = std::ceil(d.K / (double)v.tm) * std::ceil(tiles / (v.tn / 4.0));
         double rounds = std::ceil(wgs / cus) * std::min((double)v.per_cu, std::ceil(wgs / 256.0));
-        // (64 tiles a workgroup: a last round that is at most half full is of halved tiles.  91 of 700 drawn layers moved to that form, at 0.84 of
-        // their time, none more than 5 % slower)
+        // (64 tiles a workgroup: a last round that is at most half full is of halved tiles.  126 of 1533 drawn 3x3 layers moved to that form, at 0.86
+        // of their time, none more than 5 % slower)
         const double rest = wgs - 256.0 * std::floor(wgs / 256.0);
         if (v.model.grow > 0.0f && rest > 0.0 && rest <= 128.0) rounds = std::floor(wgs / 256.0) + v.model.grow;
         return v.model.call + 5.1e-5 * (double)d.K * d.C + rounds * (v.model.own + std::ceil(d.C / 16.0) * v.model.chunk);
