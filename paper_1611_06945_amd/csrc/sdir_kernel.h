@@ -10,16 +10,16 @@
 //     1.3e-7, 2 of 40x40x176 -> 16 3.7e-7 -> 1.2e-7 (the implicit GEMM split eight ways 4.7e-7, 3.6e-7), 29 of 44x44x304 -> 112 3x3 stride 2 3.3e-7 -> 1.1e-7
 //     (that one 3.5e-7), 20 of 13x13x256 -> 96 3x3 2.8e-7 -> 1.0e-7 (the fp32 window kernel split four ways 2.2e-7), for up to 1 % of the time where
 //     it is the fastest (17 of 33x33x416 -> 64 5x5 186.5 -> 188.2 us, 5 of 28x31x224 -> 256 107.1 -> 108.4, 48 of 63x66x128 -> 27 3x3 103.8 -> 104.7).  Waves that
-//     split the channels: 1.0e-7 to 5.2e-7.  Over 302 drawn layers whose untuned pick moved here the error is
-//     0.45 of the former pick's (geometric mean; 0.96 at most).
+//     split the channels: 1.0e-7 to 5.2e-7.  Over 303 drawn layers whose untuned pick moved here the error is 0.34 of the former pick's (geometric
+//     mean; 0.72 at most), over 382 that a tuned call moves 0.41 of the fastest other kernel's (0.72 at most).
 //   * A small kernel ahead splits the filters into MFMA operand order; fragments come from L2 straight into registers.
 //   * Input is read four bytes a lane (any row length, border and stride), split and stored as [part][eight channels][position], rows
 //     of the window stacked over images; a lane's window is one address, a tap an offset.  Only positions that the tile has are staged.
 //   * Tiles of 128 pixels with four waves side by side for layers that fill the chip; for smaller ones the waves split the channels,
 //     with a slab each and, where a wave has its own, no barrier in the loop.
 // What bounds it: at 5x5 the matrix units (50 images of 14x14x424 -> 96: 120 GFLOP of bf16 products in 115 us); at 3x3 the
-// staging of a chunk, 1700 clocks of loads and 1800 of splits and stores beside 3500 of products, under which two workgroups of a CU lie
-// for each other; for layers of few chunks the start, 5800 clocks, and the filters' launch, 3 us.  Rows of a 5x5 window are a loop:
+// staging of a chunk, 2200 clocks of loads and 2200 to 2900 of splits and stores beside 3900 to 4900 of products, under which two workgroups of a
+// CU lie for each other; for layers of few chunks the start, 6000 clocks, and the filters' launch, 3 us and more.  Rows of a 5x5 window are a loop:
 // laid out, a layer of few chunks waited for its instructions (this kernel by itself, 16x16x88 -> 49 11.1 -> 9.3 us, 36 of 41x39x32 -> 49 35.4 -> 32.5).
 // Measured, us per call in one run, the fastest of the other kernels -> the fastest of this one: 36 images of 41x39x32 -> 49 5x5 63 -> 35, 4 of
 // 7x10x496 -> 104 55 -> 41, 50 of 14x14x424 -> 96 234 -> 115, 13 of 35x33x112 -> 352 3x3 stride 2 41 -> 37.

@@ -17,12 +17,13 @@
 //   * Workgroups take tile after tile, one per CU; a last round with tiles for no more than half of the workgroups halves them (winow_deal.h).  us a
 //     call of fewer than 128 tiles, halved on XCDs that happened to have two workgroups for each -> on all: 17 of 13x13x256 -> 384 (84 tiles) 50.5 ->
 //     37.0, 27 of 28x28x128 -> 64 (83) 28.4 -> 20.7, 8 of 56x56x64 -> 64 (98) 20.7 -> 16.0, 19 of 28x28x128 -> 128 (118) 30.7 -> 23.3.
-// What bounds it: instruction issue.  A step is 96 MFMAs (3100 clocks) among 900 instructions, 4400 clocks; vector loads cost 25 to 30
-// clocks of issue each.  Per tile the epilogue takes 7700, addresses 2500, a workgroup's start 9000 once.  On the layer below the
-// clock falls to 1.94 GHz (2.23 with filters of zeros): the power limit is near.
+// What bounds it: instruction issue.  A step is 96 MFMAs (3100 clocks) among 900 instructions, 4200 clocks on rows of 28 pixels, 5000 on rows of 56;
+// vector loads cost 25 to 30 clocks of issue each.  Per tile the epilogue takes 7700, the next tile's addresses 2500, a workgroup's start 7300 to
+// 8300 once.  On the layer below the clock falls to 1.94 GHz (2.23 with filters of zeros): the power limit is near.
 // Measured (us per call, other inputs each time, filter transform included, winos_kernel's best -> here, same box in turn): 64 images of 56x56x64 ->
-// 192 182 -> 160, 16 of 28x28x128 -> 256 40.6 -> 34.4, 33 of 28x28x128 -> 192 48.9 -> 47.4; 20 of 13x13x256 -> 384, 96 tiles, 35.6 -> 37.0
-// (not taken).  Of 900 drawn layers 165 have 100 and more tiles; it is the fastest for 109 of them, there at 0.87 of the best time before.
+// 192 182 -> 160, 16 of 28x28x128 -> 256 40.6 -> 34.4, 33 of 28x28x128 -> 192 48.9 -> 47.4; 20 of 13x13x256 -> 384, 96 tiles, 35.1 -> 36.6
+// (not taken).  Of 754 drawn layers 177 have 100 and more tiles; it is the fastest for 100 of them, there at 0.89 of the best time before (winos_kernel and
+// the kernels ahead of it), and for 14 of 42 with 64 to 99, at 0.94.
 // Tried: eight waves, a block of tiles each (225 us: the filters' loads twice over, 64 bytes a clock and CU); planes to LDS as
 // they stand, without the columns' sums (11300 clocks an epilogue against 9600: LDS takes 64 bytes a clock); eight groups of filters ahead
 // instead of four, and v_dot2_f32_bf16 for what a part leaves (no faster, a fifth slower).
