@@ -239,6 +239,11 @@ def test_5x5_and_strided_layers_go_to_the_direct_kernel_where_it_is_faster(shape
     (ConvShape(64, 64, 56, 56, 192, 3, 3, 1, 1), True),    # 160, 182
     (ConvShape(16, 128, 28, 28, 256, 3, 3, 1, 1), True),   # 34.4, 40.6
     (ConvShape(23, 128, 28, 28, 128, 3, 3, 1, 1), True),   # 30.0, 38.8
+    (ConvShape(27, 128, 28, 28, 64, 3, 3, 1, 1), True),    # 20.7, 23.2: 83 halved tiles
+    (ConvShape(8, 64, 56, 56, 64, 3, 3, 1, 1), True),      # 16.0, 17.6
+    (ConvShape(19, 128, 28, 28, 128, 3, 3, 1, 1), True),   # 23.3, 25.6
+    (ConvShape(4, 64, 33, 33, 304, 3, 3, 1, 1), True),     # 18.2, 20.5
+    (ConvShape(17, 256, 13, 13, 384, 3, 3, 1, 1), False),  # 37.0, 34.1
     (ConvShape(20, 256, 13, 13, 384, 3, 3, 1, 1), False),  # 36.6, 35.1
     (ConvShape(13, 128, 14, 14, 384, 3, 3, 1, 1), False),  # 25.0, 19.7
 ])
